@@ -391,88 +391,97 @@ __device__ __forceinline__ void pt50_cvt(const Pt50Raw<CPT>& r, int k, double (&
 }
 
 
-// One block's (tile, k-chunk, limb): sums over the n_ai rotated inputs of plaintext x input,
-// for `rows` output rows of the tile (FULL: rows == TB, no row clamping).
-template <int TB, int CPT, int UNR, bool FULL, bool P50>
-__device__ __forceinline__ void cp_mac_tile(const uint8_t* __restrict__ pbase, const uint64_t* const* __restrict__ rx_tab,
-                                            size_t pt_stride_bj, size_t pt_stride_ai, int n, int nl, int n_ai, int limb, int k0, int rows,
-                                            double q, double qi, double (&a0)[TB][CPT], double (&a1)[TB][CPT]) {
+// One block's (tile, k-chunk, limb): WAVES waves, each TB output rows x 64 CPT coefficients.
+// Bound by HBM (the plaintexts are read once; 7 FP64 instructions per word and poly take a third
+// of the issue slots).  What the shape decides is how evenly the stream is spread: every block
+// runs as long as its n_ai terms take, so a grid of a few blocks per CU is as slow as the CU that
+// got one more.  One-wave blocks (64 threads) spread best; 256-thread blocks of the same tile left
+// 3 blocks on some CUs and 2 on others.  SPLIT > 1 divides the terms over the waves of a block
+// (their sums meet in LDS), for grids too small to keep enough loads in flight.
+// Words of the next term are loaded before the current term is multiplied.  Rows past a partial
+// last tile re-read its last row (not stored), so the body has no branches.
+template <int TB, int CPT, int SPLIT, int WAVES, bool P50>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2))) void k_cp_mac(
+    const uint64_t* __restrict__ pt, const uint64_t* const* __restrict__ rx_tab, uint64_t* __restrict__ inner, int n, int nl, int n_ai,
+    int n_bj, ModTable mt, int n_kblk) {
+  static_assert(CPT == 2 || CPT == 4, "coefficients per thread");
+  static_assert(SPLIT == 1 || SPLIT == WAVES, "every wave of a split block has its own terms");
   typedef __attribute__((address_space(1))) const uint64_t gu64;
   typedef __attribute__((address_space(1))) const u64x2 gu64x2;
-  // STREAM: non-temporal loads (the plaintexts, read once); the rotated inputs, re-read by
-  // every tile, stay cached.  A compile-time choice: a select between the two forms of the load
-  // is merged into one plain load by the optimizer, which drops the non-temporal hint.
-  auto load2 = [&](auto stream, gu64* a, double (&v)[CPT]) {
-    constexpr bool STREAM = decltype(stream)::value;
-    if constexpr (CPT >= 2) {
+  constexpr int LANES = 64 * WAVES / SPLIT;  // work-items over the coefficients
+  // Block order: k-chunk fastest, then limb, then output tile.  Consecutive blocks stream
+  // consecutive pieces of one plaintext limb-poly (the dispatcher deals them round-robin over the
+  // 8 XCDs), and the blocks of one (k-chunk, limb) -- the ones reading the same rotated-input
+  // words -- lie n_kblk * nl apart, a multiple of 8 whenever n_kblk is: one XCD, one L2.
+  const int kb = blockIdx.x % n_kblk;
+  const int limb = (blockIdx.x / n_kblk) % nl;
+  const int tile = blockIdx.x / (n_kblk * nl);
+  const int part = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / LANES) : 0;
+  const int lane = threadIdx.x % LANES;
+  const int k0 = (kb * LANES + lane) * CPT;
+  const ModEntry me = mt.m[limb];
+  const double q = me.q, qi = me.qinv;
+  const int bj0 = tile * TB;
+  const int rows = min(TB, n_bj - bj0);
+  const int ai0 = n_ai * part / SPLIT, ai1 = n_ai * (part + 1) / SPLIT;  // this wave's terms (none if n_ai < SPLIT)
+  const size_t pb = pt_poly_bytes(n, P50);
+  const size_t stride_ai = (size_t)nl * pb, stride_bj = (size_t)n_ai * stride_ai;
+  const uint8_t* pbase = (const uint8_t*)pt + (size_t)bj0 * stride_bj + (size_t)limb * pb;
+  size_t row[TB];
 #pragma unroll
-      for (int h = 0; h < CPT; h += 2) {
-        u64x2 w;
-        if constexpr (STREAM) w = __builtin_nontemporal_load((gu64x2*)(a + h));
-        else w = *(gu64x2*)(a + h);
-        v[h] = u2d(w.x);
-        v[h + 1] = u2d(w.y);
+  for (int t = 0; t < TB; ++t) row[t] = (size_t)min(t, rows - 1) * stride_bj;
+  Pt50Raw<CPT> w50[TB];
+  u64x2 w64[TB][CPT / 2], r0[CPT / 2], r1[CPT / 2];
+  auto fetch = [&](int ai) {
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      const uint8_t* poly = pbase + row[t] + (size_t)ai * stride_ai;
+      if constexpr (P50) {
+        pt50_fetch<CPT>(poly, n, k0, w50[t]);
+      } else {  // non-temporal: the plan is read once, the rotated inputs by every tile
+#pragma unroll
+        for (int h = 0; h < CPT / 2; ++h) w64[t][h] = __builtin_nontemporal_load((gu64x2*)((gu64*)poly + k0 + 2 * h));
       }
-    } else {
-      if constexpr (STREAM) v[0] = u2d(__builtin_nontemporal_load(a));
-      else v[0] = u2d(*a);
     }
-  };
-  using kStream = std::true_type;
-  using kCached = std::false_type;
-  // Row pointers: the rows past a partial tile's last re-read that row, so every row of the
-  // body runs unconditionally (branch-free, loads of all rows in flight together); their sums
-  // are never stored.
-  const uint8_t* rowp[TB];
+    gu64* rx = (gu64*)rx_tab[ai];
 #pragma unroll
-  for (int t = 0; t < TB; ++t) rowp[t] = pbase + (size_t)(FULL ? t : min(t, rows - 1)) * pt_stride_bj;
-  // poly: the (tile row, term) plaintext limb-poly
-  auto load_pt = [&](const uint8_t* poly, double (&v)[CPT]) {
-    if constexpr (P50) {
-      Pt50Raw<CPT> r;
-      pt50_fetch<CPT>(poly, n, k0, r);
-      pt50_cvt<CPT>(r, k0, v);
-    } else {
-      load2(kStream{}, (gu64*)poly + k0, v);
+    for (int h = 0; h < CPT / 2; ++h) {
+      r0[h] = *(gu64x2*)(rx + (size_t)limb * n + k0 + 2 * h);
+      r1[h] = *(gu64x2*)(rx + (size_t)(nl + limb) * n + k0 + 2 * h);
     }
   };
-  auto reduce_all = [&]() {
+  double a0[TB][CPT], a1[TB][CPT];
+#pragma unroll
+  for (int t = 0; t < TB; ++t)
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) a0[t][c] = a1[t][c] = 0.0;
+  auto reduce_all = [&] {
 #pragma unroll
     for (int t = 0; t < TB; ++t)
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) { a0[t][c] = reduce_s(a0[t][c], q, qi); a1[t][c] = reduce_s(a1[t][c], q, qi); }
+      for (int c = 0; c < CPT; ++c) {
+        a0[t][c] = reduce_s(a0[t][c], q, qi);
+        a1[t][c] = reduce_s(a1[t][c], q, qi);
+      }
   };
-  int ai = 0;
-  for (; ai + UNR <= n_ai; ai += UNR) {
-    double x0[UNR][CPT], x1[UNR][CPT], w[UNR][TB][CPT];
+  if (ai0 < ai1) fetch(ai0);
+  for (int ai = ai0; ai < ai1; ++ai) {
+    double w[TB][CPT], x0[CPT], x1[CPT];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      gu64* rx = (gu64*)rx_tab[ai + u];
-      load2(kCached{}, rx + (size_t)limb * n + k0, x0[u]);
-      load2(kCached{}, rx + (size_t)(nl + limb) * n + k0, x1[u]);
+    for (int t = 0; t < TB; ++t) {
+      if constexpr (P50) {
+        pt50_cvt<CPT>(w50[t], k0, w[t]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) w[t][c] = u2d((c & 1) ? w64[t][c / 2].y : w64[t][c / 2].x);
+      }
     }
 #pragma unroll
-    for (int u = 0; u < UNR; ++u)
-#pragma unroll
-      for (int t = 0; t < TB; ++t) load_pt(rowp[t] + (size_t)(ai + u) * pt_stride_ai, w[u][t]);
-#pragma unroll
-    for (int u = 0; u < UNR; ++u)
-#pragma unroll
-      for (int t = 0; t < TB; ++t)
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-          a0[t][c] += mulmod_s(w[u][t][c], x0[u][c], q, qi);
-          a1[t][c] += mulmod_s(w[u][t][c], x1[u][c], q, qi);
-        }
-    if (((ai + UNR) & 7) == 0) reduce_all();  // every 8 terms: |acc| stays below 2^53
-  }
-  for (; ai < n_ai; ++ai) {
-    double x0[CPT], x1[CPT], w[TB][CPT];
-    gu64* rx = (gu64*)rx_tab[ai];
-    load2(kCached{}, rx + (size_t)limb * n + k0, x0);
-    load2(kCached{}, rx + (size_t)(nl + limb) * n + k0, x1);
-#pragma unroll
-    for (int t = 0; t < TB; ++t) load_pt(rowp[t] + (size_t)ai * pt_stride_ai, w[t]);
+    for (int c = 0; c < CPT; ++c) {
+      x0[c] = u2d((c & 1) ? r0[c / 2].y : r0[c / 2].x);
+      x1[c] = u2d((c & 1) ? r1[c / 2].y : r1[c / 2].x);
+    }
+    fetch(min(ai + 1, ai1 - 1));  // the last term re-reads itself
 #pragma unroll
     for (int t = 0; t < TB; ++t)
 #pragma unroll
@@ -480,45 +489,32 @@ __device__ __forceinline__ void cp_mac_tile(const uint8_t* __restrict__ pbase, c
         a0[t][c] += mulmod_s(w[t][c], x0[c], q, qi);
         a1[t][c] += mulmod_s(w[t][c], x1[c], q, qi);
       }
-    if ((ai & 7) == 7) reduce_all();
+    if (((ai - ai0) & 7) == 7) reduce_all();  // 8 products below 0.875 q on |acc| <= q/2: |acc| < 7.5 q < 2^53
   }
-}
-
-// SPLIT: full tiles run a body without row clamping (separately compiled from the clamped
-// body of the last, partial tile); otherwise the clamped body serves every tile.
-template <int TB, int CPT, int UNR, bool SPLIT, bool P50>
-__global__ __launch_bounds__(256) void k_cp_mac(const uint64_t* __restrict__ pt, const uint64_t* const* __restrict__ rx_tab,
-                                                uint64_t* __restrict__ inner, int n, int nl, int n_ai, int n_bj, ModTable mt, int n_kblk,
-                                                int n_tiles) {
-  static_assert(CPT == 1 || CPT == 2 || CPT == 4, "coefficients per thread");
-  static_assert(UNR == 1 || UNR == 2, "unroll of the input loop");
-  // Block order: k-chunk fastest, then limb, then output tile.  Consecutive blocks stream
-  // consecutive 4 KB pieces of one plaintext limb-poly (the dispatcher deals them round-robin
-  // over the 8 XCDs), and the blocks of one (k-chunk, limb) -- the ones reading the same
-  // rotated-input words -- lie n_kblk * nl apart, a multiple of 8 whenever n_kblk is: one XCD,
-  // one L2.  (A tile-fastest order with those readers adjacent on one XCD misses L2 less often
-  // but ran 4-5 % slower on the BERT-base operator.)
-  const int kb = blockIdx.x % n_kblk;
-  const int limb = (blockIdx.x / n_kblk) % nl;
-  const int tile = blockIdx.x / (n_kblk * nl);
-  (void)n_tiles;
-  const int k0 = (kb * 256 + threadIdx.x) * CPT;
-  if (k0 >= n) return;
-  const ModEntry me = mt.m[limb];
-  const double q = me.q, qi = me.qinv;
-  const int bj0 = tile * TB;
-  const int rows = min(TB, n_bj - bj0);
-  double a0[TB][CPT], a1[TB][CPT];
+  if constexpr (SPLIT > 1) {
+    __shared__ double part_sum[SPLIT - 1][2 * TB * CPT][LANES];
+    reduce_all();
+    if (part > 0) {
 #pragma unroll
-  for (int t = 0; t < TB; ++t)
+      for (int t = 0; t < TB; ++t)
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) { a0[t][c] = 0.0; a1[t][c] = 0.0; }
-  const size_t pb = pt_poly_bytes(n, P50);
-  const size_t pt_stride_ai = (size_t)nl * pb, pt_stride_bj = (size_t)n_ai * pt_stride_ai;
-  const uint8_t* pbase = (const uint8_t*)pt + (size_t)bj0 * pt_stride_bj + (size_t)limb * pb;
-  if (SPLIT && rows == TB)
-    cp_mac_tile<TB, CPT, UNR, true, P50>(pbase, rx_tab, pt_stride_bj, pt_stride_ai, n, nl, n_ai, limb, k0, rows, q, qi, a0, a1);
-  else cp_mac_tile<TB, CPT, UNR, false, P50>(pbase, rx_tab, pt_stride_bj, pt_stride_ai, n, nl, n_ai, limb, k0, rows, q, qi, a0, a1);
+        for (int c = 0; c < CPT; ++c) {
+          part_sum[part - 1][t * CPT + c][lane] = a0[t][c];
+          part_sum[part - 1][(TB + t) * CPT + c][lane] = a1[t][c];
+        }
+    }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int s = 0; s < SPLIT - 1; ++s)
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+          a0[t][c] += part_sum[s][t * CPT + c][lane];
+          a1[t][c] += part_sum[s][(TB + t) * CPT + c][lane];
+        }
+  }
 #pragma unroll
   for (int t = 0; t < TB; ++t) {
     if (t < rows) {
@@ -533,42 +529,70 @@ __global__ __launch_bounds__(256) void k_cp_mac(const uint64_t* __restrict__ pt,
   }
 }
 
-// Tuning knob (does not change any result bit): outputs per block x coefficients per thread
-// x unroll of the input loop x split full / partial tiles.
+// Launch shapes {outputs per wave, coefficients per work-item, waves the terms are divided over,
+// waves per block}; none changes a result bit.  Shape 0 is chosen by the size of the product.
+struct MacShape {
+  int tb, cpt, split, waves;
+};
+constexpr MacShape kMacShapes[BLB_MAC_VARIANTS] = {
+    {0, 0, 0, 0}, {12, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 2, 2}, {4, 2, 4, 4}, {2, 2, 4, 4}, {8, 4, 1, 4}, {4, 4, 1, 1}, {4, 4, 2, 2},
+    {6, 4, 1, 1}, {6, 2, 1, 1}, {4, 2, 1, 1}, {4, 2, 2, 2}, {8, 2, 1, 4}, {4, 2, 1, 4}, {12, 2, 1, 4}, {6, 4, 1, 4}, {4, 4, 1, 4}};
+
+// The shape of a product, by the waves that its outputs give at 8 rows x 2 (64-bit words) or 4 rows
+// x 4 (50-bit) coefficients per work-item.  Measured alone, us of the shape taken against its
+// neighbour: 64-bit words, 2304 waves (n_ai 192, n_bj 96, 3 limbs, N = 8192): {12,2,1,1} 540, {8,2,1,1}
+// 609 (the 256-thread {8,2,1,4}: 682); 1728 waves: {8,2,1,1} 401, {8,2,2,2} 429; 960: {8,2,2,2} 130,
+// {8,2,1,1} 139; 576: 245 against 373; 384: {4,2,4,4} 15.2, {8,2,2,2} 19.8; 128: {2,2,4,4} 12.4, {8,2,2,2} 23.
+// 50-bit words, 16384 waves: {8,4,1,4} 2386 (5.6 TB/s of packed words), {4,4,1,1} 2814; 2304: {4,4,1,1} 552,
+// {8,4,1,4} 670; 1728: {4,4,1,1} 363, {4,4,2,2} 419; 960: {4,4,2,2} 119, {4,4,1,1} 154; 384: {4,2,4,4} 15.4,
+// {4,4,2,2} 22; 128: {2,2,4,4} 12.6, {4,2,4,4} 14.2.  12 rows only where they pad the outputs by little.
+MacShape mac_shape_for(int n, int nl, int n_bj, int p50) {
+  const int64_t cols = (int64_t)n * nl;
+  if (p50) {
+    const int64_t waves = cols / 256 * ((n_bj + 3) / 4);
+    if (waves >= 4096) return kMacShapes[6];
+    if (waves >= 1536) return kMacShapes[7];
+    if (waves >= 640) return kMacShapes[8];
+    return kMacShapes[waves >= 256 ? 4 : 5];
+  }
+  const int64_t waves = cols / 128 * ((n_bj + 7) / 8);
+  const int pad12 = (n_bj + 11) / 12 * 12, pad8 = (n_bj + 7) / 8 * 8;
+  if (waves >= 2048 && pad12 * 16 <= pad8 * 17) return kMacShapes[1];
+  if (waves >= 1536) return kMacShapes[2];
+  if (waves >= 512) return kMacShapes[3];
+  return kMacShapes[waves >= 256 ? 4 : 5];
+}
+
 void launch_cp_mac(blb_ctx* c, const uint64_t* pt, const uint64_t* const* rx_tab, uint64_t* inner, int nl, int n_ai, int n_bj, int variant,
                    int p50) {
-  struct Shape { int tb, cpt; };
-  static const Shape shapes[BLB_MAC_VARIANTS] = {{8, 2}, {8, 1}, {16, 2}, {4, 2}, {12, 2}, {2, 2}, {4, 2}, {2, 2}, {4, 1}, {4, 1},
-                                                 {4, 2}, {4, 2}, {8, 1}, {4, 1}, {2, 4}, {4, 4}, {2, 4}, {4, 4}};
-  const Shape sh = shapes[(variant >= 0 && variant < BLB_MAC_VARIANTS) ? variant : 0];
-  const int n_kblk = c->n / (256 * sh.cpt);
-  const int n_tiles = (n_bj + sh.tb - 1) / sh.tb;
-  const int blocks = n_kblk * nl * n_tiles;
-#define CPMAC(tb, cpt, unr, split)                                                                                                 \
-  do {                                                                                                                             \
-    if (p50) k_cp_mac<tb, cpt, unr, split, true><<<blocks, 256, 0, c->stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk, n_tiles); \
-    else k_cp_mac<tb, cpt, unr, split, false><<<blocks, 256, 0, c->stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk, n_tiles); \
-  } while (0)
-  switch (variant) {
-    case 1: CPMAC(8, 1, 1, false); break;
-    case 2: CPMAC(16, 2, 1, false); break;
-    case 3: CPMAC(4, 2, 1, false); break;
-    case 4: CPMAC(12, 2, 1, false); break;
-    case 5: CPMAC(2, 2, 1, false); break;
-    case 6: CPMAC(4, 2, 2, false); break;
-    case 7: CPMAC(2, 2, 2, false); break;
-    case 8: CPMAC(4, 1, 1, false); break;
-    case 9: CPMAC(4, 1, 2, false); break;
-    case 10: CPMAC(4, 2, 2, true); break;
-    case 11: CPMAC(4, 2, 1, true); break;
-    case 12: CPMAC(8, 1, 1, true); break;
-    case 13: CPMAC(4, 1, 2, true); break;
-    case 14: CPMAC(2, 4, 1, false); break;
-    case 15: CPMAC(4, 4, 1, false); break;
-    case 16: CPMAC(2, 4, 1, true); break;
-    case 17: CPMAC(4, 4, 1, true); break;
-    default: CPMAC(8, 2, 1, false); break;
+  const MacShape sh = variant > 0 && variant < BLB_MAC_VARIANTS ? kMacShapes[variant] : mac_shape_for(c->n, nl, n_bj, p50);
+  const int n_kblk = c->n / (64 * sh.waves / sh.split * sh.cpt);
+  const int blocks = n_kblk * nl * ((n_bj + sh.tb - 1) / sh.tb);
+#define CPMAC(tb_, cpt_, split_, waves_)                                                                                            \
+  if (sh.tb == tb_ && sh.cpt == cpt_ && sh.split == split_ && sh.waves == waves_) {                                                 \
+    if (p50)                                                                                                                        \
+      k_cp_mac<tb_, cpt_, split_, waves_, true><<<blocks, 64 * waves_, 0, c->stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk); \
+    else                                                                                                                            \
+      k_cp_mac<tb_, cpt_, split_, waves_, false><<<blocks, 64 * waves_, 0, c->stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk); \
+    return;                                                                                                                         \
   }
+  CPMAC(12, 2, 1, 1)
+  CPMAC(8, 2, 1, 1)
+  CPMAC(8, 2, 2, 2)
+  CPMAC(4, 2, 4, 4)
+  CPMAC(2, 2, 4, 4)
+  CPMAC(8, 4, 1, 4)
+  CPMAC(4, 4, 1, 1)
+  CPMAC(4, 4, 2, 2)
+  CPMAC(6, 4, 1, 1)
+  CPMAC(6, 2, 1, 1)
+  CPMAC(4, 2, 1, 1)
+  CPMAC(4, 2, 2, 2)
+  CPMAC(8, 2, 1, 4)
+  CPMAC(4, 2, 1, 4)
+  CPMAC(12, 2, 1, 4)
+  CPMAC(6, 4, 1, 4)
+  CPMAC(4, 4, 1, 4)
 #undef CPMAC
 }
 

@@ -626,6 +626,39 @@ def test_mac_variants_bit_identical(c2s, shape, fmt):
     B.blb_keys_destroy(r["keys_g"])
 
 
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("d_out", [33, 128, 250, 512, 760, 1400])
+def test_mac_shape_by_size(c2s, d_out, fmt):
+    """The launch shape taken by size (knob 0) at sizes on each side of every bound of its rule (2 to
+    44 column blocks, 8 to 176 outputs) gives the words of a fixed 8 x 2 shape, a partial last tile and
+    an input count that is no multiple of the waves sharing the terms included."""
+    B = c2s.B
+    L, d_in, level = 100, 40, 2
+    rng = np.random.default_rng(1700 + d_out)
+    B.blb_ctx_set_knob(c2s.h, B.BLB_KNOB_PLAN_FORMAT, fmt)
+    try:
+        plan = B.blb_plan_matmul_cp(c2s.h, rng.normal(0, 0.02, (d_in, d_out)), L, level)
+    finally:
+        B.blb_ctx_set_knob(c2s.h, B.BLB_KNOB_PLAN_FORMAT, 0)
+    g = B.blb_plan_info(plan)
+    keys = B.blb_keygen(c2s.h, 1701, [i * g["Lp"] for i in range(1, g["B"])] + [j * g["B"] * g["Lp"] for j in range(1, g["G"])])
+    mods = B.blb_ctx_moduli(c2s.h, c2s.n_q + c2s.n_sp)[: level + 1]
+    X = [c2s.ct(level) for _ in range(g["n_in"])]
+    for x in X:  # any residues do: the product is exact
+        B.blb_import(c2s.h, np.stack([np.stack([rng.integers(0, int(q), c2s.n, dtype=np.uint64) for q in mods]) for _ in range(2)]), x)
+        x.scale = 2.0 ** 40
+    words = []
+    for var in (13, 0):
+        B.blb_ctx_set_knob(c2s.h, B.BLB_KNOB_MAC_VARIANT, var)
+        Y = [c2s.ct(level - 1) for _ in range(g["n_out"])]
+        B.blb_matmul_cp(c2s.h, keys, plan, X, Y)
+        words.append([c2s.export(y) for y in Y])
+    assert all(np.array_equal(a, b) for a, b in zip(*words))
+    torch.cuda.synchronize()
+    B.blb_plan_destroy(plan)
+    B.blb_keys_destroy(keys)
+
+
 # --------------------------------------------------------------------------------------
 # the batched transform on its own
 # --------------------------------------------------------------------------------------
