@@ -128,6 +128,7 @@ void stack_fit(blb_ctx* c, Workspace* w) {
   // a quarter of headroom over the deepest need seen (doubling would hold tens of GB idle once
   // batches of large operators have run)
   const size_t cap = (w->need + w->need / 4 + quantum - 1) / quantum * quantum;
+  run_held(c);  // launches held back still use the present buffer
   (void)hipStreamSynchronize(w->stream);
   stack_release(c, w);
   bool ok = !c->budget || c->dev_bytes + cap <= c->budget;
@@ -219,6 +220,7 @@ struct Tmp {
     } else if (c->fixed && !c->rec) {
       c->fixed->off = off0;
     }
+    if (!ptrs.empty()) run_held(c);  // freed in stream order: after the launches that use them
     for (void* p : ptrs) (void)hipFreeAsync(p, c->stream);
   }
 };
@@ -243,7 +245,8 @@ Uploader* ring_for(blb_ctx* c) {
   if (!u) return nullptr;
   u->stream = c->stream;
   u->cap = kUploadCap;
-  if (hipHostMalloc((void**)&u->host, u->cap, hipHostMallocDefault) != hipSuccess || hipMalloc((void**)&u->dev, u->cap) != hipSuccess) {
+  if (hipHostMalloc((void**)&u->host, u->cap, hipHostMallocMapped) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&u->mapped, u->host, 0) != hipSuccess || hipMalloc((void**)&u->dev, u->cap) != hipSuccess) {
     (void)hipGetLastError();
     ring_free(u);
     return nullptr;
@@ -256,8 +259,30 @@ void uploader_free(blb_ctx* c) {
   for (Uploader* u : c->ups) ring_free(u);
   c->ups.clear();
 }
-// Copies `bytes` from host memory to a device region that stays valid for all work enqueued
-// on the stream before the ring wraps back onto it.
+// Copies the tables written since the last call of this and, once the open region is large enough,
+// closes it with an event.
+void stage_tables(blb_ctx* c, Uploader& u, bool close) {
+  if (u.head > u.staged) launch_stage(u.stream, u.dev + u.staged, u.mapped + u.staged, u.head - u.staged);
+  u.staged = u.head;
+  if (u.head == u.open || !(close || u.head - u.open >= Uploader::kRegion)) return;
+  hipEvent_t ev = nullptr;
+  if (!u.free_events.empty()) {
+    ev = u.free_events.back();
+    u.free_events.pop_back();
+  } else if (c->fixed || hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+    ev = nullptr;
+  }
+  if (ev) {
+    (void)hipEventRecord(ev, u.stream);
+    u.inflight.push_back(UploadRegion{u.open, u.head, ev});
+  } else {
+    (void)hipStreamSynchronize(u.stream);
+  }
+  u.open = u.head;
+}
+// Writes `bytes` of a table to the ring of the context's stream; the device region returned holds
+// them for all work enqueued on the stream before the ring wraps back onto it.  Inside an eager
+// call the copy waits for run_held (with the launches that read the table), else it is enqueued at once.
 void* upload(blb_ctx* c, const void* data, size_t bytes) {
   if (c->rec) {  // recording: the table lives in the executor's blob, copied once after capture
     ExecRec* r = c->rec;
@@ -279,36 +304,28 @@ void* upload(blb_ctx* c, const void* data, size_t bytes) {
   }
   if (!up) return nullptr;
   Uploader& u = *up;
+  const size_t used = bytes;
   bytes = align_up(bytes, 256);
   if (bytes > u.cap) return nullptr;
-  size_t lo = u.head;
-  if (lo + bytes > u.cap) lo = 0;
-  const size_t hi = lo + bytes;
-  // staging bytes about to be rewritten may still be read by their earlier copy
-  std::deque<UploadRegion> keep;
-  for (const UploadRegion& e : u.inflight) {
-    if (e.lo < hi && lo < e.hi) {
-      (void)hipEventSynchronize(e.copied);
-      u.free_events.push_back(e.copied);
-    } else {
-      keep.push_back(e);
-    }
+  auto retire = [&] {
+    const UploadRegion e = u.inflight.front();
+    u.inflight.pop_front();
+    (void)hipEventSynchronize(e.copied);
+    u.free_events.push_back(e.copied);
+  };
+  if (u.head + bytes > u.cap) {  // wrap: what is written so far is copied, the regions skipped at the end are retired
+    run_held(c);
+    stage_tables(c, u, true);
+    while (!u.inflight.empty() && u.inflight.front().lo >= u.head) retire();
+    u.head = u.open = u.staged = 0;
   }
-  u.inflight.swap(keep);
-  memcpy(u.host + lo, data, bytes);
-  if (hipMemcpyAsync(u.dev + lo, u.host + lo, bytes, hipMemcpyHostToDevice, c->stream) != hipSuccess) return nullptr;
-  hipEvent_t ev;
-  if (!u.free_events.empty()) {
-    ev = u.free_events.back();
-    u.free_events.pop_back();
-  } else if (c->fixed || hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
-    (void)hipStreamSynchronize(c->stream);
-    u.head = hi;
-    return u.dev + lo;
-  }
-  (void)hipEventRecord(ev, c->stream);
-  u.inflight.push_back(UploadRegion{lo, hi, ev});
+  const size_t lo = u.head, hi = lo + bytes;
+  // staging bytes about to be rewritten may still be read by their earlier copy (oldest regions first)
+  while (!u.inflight.empty() && u.inflight.front().lo < hi && lo < u.inflight.front().hi) retire();
+  memcpy(u.host + lo, data, used);
   u.head = hi;
+  if (c->defer) c->defer->ring = up;
+  else stage_tables(c, u, false);
   return u.dev + lo;
 }
 
@@ -349,6 +366,27 @@ struct Span {
     }
   }
 };
+
+// Runs one eager call's body with its launches held back (nothing is held while a graph is being
+// recorded, launches are timed, or an allocation-free call runs).
+template <class F>
+int in_call(blb_ctx* c, F&& body) {
+  if (!c || c->defer || c->rec || c->fixed || c->timing) return body();
+  Deferred d;
+  c->defer = &d;
+  int rc = body();
+  run_held(c);
+  c->defer = nullptr;
+  if (rc == BLB_OK && (d.failed || hipGetLastError() != hipSuccess)) rc = BLB_EDEVICE;
+  return rc;
+}
+
+// device-to-device copy in the order of the launches
+void copy_words(blb_ctx* c, uint64_t* dst, const uint64_t* src, size_t words) {
+  emit(c, [=, stream = c->stream] {
+    if (hipMemcpyAsync(dst, src, words * 8, hipMemcpyDeviceToDevice, stream) != hipSuccess && c->defer) c->defer->failed = true;
+  });
+}
 
 // descriptor batches can exceed the ring: split into chunks
 void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind) {
@@ -453,9 +491,8 @@ void build_ks_level(blb_ctx* c, int level, KsLevelConst* k) {
 }
 
 const SwKey* find_key(const blb_keys* k, uint64_t id) {
-  for (const SwKey& s : k->keys)
-    if (s.id == id) return &s;
-  return nullptr;
+  const auto it = k->index.find(id);
+  return it == k->index.end() ? nullptr : &k->keys[it->second];
 }
 
 uint32_t galois_left(const blb_ctx* c, int64_t steps) {
@@ -654,6 +691,17 @@ int encode_dense_dev(blb_ctx* c, const double* d_vals, int n_vals, int count, do
 }
 
 }  // namespace
+
+void run_held(blb_ctx* c) {
+  Deferred* d = c->defer;
+  if (!d) return;
+  if (d->ring) stage_tables(c, *d->ring, false);
+  std::vector<std::function<void()>> ops;
+  ops.swap(d->ops);
+  for (auto& f : ops) f();
+  ops.clear();
+  if (d->ops.empty()) d->ops.swap(ops);  // keeps the capacity
+}
 
 // a stream is about to be destroyed after a synchronisation: drop its stack of temporaries
 void stack_forget_stream(blb_ctx* c, hipStream_t s) {
@@ -1070,6 +1118,7 @@ int blb_keygen(blb_ctx* c, uint64_t seed, const int32_t* rot_steps, int n_rot, b
   }
   // relinearisation key: s' = s^2
   launch_ew(c, EW_MUL, sp, K->s_ntt, K->s_ntt, nullptr, nm, all);
+  K->index[0] = K->keys.size();
   K->keys.push_back(SwKey{0, nullptr});
   if ((rc = make_swk(c, K, sp, 0, &K->keys.back()))) {
     blb_keys_destroy(K);
@@ -1079,6 +1128,7 @@ int blb_keygen(blb_ctx* c, uint64_t seed, const int32_t* rot_steps, int n_rot, b
     const uint32_t g = galois_left(c, rot_steps[r]);
     if (g == 1 || find_key(K, g)) continue;
     launch_automorph(c, sp, K->s_ntt, nm, g);
+    K->index[g] = K->keys.size();
     K->keys.push_back(SwKey{g, nullptr});
     if ((rc = make_swk(c, K, sp, g, &K->keys.back()))) {
       blb_keys_destroy(K);
@@ -1269,12 +1319,12 @@ int blb_import(blb_ctx* c, const uint64_t* host_words, blb_ct* ct) {
 // ------------------------------------------------------------------------------------------
 // rotate / rescale
 // ------------------------------------------------------------------------------------------
-int blb_rotate(blb_ctx* c, const blb_keys* K, const blb_ct* in, int32_t steps, blb_ct* out) {
+static int rotate_call(blb_ctx* c, const blb_keys* K, const blb_ct* in, int32_t steps, blb_ct* out) {
   if (!c || !K || !out || !out->data || check_ct(c, in) || in->degree != 1 || in->data == out->data) return BLB_EINVAL;
   const int n = c->n, nl = in->level + 1;
   const uint32_t g = galois_left(c, steps);
   if (g == 1) {
-    if (hipMemcpyAsync(out->data, in->data, (size_t)2 * nl * n * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess) return BLB_EDEVICE;
+    copy_words(c, out->data, in->data, (size_t)2 * nl * n);
   } else {
     const SwKey* key = find_key(K, g);
     if (!key) return BLB_ENOKEY;
@@ -1287,6 +1337,9 @@ int blb_rotate(blb_ctx* c, const blb_keys* K, const blb_ct* in, int32_t steps, b
   out->degree = 1;
   out->scale = in->scale;
   return BLB_OK;
+}
+int blb_rotate(blb_ctx* c, const blb_keys* K, const blb_ct* in, int32_t steps, blb_ct* out) {
+  return in_call(c, [&] { return rotate_call(c, K, in, steps, out); });
 }
 
 // blb_rotate with every temporary in the device's fixed scratch array: the key switch's
@@ -1309,7 +1362,7 @@ int blb_rotate_noalloc(blb_ctx* c, const blb_keys* K, const blb_ct* in, int32_t 
   return rc;
 }
 
-int blb_rescale(blb_ctx* c, const blb_ct* in, blb_ct* out) {
+static int rescale_call(blb_ctx* c, const blb_ct* in, blb_ct* out) {
   if (!c || !out || !out->data || check_ct(c, in) || in->data == out->data) return BLB_EINVAL;
   if (in->level < 1) return BLB_ELEVEL;
   const int rc = rescale_batch(c, in->level, in->degree + 1, {in->data}, {out->data});
@@ -1318,6 +1371,9 @@ int blb_rescale(blb_ctx* c, const blb_ct* in, blb_ct* out) {
   out->degree = in->degree;
   out->scale = in->scale / (double)c->mod[in->level];
   return BLB_OK;
+}
+int blb_rescale(blb_ctx* c, const blb_ct* in, blb_ct* out) {
+  return in_call(c, [&] { return rescale_call(c, in, out); });
 }
 
 // Batched negacyclic transform of caller-owned limb-polys [n_polys][n_limbs][N], in place;
@@ -1568,7 +1624,7 @@ int blb_plan_info(const blb_plan* P, int32_t* info) {
   return BLB_OK;
 }
 
-int blb_matmul_cp(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct* X, int n_in, blb_ct* Y, int n_out) {
+static int matmul_cp_call(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct* X, int n_in, blb_ct* Y, int n_out) {
   if (!c || !K || !P || !X || !Y || P->kind != 1) return BLB_EINVAL;
   const CpGeom& g = P->g;
   if (n_in != g.n_in || n_out != g.n_out) return BLB_EINVAL;
@@ -1670,6 +1726,9 @@ int blb_matmul_cp(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct
   }
   return BLB_OK;
 }
+int blb_matmul_cp(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct* X, int n_in, blb_ct* Y, int n_out) {
+  return in_call(c, [&] { return matmul_cp_call(c, K, P, X, n_in, Y, n_out); });
+}
 
 // ------------------------------------------------------------------------------------------
 // mask-and-share
@@ -1710,7 +1769,7 @@ int blb_rerandomize(blb_ctx* c, const blb_keys* K, blb_ct* cts, int n_ct, uint64
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
 
-int blb_mask_to_share(blb_ctx* c, blb_ct* cts, int n_ct, uint64_t seed, int target_level, uint64_t* share_dev) {
+static int mask_to_share_call(blb_ctx* c, blb_ct* cts, int n_ct, uint64_t seed, int target_level, uint64_t* share_dev) {
   if (!c || !cts || n_ct < 1 || !share_dev) return BLB_EINVAL;
   for (int t = 0; t < n_ct; ++t) {
     if (check_ct(c, &cts[t]) || cts[t].degree != 1) return BLB_EINVAL;
@@ -1726,10 +1785,8 @@ int blb_mask_to_share(blb_ctx* c, blb_ct* cts, int n_ct, uint64_t seed, int targ
     if (nl != tl) {
       uint64_t* c1tmp = tmp.get<uint64_t>((size_t)tl * n);
       if (!c1tmp) return BLB_ENOMEM;
-      if (hipMemcpyAsync(c1tmp, cts[t].data + (size_t)nl * n, (size_t)tl * n * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-        return BLB_EDEVICE;
-      if (hipMemcpyAsync(cts[t].data + (size_t)tl * n, c1tmp, (size_t)tl * n * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-        return BLB_EDEVICE;
+      copy_words(c, c1tmp, cts[t].data + (size_t)nl * n, (size_t)tl * n);
+      copy_words(c, cts[t].data + (size_t)tl * n, c1tmp, (size_t)tl * n);
     }
   }
   {
@@ -1747,9 +1804,12 @@ int blb_mask_to_share(blb_ctx* c, blb_ct* cts, int n_ct, uint64_t seed, int targ
   for (int t = 0; t < n_ct; ++t) cts[t].level = target_level;
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
+int blb_mask_to_share(blb_ctx* c, blb_ct* cts, int n_ct, uint64_t seed, int target_level, uint64_t* share_dev) {
+  return in_call(c, [&] { return mask_to_share_call(c, cts, n_ct, seed, target_level, share_dev); });
+}
 
 // c0 += NTT(share) for every ciphertext: the server's step of the MPC-to-CKKS conversion
-int blb_add_share(blb_ctx* c, blb_ct* cts, int n_ct, const uint64_t* share_dev) {
+static int add_share_call(blb_ctx* c, blb_ct* cts, int n_ct, const uint64_t* share_dev) {
   if (!c || !cts || n_ct < 1 || !share_dev) return BLB_EINVAL;
   for (int t = 0; t < n_ct; ++t) {
     if (check_ct(c, &cts[t]) || cts[t].degree != 1) return BLB_EINVAL;
@@ -1768,6 +1828,9 @@ int blb_add_share(blb_ctx* c, blb_ct* cts, int n_ct, const uint64_t* share_dev) 
     ntt_descs(c, d, NTT_ADDTO);
   }
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
+}
+int blb_add_share(blb_ctx* c, blb_ct* cts, int n_ct, const uint64_t* share_dev) {
+  return in_call(c, [&] { return add_share_call(c, cts, n_ct, share_dev); });
 }
 
 }  // extern "C"
@@ -2472,7 +2535,7 @@ int cc_steps23_bsgs_dev(blb_ctx* c, const blb_keys* K, const blb_plan* P, const 
 
 extern "C" {
 
-int blb_matmul_cc(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct* A, const blb_ct* Bp, int n_ct, blb_ct* Cd, int n_out) {
+static int matmul_cc_call(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct* A, const blb_ct* Bp, int n_ct, blb_ct* Cd, int n_out) {
   if (!c || !K || !P || !A || !Bp || !Cd || P->kind != 2) return BLB_EINVAL;
   if (n_ct != P->n_ct || n_out != P->n_out) return BLB_EINVAL;
   const int level_in = P->level, level = P->level - P->hom1, n = c->n, lp = P->Lp;
@@ -2738,6 +2801,9 @@ int blb_matmul_cc(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct
   }
   return BLB_OK;
 }
+int blb_matmul_cc(blb_ctx* c, const blb_keys* K, const blb_plan* P, const blb_ct* A, const blb_ct* Bp, int n_ct, blb_ct* Cd, int n_out) {
+  return in_call(c, [&] { return matmul_cc_call(c, K, P, A, Bp, n_ct, Cd, n_out); });
+}
 
 }  // extern "C"
 
@@ -2900,7 +2966,7 @@ void blb_exec_destroy(blb_exec* E) {
 // ==========================================================================================
 extern "C" {
 
-int blb_batch_matmul_cp(blb_ctx* c, const blb_cp_instance* inst, int n_inst) {
+static int batch_matmul_cp_call(blb_ctx* c, const blb_cp_instance* inst, int n_inst) {
   if (!c || !inst || n_inst < 1) return BLB_EINVAL;
   const int n = c->n;
   const int level = inst[0].plan ? inst[0].plan->level : -1;
@@ -3082,6 +3148,9 @@ int blb_batch_matmul_cp(blb_ctx* c, const blb_cp_instance* inst, int n_inst) {
     }
   return BLB_OK;
 }
+int blb_batch_matmul_cp(blb_ctx* c, const blb_cp_instance* inst, int n_inst) {
+  return in_call(c, [&] { return batch_matmul_cp_call(c, inst, n_inst); });
+}
 
 int blb_exec_create_batch_cp(blb_ctx* c, const blb_cp_instance* inst, int n_inst, int mask_target_level, uint64_t* share_dev,
                              blb_exec** out) {
@@ -3133,7 +3202,7 @@ int blb_exec_create_batch_cp(blb_ctx* c, const blb_cp_instance* inst, int n_inst
 // ==========================================================================================
 extern "C" {
 
-int blb_rotate_sum(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, int block, int n_blocks, int direction, int mask,
+static int rotate_sum_call(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, int block, int n_blocks, int direction, int mask,
                    blb_ct* out) {
   if (!c || !K || !in || !out || n_ct < 1 || block < 1 || n_blocks < 1 || (n_blocks & (n_blocks - 1))) return BLB_EINVAL;
   if ((direction != 0 && direction != 1) || (mask != 0 && mask != 1) || (mask && direction != 0)) return BLB_EINVAL;
@@ -3160,15 +3229,18 @@ int blb_rotate_sum(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, in
   uint64_t* rot = tmp.get<uint64_t>((size_t)n_ct * ctw);
   uint64_t* mpt = mask ? tmp.get<uint64_t>((size_t)nl * n) : nullptr;
   if (tmp.failed) return BLB_ENOMEM;
-  for (int t = 0; t < n_ct; ++t)
-    if (hipMemcpyAsync(cur + (size_t)t * ctw, in[t].data, ctw * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess) return BLB_EDEVICE;
   int rc = BLB_OK;
+  if (keys.empty())
+    for (int t = 0; t < n_ct; ++t) copy_words(c, cur + (size_t)t * ctw, in[t].data, ctw);
+  // the last sums go straight to the outputs unless a mask follows; a single step's sums read the
+  // inputs, which outputs may overlap in another order, so they stay in `cur` too
+  const bool direct = !mask && keys.size() >= 2;
   // m^i = m^{i-1} + Rot^{2^{i-1} block}(m^{i-1}): one batch of n_ct key switches, then an add
   for (size_t s = 0; s < keys.size(); ++s) {
     std::vector<const uint64_t*> srcs;
     std::vector<KsReq> reqs;
     for (int t = 0; t < n_ct; ++t) {
-      const uint64_t* x = cur + (size_t)t * ctw;
+      const uint64_t* x = s == 0 ? in[t].data : cur + (size_t)t * ctw;
       srcs.push_back(x + (size_t)nl * n);
       reqs.push_back(KsReq{t, keys[s], gals[s], rot + (size_t)t * ctw, x, gals[s], nullptr});
     }
@@ -3176,9 +3248,9 @@ int blb_rotate_sum(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, in
     std::vector<const uint64_t*> terms;
     std::vector<uint64_t*> dsts;
     for (int t = 0; t < n_ct; ++t) {
-      terms.push_back(cur + (size_t)t * ctw);
+      terms.push_back(s == 0 ? in[t].data : cur + (size_t)t * ctw);
       terms.push_back(rot + (size_t)t * ctw);
-      dsts.push_back(cur + (size_t)t * ctw);
+      dsts.push_back(direct && s + 1 == keys.size() ? out[t].data : cur + (size_t)t * ctw);
     }
     const uint64_t* const* t_dev = upload_vec(c, terms);
     uint64_t* const* d_dev = (uint64_t* const*)upload(c, dsts.data(), dsts.size() * sizeof(uint64_t*));
@@ -3194,9 +3266,11 @@ int blb_rotate_sum(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, in
   }
   if (mask) {
     // keep the first block: mask [1 x block, 0, ...] at scale q_level, then rescale
-    std::vector<double> v((size_t)S, 0.0);
-    for (int j = 0; j < block; ++j) v[j] = 1.0;
-    if ((rc = encode_vectors_ntt(c, v, 1, (double)c->mod[level], level, mpt))) return rc;
+    // (coefficients of a 0/1 vector are at most the scale: the encoder cannot overflow)
+    double* buf = tmp.get<double>((size_t)2 * S * 4);
+    if (tmp.failed) return BLB_ENOMEM;
+    run_encode_block(c, block, buf, buf + (size_t)S * 4, (double)c->mod[level], nl, mpt, c->d_flag);
+    ntt_regular(c, mpt, nl, nl, true);
     std::vector<CcPair> pairs;
     for (int t = 0; t < n_ct; ++t) pairs.push_back(CcPair{cur + (size_t)t * ctw, mpt, nullptr, nullptr, cur + (size_t)t * ctw});
     const CcPair* p_dev = upload_vec(c, pairs);
@@ -3207,9 +3281,8 @@ int blb_rotate_sum(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, in
       launch_mask_pair(c, p_dev, n_ct, nl);
     }
     if ((rc = rescale_batch(c, level, 2, rin, rout))) return rc;
-  } else {
-    for (int t = 0; t < n_ct; ++t)
-      if (hipMemcpyAsync(rout[t], rin[t], ctw * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess) return BLB_EDEVICE;
+  } else if (!direct) {
+    for (int t = 0; t < n_ct; ++t) copy_words(c, rout[t], rin[t], ctw);
   }
   const double sc = in[0].scale;
   for (int t = 0; t < n_ct; ++t) {
@@ -3218,6 +3291,10 @@ int blb_rotate_sum(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, in
     out[t].scale = sc;
   }
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
+}
+int blb_rotate_sum(blb_ctx* c, const blb_keys* K, const blb_ct* in, int n_ct, int block, int n_blocks, int direction, int mask,
+                   blb_ct* out) {
+  return in_call(c, [&] { return rotate_sum_call(c, K, in, n_ct, block, n_blocks, direction, mask, out); });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -3248,7 +3325,7 @@ void set_out(blb_ct* out, int n_ct, int level, const double* scales) {
 }
 }  // namespace
 
-int blb_ew_add(blb_ctx* c, const blb_ct* a, const blb_ct* b, int n_ct, blb_ct* out) {
+static int ew_add_call(blb_ctx* c, const blb_ct* a, const blb_ct* b, int n_ct, blb_ct* out) {
   if (!b) return BLB_EINVAL;
   int rc = check_pairs(c, a, b, n_ct, out, true);
   if (rc) return rc;
@@ -3272,8 +3349,11 @@ int blb_ew_add(blb_ctx* c, const blb_ct* a, const blb_ct* b, int n_ct, blb_ct* o
   set_out(out, n_ct, a[0].level, sc.data());
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
+int blb_ew_add(blb_ctx* c, const blb_ct* a, const blb_ct* b, int n_ct, blb_ct* out) {
+  return in_call(c, [&] { return ew_add_call(c, a, b, n_ct, out); });
+}
 
-int blb_ew_add_plain(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_dev, blb_ct* out) {
+static int ew_add_plain_call(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_dev, blb_ct* out) {
   if (!pt_dev) return BLB_EINVAL;
   int rc = check_pairs(c, a, nullptr, n_ct, out, false);
   if (rc) return rc;
@@ -3282,9 +3362,7 @@ int blb_ew_add_plain(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_d
   std::vector<double> sc;
   for (int t = 0; t < n_ct; ++t) {
     sc.push_back(a[t].scale);
-    if (out[t].data != a[t].data &&
-        hipMemcpyAsync(out[t].data, a[t].data, ctw * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-      return BLB_EDEVICE;
+    if (out[t].data != a[t].data) copy_words(c, out[t].data, a[t].data, ctw);
   }
   std::vector<PolyDesc> d;
   for (int t = 0; t < n_ct; ++t)
@@ -3300,8 +3378,11 @@ int blb_ew_add_plain(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_d
   set_out(out, n_ct, a[0].level, sc.data());
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
+int blb_ew_add_plain(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_dev, blb_ct* out) {
+  return in_call(c, [&] { return ew_add_plain_call(c, a, n_ct, pt_dev, out); });
+}
 
-int blb_ew_mul_plain(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_dev, double pt_scale, blb_ct* out) {
+static int ew_mul_plain_call(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_dev, double pt_scale, blb_ct* out) {
   if (!pt_dev || !(pt_scale > 0)) return BLB_EINVAL;
   int rc = check_pairs(c, a, nullptr, n_ct, out, false);
   if (rc) return rc;
@@ -3329,8 +3410,11 @@ int blb_ew_mul_plain(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_d
   set_out(out, n_ct, a[0].level, sc.data());
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
+int blb_ew_mul_plain(blb_ctx* c, const blb_ct* a, int n_ct, const uint64_t* pt_dev, double pt_scale, blb_ct* out) {
+  return in_call(c, [&] { return ew_mul_plain_call(c, a, n_ct, pt_dev, pt_scale, out); });
+}
 
-int blb_ew_mul_relin(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_ct* b, int n_ct, blb_ct* out) {
+static int ew_mul_relin_call(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_ct* b, int n_ct, blb_ct* out) {
   if (!K || !b) return BLB_EINVAL;
   int rc = check_pairs(c, a, b, n_ct, out, false);
   if (rc) return rc;
@@ -3367,8 +3451,11 @@ int blb_ew_mul_relin(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_c
   set_out(out, n_ct, level, sc.data());
   return BLB_OK;
 }
+int blb_ew_mul_relin(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_ct* b, int n_ct, blb_ct* out) {
+  return in_call(c, [&] { return ew_mul_relin_call(c, K, a, b, n_ct, out); });
+}
 
-int blb_scalar_op(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_ct* s, int n_ct, int block, int n_blocks, int op,
+static int scalar_op_call(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_ct* s, int n_ct, int block, int n_blocks, int op,
                   int from_sum, blb_ct* out) {
   if (!c || !K || !s || (op != 0 && op != 1) || (from_sum != 0 && from_sum != 1)) return BLB_EINVAL;
   int rc = check_pairs(c, a, s, n_ct, out, op == 0);
@@ -3384,6 +3471,10 @@ int blb_scalar_op(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_ct* 
   // broadcast of the first block (right rotate-and-sum), or the unmasked summation (left)
   if ((rc = blb_rotate_sum(c, K, s, n_ct, block, n_blocks, from_sum ? 0 : 1, 0, vs.data()))) return rc;
   return op == 0 ? blb_ew_add(c, a, vs.data(), n_ct, out) : blb_ew_mul_relin(c, K, a, vs.data(), n_ct, out);
+}
+int blb_scalar_op(blb_ctx* c, const blb_keys* K, const blb_ct* a, const blb_ct* s, int n_ct, int block, int n_blocks, int op,
+                  int from_sum, blb_ct* out) {
+  return in_call(c, [&] { return scalar_op_call(c, K, a, s, n_ct, block, n_blocks, op, from_sum, out); });
 }
 
 }  // extern "C"

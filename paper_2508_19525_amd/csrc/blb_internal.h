@@ -5,6 +5,9 @@
 #include <stdint.h>
 #include <stddef.h>
 #include <deque>
+#include <functional>
+#include <unordered_map>
+#include <utility>
 #include <vector>
 #include "../../include/blb.h"
 
@@ -152,23 +155,36 @@ struct CpDiag {
 // ---------------------------------------------------------------------------------------
 // Host-side structures
 // ---------------------------------------------------------------------------------------
-// Descriptor upload ring: pinned host staging + device mirror; a host region is reused only
-// after the copy that last read it has completed.
-// Pinned staging ring for descriptor tables, one per stream: host bytes are copied to the
-// same offsets of a device ring on that stream, so a region's readers (kernels enqueued on the
-// stream after its copy) always run before the copy that later overwrites it; the host only
-// waits for the earlier copy of a region before rewriting its staging bytes.
+// Ring of descriptor tables, one per stream: tables are written to pinned, mapped host memory and
+// copied to the same offsets of a device ring by a kernel on that stream, so a region's readers
+// (kernels enqueued on the stream after its copy) always run before the copy that later
+// overwrites it; the host only waits for the earlier copies of a region before rewriting its
+// staging bytes.  Regions are retired oldest first; an event closes a region of kRegion bytes or
+// more, not every table.
 struct UploadRegion {
   size_t lo, hi;
   hipEvent_t copied;
 };
 struct Uploader {
+  static constexpr size_t kRegion = size_t(256) << 10;
   hipStream_t stream = nullptr;
   char* host = nullptr;
+  char* mapped = nullptr;  // the device's address of `host`
   char* dev = nullptr;
   size_t cap = 0, head = 0;
+  size_t open = 0;    // start of the region no event covers yet
+  size_t staged = 0;  // tables below this offset of the open region are copied (or queued to be)
   std::deque<UploadRegion> inflight;
   std::vector<hipEvent_t> free_events;
+};
+
+// Launches of one eager call, held back until the call's tables can be copied together: one
+// staging kernel and then the launches in order, instead of a copy between any two of them.
+struct Deferred {
+  static constexpr size_t kMost = 12;  // held launches; the device starts on a long call's first ones meanwhile
+  Uploader* ring = nullptr;            // set by the first table of the call
+  std::vector<std::function<void()>> ops;
+  bool failed = false;
 };
 
 // Kernel timing spans recorded with HIP events on the context stream (when enabled).
@@ -218,6 +234,7 @@ struct Workspace {
 struct blb_ctx {
   int log_n, n, n_q, n_sp, dnum, alpha;
   ExecRec* rec = nullptr;
+  Deferred* defer = nullptr;       // set while an eager call holds its launches back
   FixedArena* fixed = nullptr;     // set only inside an allocation-free entry point
   std::vector<Workspace*> stacks;  // stacks of temporaries by stream
   bool timing = false;
@@ -266,6 +283,7 @@ struct blb_keys {
   uint64_t* s_ntt;  // secret in evaluation form for all moduli [modulus][N]
   uint64_t* pk = nullptr;  // public key (-a s + e, a), evaluation form [2][n_q][N]
   std::vector<SwKey> keys;
+  std::unordered_map<uint64_t, size_t> index;  // id -> position in keys
   size_t bytes;
 };
 
@@ -314,6 +332,19 @@ struct blb_plan {
 // ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
+// copies the tables of the call so far and runs the launches it holds back
+void run_held(blb_ctx* c);
+// every launch on the context's stream goes through here
+template <class F>
+void emit(blb_ctx* c, F&& f) {
+  if (!c->defer) {
+    f();
+    return;
+  }
+  c->defer->ops.emplace_back(std::forward<F>(f));
+  if (c->defer->ops.size() >= Deferred::kMost) run_held(c);
+}
+void launch_stage(hipStream_t stream, void* dst, const void* src_mapped, size_t bytes);
 struct PolyDesc;
 void launch_sample_uniform(blb_ctx* c, uint64_t* out, int n_limbs, ModMap map, uint64_t seed, uint32_t obj, uint32_t tag);
 void launch_sample_int(blb_ctx* c, uint64_t* out, int n_limbs, ModMap map, uint64_t seed, uint32_t obj, uint32_t tag, bool gaussian);
@@ -369,5 +400,6 @@ void launch_zero(blb_ctx* c, uint64_t* dst, size_t words);
 // paired: the buffers hold (count + 1) / 2 complex vectors, each packing two real inputs
 int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
                      int* d_overflow);
+int run_encode_block(blb_ctx* c, int block, double* bufA, double* bufB, double scale, int nl, uint64_t* out, int* d_overflow);
 int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
                   int* d_overflow, CpDiag dg = CpDiag{nullptr, 0, 0, 0});

@@ -76,15 +76,18 @@ void upload_cdt(const uint64_t* table20) { (void)hipMemcpyToSymbol(HIP_SYMBOL(c_
 
 void launch_sample_uniform(blb_ctx* c, uint64_t* out, int n_limbs, ModMap map, uint64_t seed, uint32_t obj, uint32_t tag) {
   dim3 grid((c->n + 255) / 256, n_limbs);
-  k_sample_uniform<<<grid, 256, 0, c->stream>>>(out, c->n, map, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), obj, tag);
+  emit(c, [=, stream = c->stream] { k_sample_uniform<<<grid, 256, 0, stream>>>(out, c->n, map, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), obj, tag); });
 }
 void launch_sample_int(blb_ctx* c, uint64_t* out, int n_limbs, ModMap map, uint64_t seed, uint32_t obj, uint32_t tag, bool gaussian) {
-  k_sample_int<<<(c->n + 255) / 256, 256, 0, c->stream>>>(out, c->n, n_limbs, map, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), obj,
-                                                          tag, gaussian ? 1 : 0);
+  emit(c, [=, stream = c->stream] {
+    k_sample_int<<<(c->n + 255) / 256, 256, 0, stream>>>(out, c->n, n_limbs, map, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), obj, tag,
+                                                    gaussian ? 1 : 0);
+  });
 }
 void launch_sample_flood(blb_ctx* c, uint64_t* out, int n_limbs, ModMap map, uint64_t seed, uint32_t obj, uint32_t tag, int bits) {
-  k_sample_int<<<(c->n + 255) / 256, 256, 0, c->stream>>>(out, c->n, n_limbs, map, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), obj,
-                                                          tag, bits);
+  emit(c, [=, stream = c->stream] {
+    k_sample_int<<<(c->n + 255) / 256, 256, 0, stream>>>(out, c->n, n_limbs, map, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), obj, tag, bits);
+  });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -111,7 +114,7 @@ __global__ void k_ew(int op, uint64_t* out, const uint64_t* a, const uint64_t* b
 void launch_ew(blb_ctx* c, int op, uint64_t* out, const uint64_t* a, const uint64_t* b, const uint64_t* cc, int count, ModMap map) {
   if (count <= 0) return;
   dim3 grid((c->n + 255) / 256, count);
-  k_ew<<<grid, 256, 0, c->stream>>>(op, out, a, b, cc, c->n, map, c->mt);
+  emit(c, [=, stream = c->stream] { k_ew<<<grid, 256, 0, stream>>>(op, out, a, b, cc, c->n, map, c->mt); });
 }
 
 // encryption / key combination in evaluation form:
@@ -134,7 +137,7 @@ __global__ void k_rlwe_combine(uint64_t* out0, const uint64_t* a, const uint64_t
 void launch_rlwe_combine(blb_ctx* c, uint64_t* out0, const uint64_t* a, const uint64_t* s, const uint64_t* e, const uint64_t* extra,
                          LimbVals extra_mul, int n_limbs, ModMap map) {
   dim3 grid((c->n + 255) / 256, n_limbs);
-  k_rlwe_combine<<<grid, 256, 0, c->stream>>>(out0, a, s, e, extra, extra_mul, c->n, map, c->mt);
+  emit(c, [=, stream = c->stream] { k_rlwe_combine<<<grid, 256, 0, stream>>>(out0, a, s, e, extra, extra_mul, c->n, map, c->mt); });
 }
 
 // evaluation-form automorphism of `count` polys
@@ -146,7 +149,7 @@ __global__ void k_automorph(uint64_t* out, const uint64_t* in, int n, int log_n,
 }
 void launch_automorph(blb_ctx* c, uint64_t* out, const uint64_t* in, int count, uint32_t g) {
   dim3 grid((c->n + 255) / 256, count);
-  k_automorph<<<grid, 256, 0, c->stream>>>(out, in, c->n, c->log_n, g);
+  emit(c, [=, stream = c->stream] { k_automorph<<<grid, 256, 0, stream>>>(out, in, c->n, c->log_n, g); });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -178,7 +181,7 @@ __global__ void k_modup(const uint64_t* dcoef, uint64_t* X, const KsLevelConst* 
 }
 void launch_modup(blb_ctx* c, const uint64_t* dcoef, uint64_t* X, const KsLevelConst* kc_dev, int n_src, int nl, int n_ext, int n_digits) {
   dim3 grid((c->n + 255) / 256, n_src * n_digits);
-  k_modup<<<grid, 256, 0, c->stream>>>(dcoef, X, kc_dev, c->n, nl, n_ext, n_digits);
+  emit(c, [=, stream = c->stream] { k_modup<<<grid, 256, 0, stream>>>(dcoef, X, kc_dev, c->n, nl, n_ext, n_digits); });
 }
 
 // Operands reached through descriptors in memory are addressed as global memory explicitly
@@ -236,7 +239,7 @@ __global__ void k_ks_inner(const KsOut* __restrict__ outs, const uint64_t* __res
 void launch_ks_inner(blb_ctx* c, const KsOut* outs_dev, int n_out, const uint64_t* X, const KsLevelConst* kc_dev, uint64_t* U, int nl,
                      int n_ext, int n_digits) {
   dim3 grid((c->n / 2 + 255) / 256, n_out * n_ext);
-  k_ks_inner<<<grid, 256, 0, c->stream>>>(outs_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, n_digits, c->n_q);
+  emit(c, [=, stream = c->stream] { k_ks_inner<<<grid, 256, 0, stream>>>(outs_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, n_digits, c->n_q); });
 }
 
 // The same inner product for a group of outputs that share a switching key and Galois element:
@@ -305,7 +308,7 @@ __global__ void k_ks_inner_grp(const KsOut* __restrict__ outs, const int* __rest
 void launch_ks_inner_grouped(blb_ctx* c, const KsOut* outs_dev, const int* ord_dev, const KsGroup* groups_dev, int n_groups,
                              const uint64_t* X, const KsLevelConst* kc_dev, uint64_t* U, int nl, int n_ext, int n_digits) {
   dim3 grid((c->n / 2 + 255) / 256, n_groups * n_ext);
-  k_ks_inner_grp<<<grid, 256, 0, c->stream>>>(outs_dev, ord_dev, groups_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, n_digits, c->n_q);
+  emit(c, [=, stream = c->stream] { k_ks_inner_grp<<<grid, 256, 0, stream>>>(outs_dev, ord_dev, groups_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, n_digits, c->n_q); });
 }
 
 // ModDown conversion: corr_i = sum_t [u_{p_t} * Phat_t^-1]_{p_t} * [Phat_t]_{q_i}  (coefficient
@@ -328,7 +331,7 @@ __global__ void k_moddown_conv(const uint64_t* U, uint64_t* Corr, const KsLevelC
 }
 void launch_moddown_conv(blb_ctx* c, const uint64_t* U, uint64_t* Corr, const KsLevelConst* kc_dev, int n_out, int nl, int n_ext) {
   dim3 grid((c->n + 255) / 256, n_out * 2);
-  k_moddown_conv<<<grid, 256, 0, c->stream>>>(U, Corr, kc_dev, c->n, nl, n_ext, c->n_sp);
+  emit(c, [=, stream = c->stream] { k_moddown_conv<<<grid, 256, 0, stream>>>(U, Corr, kc_dev, c->n, nl, n_ext, c->n_sp); });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -571,9 +574,9 @@ void launch_cp_mac(blb_ctx* c, const uint64_t* pt, const uint64_t* const* rx_tab
 #define CPMAC(tb_, cpt_, split_, waves_)                                                                                            \
   if (sh.tb == tb_ && sh.cpt == cpt_ && sh.split == split_ && sh.waves == waves_) {                                                 \
     if (p50)                                                                                                                        \
-      k_cp_mac<tb_, cpt_, split_, waves_, true><<<blocks, 64 * waves_, 0, c->stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk); \
+      emit(c, [=, stream = c->stream] { k_cp_mac<tb_, cpt_, split_, waves_, true><<<blocks, 64 * waves_, 0, stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk); }); \
     else                                                                                                                            \
-      k_cp_mac<tb_, cpt_, split_, waves_, false><<<blocks, 64 * waves_, 0, c->stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk); \
+      emit(c, [=, stream = c->stream] { k_cp_mac<tb_, cpt_, split_, waves_, false><<<blocks, 64 * waves_, 0, stream>>>(pt, rx_tab, inner, c->n, nl, n_ai, n_bj, c->mt, n_kblk); }); \
     return;                                                                                                                         \
   }
   CPMAC(12, 2, 1, 1)
@@ -612,7 +615,7 @@ __global__ void k_sum_cts(const uint64_t* const* __restrict__ srcs, uint64_t* co
 }
 void launch_sum_cts(blb_ctx* c, const uint64_t* const* srcs, uint64_t* const* dsts, int n_out, int n_terms, int nl) {
   dim3 grid((2 * nl * c->n + 255) / 256, n_out);
-  k_sum_cts<<<grid, 256, 0, c->stream>>>(srcs, dsts, n_terms, c->n, nl, c->mt);
+  emit(c, [=, stream = c->stream] { k_sum_cts<<<grid, 256, 0, stream>>>(srcs, dsts, n_terms, c->n, nl, c->mt); });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -640,19 +643,28 @@ __global__ void k_mask_sample(uint64_t* r_out, uint64_t* share, int n, int tl, M
 void launch_mask_sample(blb_ctx* c, uint64_t* r_out, uint64_t* share, int n_ct, int tl, uint64_t seed, const uint64_t* seed_dev,
                         uint32_t tag) {
   dim3 grid((c->n + 255) / 256, n_ct * tl);
-  k_mask_sample<<<grid, 256, 0, c->stream>>>(r_out, share, c->n, tl, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), seed_dev, tag);
+  emit(c, [=, stream = c->stream] { k_mask_sample<<<grid, 256, 0, stream>>>(r_out, share, c->n, tl, c->mt, (uint32_t)seed, (uint32_t)(seed >> 32), seed_dev, tag); });
 }
 
 __global__ void k_set_u64(uint64_t* dst, uint64_t v) { *dst = v; }
-void launch_set_u64(blb_ctx* c, uint64_t* dst, uint64_t value) { k_set_u64<<<1, 1, 0, c->stream>>>(dst, value); }
+void launch_set_u64(blb_ctx* c, uint64_t* dst, uint64_t value) { emit(c, [=, stream = c->stream] { k_set_u64<<<1, 1, 0, stream>>>(dst, value); }); }
 
 __global__ void k_zero(uint64_t* dst, size_t words) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < words) dst[i] = 0;
 }
+// a descriptor table from mapped host memory to its device region, 16 bytes per work-item
+__global__ void k_stage(uint4* __restrict__ dst, const uint4* __restrict__ src, unsigned n16) {
+  const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n16) dst[i] = src[i];
+}
+void launch_stage(hipStream_t stream, void* dst, const void* src_mapped, size_t bytes) {
+  const unsigned n16 = (unsigned)(bytes / 16);
+  k_stage<<<(n16 + 255) / 256, 256, 0, stream>>>((uint4*)dst, (const uint4*)src_mapped, n16);
+}
 void launch_zero(blb_ctx* c, uint64_t* dst, size_t words) {
   if (!words) return;
-  k_zero<<<(unsigned)((words + 255) / 256), 256, 0, c->stream>>>(dst, words);
+  emit(c, [=, stream = c->stream] { k_zero<<<(unsigned)((words + 255) / 256), 256, 0, stream>>>(dst, words); });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -716,6 +728,14 @@ struct EncSrcDense {
     const int j = slot_inv[u];
     return cdd{dd{j < n_vals ? v[j] : 0.0, 0.0}, dd{0.0, 0.0}};
   }
+};
+
+// The first-block mask: 1 in slots 0 .. block - 1, 0 elsewhere.
+struct EncSrcBlock {
+  int block;
+  const int32_t* slot_inv;
+  __device__ int begin(int) const { return block; }
+  __device__ cdd operator()(int b, int u) const { return cdd{dd{slot_inv[u] < b ? 1.0 : 0.0, 0.0}, dd{0.0, 0.0}}; }
 };
 
 // matmul_cp diagonal plaintexts, two per complex vector (plaintext p0 + 2 pp in the real part,
@@ -1001,20 +1021,23 @@ int encode_with(blb_ctx* c, const Src& src, int count, double* bufA, double* buf
   if (M1 != 16 && M1 != 32 && M1 != 64) return BLB_EINVAL;  // M1 = 8 R2, R2 = 2, 4, 8; M1 >= kEncRB
   const int n_vec = paired ? (count + 1) / 2 : count;  // complex vectors transformed
   const dim3 gc(kEncM2 / kEncCB, n_vec);
-  if (M1 == 64) k_enc_cols<Src, 8><<<gc, kEncCB * 8, 0, c->stream>>>(src, bufB, c->d_enc_tw, M);
-  else if (M1 == 32) k_enc_cols<Src, 4><<<gc, kEncCB * 8, 0, c->stream>>>(src, bufB, c->d_enc_tw, M);
-  else k_enc_cols<Src, 2><<<gc, kEncCB * 8, 0, c->stream>>>(src, bufB, c->d_enc_tw, M);
-  k_enc_rows<<<dim3(M1 / kEncRB, n_vec), kEncRB * 16, 0, c->stream>>>(bufB, bufA, c->d_enc_tw, M, M1);
+  if (M1 == 64) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 8><<<gc, kEncCB * 8, 0, stream>>>(src, bufB, c->d_enc_tw, M); });
+  else if (M1 == 32) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 4><<<gc, kEncCB * 8, 0, stream>>>(src, bufB, c->d_enc_tw, M); });
+  else emit(c, [=, stream = c->stream] { k_enc_cols<Src, 2><<<gc, kEncCB * 8, 0, stream>>>(src, bufB, c->d_enc_tw, M); });
+  emit(c, [=, stream = c->stream] { k_enc_rows<<<dim3(M1 / kEncRB, n_vec), kEncRB * 16, 0, stream>>>(bufB, bufA, c->d_enc_tw, M, M1); });
   dim3 grid((M + 255) / 256, n_vec);
   if (paired)
-    k_enc_final_pair<<<grid, 256, 0, c->stream>>>(bufA, c->d_enc_twist, scale / (double)M, M, nl, c->mt, c->d_mods, out, count, d_overflow);
+    emit(c, [=, stream = c->stream] { k_enc_final_pair<<<grid, 256, 0, stream>>>(bufA, c->d_enc_twist, scale / (double)M, M, nl, c->mt, c->d_mods, out, count, d_overflow); });
   else
-    k_enc_final<<<grid, 256, 0, c->stream>>>(bufA, c->d_enc_twist, scale / (double)M, M, nl, c->mt, c->d_mods, out, d_overflow);
+    emit(c, [=, stream = c->stream] { k_enc_final<<<grid, 256, 0, stream>>>(bufA, c->d_enc_twist, scale / (double)M, M, nl, c->mt, c->d_mods, out, d_overflow); });
   return BLB_OK;
 }
 int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
                      int* d_overflow) {
   return encode_with(c, EncSrcDense{vals, n_vals, c->d_slot_inv}, count, bufA, bufB, scale, nl, out, d_overflow, false);
+}
+int run_encode_block(blb_ctx* c, int block, double* bufA, double* bufB, double scale, int nl, uint64_t* out, int* d_overflow) {
+  return encode_with(c, EncSrcBlock{block, c->d_slot_inv}, 1, bufA, bufB, scale, nl, out, d_overflow, false);
 }
 int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
                   int* d_overflow, CpDiag dg) {
@@ -1042,7 +1065,7 @@ __global__ void k_mask_pair(const CcPair* __restrict__ pairs, int nl, int n, Mod
 void launch_mask_pair(blb_ctx* c, const CcPair* pairs_dev, int n_pairs, int nl) {
   if (n_pairs <= 0) return;
   dim3 grid((2 * nl * c->n + 255) / 256, n_pairs);
-  k_mask_pair<<<grid, 256, 0, c->stream>>>(pairs_dev, nl, c->n, c->mt);
+  emit(c, [=, stream = c->stream] { k_mask_pair<<<grid, 256, 0, stream>>>(pairs_dev, nl, c->n, c->mt); });
 }
 
 // T3[t] = sum_a A_a (x) R[t][a]: degree-2 output (d0, d1, d2) at nl2 limbs.  A_a is at a
@@ -1078,7 +1101,7 @@ __global__ void k_tensor_sum(const uint64_t* const* __restrict__ A_tab, const ui
 void launch_tensor_sum(blb_ctx* c, const uint64_t* const* A_tab, const uint64_t* const* R_tab, uint64_t* T3, int n_t, int n_ct, int nlA,
                        int nl2, bool a_per_t) {
   dim3 grid((c->n + 255) / 256, n_t * nl2);
-  k_tensor_sum<<<grid, 256, 0, c->stream>>>(A_tab, R_tab, T3, n_ct, nlA, nl2, c->n, c->mt, a_per_t ? 1 : 0);
+  emit(c, [=, stream = c->stream] { k_tensor_sum<<<grid, 256, 0, stream>>>(A_tab, R_tab, T3, n_ct, nlA, nl2, c->n, c->mt, a_per_t ? 1 : 0); });
 }
 
 // out[o] (+)= sum over its terms of ct (.) mask, whole degree-1 ciphertexts at nl limbs
@@ -1101,7 +1124,7 @@ __global__ void k_masked_acc(const CcTerm* __restrict__ terms, const int* __rest
 void launch_masked_acc(blb_ctx* c, const CcTerm* terms, const int* off, uint64_t* const* outs, int n_out, int nl, bool accumulate) {
   if (n_out <= 0) return;
   dim3 grid((2 * nl * c->n + 255) / 256, n_out);
-  k_masked_acc<<<grid, 256, 0, c->stream>>>(terms, off, outs, nl, c->n, c->mt, accumulate ? 1 : 0);
+  emit(c, [=, stream = c->stream] { k_masked_acc<<<grid, 256, 0, stream>>>(terms, off, outs, nl, c->n, c->mt, accumulate ? 1 : 0); });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1267,8 +1290,8 @@ void launch_cp_mac_batch(blb_ctx* c, const MacGroup* groups, const MacItem* item
   const int blocks = std::min(n_items, grid);
 #define MB(a, b, d)                                                                                   \
   do {                                                                                                \
-    if (p50) k_cp_mac_batch<a, b, d, true><<<blocks, 256, 0, c->stream>>>(groups, items, n_items, c->n, c->mt);  \
-    else k_cp_mac_batch<a, b, d, false><<<blocks, 256, 0, c->stream>>>(groups, items, n_items, c->n, c->mt); \
+    if (p50) emit(c, [=, stream = c->stream] { k_cp_mac_batch<a, b, d, true><<<blocks, 256, 0, stream>>>(groups, items, n_items, c->n, c->mt); });  \
+    else emit(c, [=, stream = c->stream] { k_cp_mac_batch<a, b, d, false><<<blocks, 256, 0, stream>>>(groups, items, n_items, c->n, c->mt); }); \
   } while (0)
   if (tb == 4 && ib == 1) MB(4, 1, 2);
   else if (tb == 2 && ib == 4) MB(2, 4, 2);
@@ -1300,7 +1323,7 @@ __global__ void k_sum_var(const uint64_t* const* __restrict__ srcs, const int* _
 void launch_sum_var(blb_ctx* c, const uint64_t* const* srcs, const int* off, uint64_t* const* dsts, int n_out, int nl) {
   if (n_out <= 0) return;
   dim3 grid((2 * nl * c->n + 255) / 256, n_out);
-  k_sum_var<<<grid, 256, 0, c->stream>>>(srcs, off, dsts, c->n, nl, c->mt);
+  emit(c, [=, stream = c->stream] { k_sum_var<<<grid, 256, 0, stream>>>(srcs, off, dsts, c->n, nl, c->mt); });
 }
 
 // out[t] = k * in[t] for whole degree-1 ciphertexts (exact integer scalar, every limb); in[t]
@@ -1318,5 +1341,5 @@ __global__ void k_scale_cts(const uint64_t* const* __restrict__ in, uint64_t* __
 void launch_scale_cts(blb_ctx* c, const uint64_t* const* in, uint64_t* out, int count, int nl, double k, int nl_in) {
   if (count <= 0) return;
   dim3 grid((2 * nl * c->n + 255) / 256, count);
-  k_scale_cts<<<grid, 256, 0, c->stream>>>(in, out, c->n, nl, nl_in > nl ? nl_in : nl, k, c->mt);
+  emit(c, [=, stream = c->stream] { k_scale_cts<<<grid, 256, 0, stream>>>(in, out, c->n, nl, nl_in > nl ? nl_in : nl, k, c->mt); });
 }

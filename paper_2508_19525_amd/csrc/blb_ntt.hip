@@ -387,18 +387,18 @@ void launch_ntt_pt(blb_ctx* c, NttSrc d_descs, int count, LoadOp ld, StoreOp st)
       const int per_cu = std::max(1, (160 * 1024) / (int)((c->n + c->n / 16) * sizeof(double)));
       const int grid = std::min(count, c->n_cu * per_cu);
       switch (c->log_n) {
-        case 12: k_ntt_pipe<12, PT, FWD><<<grid, threads, 0, c->stream>>>(d_descs, tw, c->mt, ld, st, count); break;
-        case 13: k_ntt_pipe<13, PT, FWD><<<grid, threads, 0, c->stream>>>(d_descs, tw, c->mt, ld, st, count); break;
-        case 14: k_ntt_pipe<14, PT, FWD><<<grid, threads, 0, c->stream>>>(d_descs, tw, c->mt, ld, st, count); break;
+        case 12: emit(c, [=, stream = c->stream] { k_ntt_pipe<12, PT, FWD><<<grid, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st, count); }); break;
+        case 13: emit(c, [=, stream = c->stream] { k_ntt_pipe<13, PT, FWD><<<grid, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st, count); }); break;
+        case 14: emit(c, [=, stream = c->stream] { k_ntt_pipe<14, PT, FWD><<<grid, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st, count); }); break;
         default: break;
       }
       return;
     }
   }
   switch (c->log_n) {
-    case 12: k_ntt<12, PT, FWD><<<count, threads, 0, c->stream>>>(d_descs, tw, c->mt, ld, st); break;
-    case 13: k_ntt<13, PT, FWD><<<count, threads, 0, c->stream>>>(d_descs, tw, c->mt, ld, st); break;
-    case 14: k_ntt<14, PT, FWD><<<count, threads, 0, c->stream>>>(d_descs, tw, c->mt, ld, st); break;
+    case 12: emit(c, [=, stream = c->stream] { k_ntt<12, PT, FWD><<<count, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st); }); break;
+    case 13: emit(c, [=, stream = c->stream] { k_ntt<13, PT, FWD><<<count, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st); }); break;
+    case 14: emit(c, [=, stream = c->stream] { k_ntt<14, PT, FWD><<<count, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st); }); break;
     default: break;
   }
 }

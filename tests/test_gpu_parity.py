@@ -659,6 +659,58 @@ def test_mac_shape_by_size(c2s, d_out, fmt):
     B.blb_keys_destroy(keys)
 
 
+def test_descriptor_ring_wraps(c1):
+    """Eager calls whose tables fill the 64 MiB descriptor ring more than once (about 3 KiB a rotation):
+    the last rotations equal the first, word for word."""
+    B = c1.B
+    rng = np.random.default_rng(1801)
+    steps = [1, 5]
+    keys = B.blb_keygen(c1.h, 1802, steps)
+    x, level = c1.ct(1), 1
+    mods = B.blb_ctx_moduli(c1.h, c1.n_q + c1.n_sp)[: level + 1]
+    B.blb_import(c1.h, np.stack([np.stack([rng.integers(0, int(q), c1.n, dtype=np.uint64) for q in mods]) for _ in range(2)]), x)
+    x.scale = 2.0 ** 30
+    y = [c1.ct(level) for _ in steps]
+    for k, st in enumerate(steps):
+        B.blb_rotate(c1.h, keys, x, st, y[k])
+    want = [c1.export(v) for v in y]
+    for i in range(30000):
+        B.blb_rotate(c1.h, keys, x, steps[i % 2], y[i % 2])
+    assert all(np.array_equal(c1.export(v), w) for v, w in zip(y, want))
+    B.blb_keys_destroy(keys)
+
+
+@pytest.mark.parametrize("n_blocks", [1, 2, 4])
+@pytest.mark.parametrize("direction,mask", [(0, False), (0, True), (1, False)])
+def test_rotate_sum_overlapping_outputs(c1, n_blocks, direction, mask):
+    """Sums and broadcasts of no, one and two steps whose outputs are the inputs' buffers in another
+    order give the words of a call with buffers of its own."""
+    B = c1.B
+    rng = np.random.default_rng(1803 + n_blocks)
+    block, level, n_ct = 64, 1, 3
+    steps = [s * st for st in (block, 2 * block) for s in (1, -1)]
+    keys = B.blb_keygen(c1.h, 1804, steps)
+    mods = B.blb_ctx_moduli(c1.h, c1.n_q + c1.n_sp)[: level + 1]
+    words = [np.stack([np.stack([rng.integers(0, int(q), c1.n, dtype=np.uint64) for q in mods]) for _ in range(2)]) for _ in range(n_ct)]
+
+    def inputs():
+        out = [c1.ct(level) for _ in range(n_ct)]
+        for x, w in zip(out, words):
+            B.blb_import(c1.h, w, x)
+            x.scale = 2.0 ** 30
+        return out
+
+    own = [c1.ct(level) for _ in range(n_ct)]
+    B.blb_rotate_sum(c1.h, keys, inputs(), own, block, n_blocks, direction, mask)
+    x = inputs()
+    over = [B.blb_ct(x[(t + 1) % n_ct].data, level, 1, 0.0) for t in range(n_ct)]
+    B.blb_rotate_sum(c1.h, keys, x, over, block, n_blocks, direction, mask)
+    for a, b in zip(own, over):
+        assert (a.level, a.scale) == (b.level, b.scale)
+        assert np.array_equal(c1.export(a), c1.export(b))
+    B.blb_keys_destroy(keys)
+
+
 # --------------------------------------------------------------------------------------
 # the batched transform on its own
 # --------------------------------------------------------------------------------------
