@@ -352,43 +352,53 @@ struct Pt50Raw {
   uint32_t top;
 };
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-// (p may come from a descriptor in memory: the planes are addressed as global memory explicitly,
-// so the loads are global, not flat, ones)
+// Byte offsets of word k's pieces in a limb-poly of n words: one set per work-item, added to the
+// (uniform) address of each limb-poly, so a row costs one scalar address, not one per plane (which
+// spilled at 8 rows x 4 coefficients).
+struct Pt50Off {
+  uint32_t lo, mid, top;
+};
+__device__ __forceinline__ Pt50Off pt50_off(int n, int k) {
+  Pt50Off o{4u * (uint32_t)k, 4u * (uint32_t)n + 2u * (uint32_t)k, 6u * (uint32_t)n + ((uint32_t)k >> 2)};
+  asm volatile("" : "+v"(o.lo), "+v"(o.mid), "+v"(o.top));  // opaque: kept out of the scalar address
+  return o;
+}
+// (p may come from a descriptor in memory: addressed as global memory explicitly, so the loads are
+// global, not flat, ones)
 template <int CPT>
-__device__ __forceinline__ void pt50_fetch(const uint8_t* __restrict__ p, int n, int k, Pt50Raw<CPT>& r) {
-  typedef __attribute__((address_space(1))) const uint32_t g32;
+__device__ __forceinline__ void pt50_fetch(const uint8_t* __restrict__ p, const Pt50Off& o, Pt50Raw<CPT>& r) {
+  typedef __attribute__((address_space(1))) const uint8_t g8;
   typedef __attribute__((address_space(1))) const uint16_t g16;
+  typedef __attribute__((address_space(1))) const uint32_t g32;
   typedef __attribute__((address_space(1))) const u32x2 g32x2;
   typedef __attribute__((address_space(1))) const u32x4 g32x4;
-  g32* lo = (g32*)p;
-  g16* mid = (g16*)(p + (size_t)4 * n);
-  g32* top = (g32*)(p + (size_t)6 * n);
+  g8* g = (g8*)p;
   if constexpr (CPT == 4) {
-    const u32x4 l = __builtin_nontemporal_load((g32x4*)(lo + k));
+    const u32x4 l = __builtin_nontemporal_load((g32x4*)(g + o.lo));
     r.lo[0] = l.x;
     r.lo[1] = l.y;
     r.lo[2] = l.z;
     r.lo[3] = l.w;
-    const u32x2 m = __builtin_nontemporal_load((g32x2*)(mid + k));
+    const u32x2 m = __builtin_nontemporal_load((g32x2*)(g + o.mid));
     r.mid[0] = m.x;
     r.mid[1] = m.y;
   } else if constexpr (CPT == 2) {
-    const u32x2 l = __builtin_nontemporal_load((g32x2*)(lo + k));
+    const u32x2 l = __builtin_nontemporal_load((g32x2*)(g + o.lo));
     r.lo[0] = l.x;
     r.lo[1] = l.y;
-    r.mid[0] = __builtin_nontemporal_load((g32*)(mid + k));
+    r.mid[0] = __builtin_nontemporal_load((g32*)(g + o.mid));
   } else {
-    r.lo[0] = __builtin_nontemporal_load(lo + k);
-    r.mid[0] = __builtin_nontemporal_load(mid + k);
+    r.lo[0] = __builtin_nontemporal_load((g32*)(g + o.lo));
+    r.mid[0] = __builtin_nontemporal_load((g16*)(g + o.mid));
   }
-  r.top = __builtin_nontemporal_load(top + (k >> 4));
+  r.top = __builtin_nontemporal_load(g + o.top);  // the byte that holds words k & ~3 .. k | 3 (u32 words, little-endian)
 }
 __device__ __forceinline__ double pt50_make(uint32_t lo, uint32_t mid16, uint32_t top2) {
   return __hiloint2double((int)(0x43300000u | (top2 << 16) | mid16), (int)lo) - BLB_TWO52;
 }
 template <int CPT>
 __device__ __forceinline__ void pt50_cvt(const Pt50Raw<CPT>& r, int k, double (&v)[CPT]) {
-  const uint32_t t = r.top >> (2 * (k & 15));
+  const uint32_t t = CPT == 4 ? r.top : r.top >> (2 * (k & 3));
 #pragma unroll
   for (int j = 0; j < CPT; ++j) v[j] = pt50_make(r.lo[j], (j & 1) ? r.mid[j / 2] >> 16 : r.mid[j / 2] & 0xFFFFu, (t >> (2 * j)) & 3u);
 }
@@ -433,6 +443,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
   size_t row[TB];
 #pragma unroll
   for (int t = 0; t < TB; ++t) row[t] = (size_t)min(t, rows - 1) * stride_bj;
+  const Pt50Off off50 = pt50_off(n, k0);
   Pt50Raw<CPT> w50[TB];
   u64x2 w64[TB][CPT / 2], r0[CPT / 2], r1[CPT / 2];
   auto fetch = [&](int ai) {
@@ -440,7 +451,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
     for (int t = 0; t < TB; ++t) {
       const uint8_t* poly = pbase + row[t] + (size_t)ai * stride_ai;
       if constexpr (P50) {
-        pt50_fetch<CPT>(poly, n, k0, w50[t]);
+        pt50_fetch<CPT>(poly, off50, w50[t]);
       } else {  // non-temporal: the plan is read once, the rotated inputs by every tile
 #pragma unroll
         for (int h = 0; h < CPT / 2; ++h) w64[t][h] = __builtin_nontemporal_load((gu64x2*)((gu64*)poly + k0 + 2 * h));
@@ -546,15 +557,17 @@ constexpr MacShape kMacShapes[BLB_MAC_VARIANTS] = {
 // neighbour: 64-bit words, 2304 waves (n_ai 192, n_bj 96, 3 limbs, N = 8192): {12,2,1,1} 540, {8,2,1,1}
 // 609 (the 256-thread {8,2,1,4}: 682); 1728 waves: {8,2,1,1} 401, {8,2,2,2} 429; 960: {8,2,2,2} 130,
 // {8,2,1,1} 139; 576: 245 against 373; 384: {4,2,4,4} 15.2, {8,2,2,2} 19.8; 128: {2,2,4,4} 12.4, {8,2,2,2} 23.
-// 50-bit words, 16384 waves: {8,4,1,4} 2386 (5.6 TB/s of packed words), {4,4,1,1} 2814; 2304: {4,4,1,1} 552,
-// {8,4,1,4} 670; 1728: {4,4,1,1} 363, {4,4,2,2} 419; 960: {4,4,2,2} 119, {4,4,1,1} 154; 384: {4,2,4,4} 15.4,
-// {4,4,2,2} 22; 128: {2,2,4,4} 12.6, {4,2,4,4} 14.2.  12 rows only where they pad the outputs by little.
+// 50-bit words, 16384 waves: {8,4,1,4} 2386 (5.6 TB/s of packed words), {4,4,1,1} 2814; 3072: {6,4,1,1} 343,
+// {4,4,1,1} 370; 2304: {6,4,1,1} 561, {4,4,1,1} 643, {8,4,1,4} 753 and 1728: {4,4,1,4} 418, {4,4,1,1} 438, {6,4,1,1} 465
+// (both inside the operator); 960: {4,4,2,2} 119, {4,4,1,1} 154; 384: {4,2,4,4} 15.4, {4,4,2,2} 22; 128:
+// {2,2,4,4} 12.6, {4,2,4,4} 14.2.  12 rows only where they pad the outputs by little.
 MacShape mac_shape_for(int n, int nl, int n_bj, int p50) {
   const int64_t cols = (int64_t)n * nl;
   if (p50) {
     const int64_t waves = cols / 256 * ((n_bj + 3) / 4);
     if (waves >= 4096) return kMacShapes[6];
-    if (waves >= 1536) return kMacShapes[7];
+    if (waves >= 2048) return kMacShapes[9];
+    if (waves >= 1536) return kMacShapes[17];
     if (waves >= 640) return kMacShapes[8];
     return kMacShapes[waves >= 256 ? 4 : 5];
   }
@@ -1150,6 +1163,7 @@ __global__ __launch_bounds__(256) void k_cp_mac_batch(const MacGroup* __restrict
     const MacGroup gr = groups[item.group];
     const int k0 = (item.kb * 256 + threadIdx.x) * CPT;
     if (k0 >= n) continue;
+    const Pt50Off off50 = pt50_off(n, k0);
     for (int limb = item.limb; limb < item.limb + item.n_limb; ++limb) {
     const int nl = gr.nl, n_ai = gr.n_ai, n_bj = gr.n_bj;
     const ModEntry me = mt.m[limb];
@@ -1171,7 +1185,7 @@ __global__ __launch_bounds__(256) void k_cp_mac_batch(const MacGroup* __restrict
 #pragma unroll
       for (int t = 0; t < TB; ++t) {
         if constexpr (P50) {
-          pt50_fetch<CPT>(pt[t] + (size_t)ai * term, n, k0, rw[t]);
+          pt50_fetch<CPT>(pt[t] + (size_t)ai * term, off50, rw[t]);
         } else {
           const gu64c* a = (const gu64c*)(pt[t] + (size_t)ai * term) + k0;
           if constexpr (CPT >= 2) {
