@@ -72,7 +72,9 @@ void blb_ctx_destroy(blb_ctx* ctx);
 int blb_ctx_moduli(const blb_ctx* ctx, uint64_t* out);
 /* Library-owned device bytes currently allocated (keys, plans, scratch). */
 uint64_t blb_ctx_device_bytes(const blb_ctx* ctx);
-/* Synchronises the stream and returns cached temporary memory of the eager path to the device. */
+/* Synchronises the stream and returns memory kept for later calls to the device: the temporaries of
+ * the eager path and the blocks of destroyed matmul_cp plans (at most 1/32 of the device's
+ * memory, kept for the next plans and not counted by blb_ctx_device_bytes). */
 int blb_ctx_trim(blb_ctx* ctx);
 const char* blb_status_str(int code);
 

@@ -82,11 +82,75 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // ------------------------------------------------------------------------------------------
 // device memory with budget accounting
 // ------------------------------------------------------------------------------------------
+// Idle plan memory.  Mapping and unmapping a plan's gigabytes takes longer than generating it
+// (3.6 GB: hipMalloc and hipFree about 92 ms, generation 5), so destroyed plans' blocks are kept for
+// the next plans, oldest given back first beyond 1/32 of the device's memory.  Blocks
+// enter the list after a device synchronisation (as hipFree does), so any context and stream of the
+// device may take them.  All are given back by blb_ctx_trim, with the device's last context, and
+// before an allocation of this library fails for lack of memory.
+struct IdleBlock {
+  int device;
+  void* p;
+  size_t bytes;
+};
+std::mutex g_idle_mu;
+std::deque<IdleBlock> g_idle;      // oldest first
+std::unordered_map<int, int> g_ctx_count;  // live contexts per device
+
+// frees the device's idle blocks, oldest first, until at most `keep` bytes remain; bytes freed
+size_t idle_release(int device, size_t keep) {
+  std::lock_guard<std::mutex> lk(g_idle_mu);
+  size_t held = 0, freed = 0;
+  for (const IdleBlock& b : g_idle)
+    if (b.device == device) held += b.bytes;
+  for (auto it = g_idle.begin(); it != g_idle.end() && held - freed > keep;) {
+    if (it->device != device) {
+      ++it;
+      continue;
+    }
+    (void)hipFree(it->p);
+    freed += it->bytes;
+    it = g_idle.erase(it);
+  }
+  return freed;
+}
+// the smallest idle block that fits and wastes at most a quarter of the request; null if there is none
+void* idle_take(int device, size_t bytes, size_t* got) {
+  std::lock_guard<std::mutex> lk(g_idle_mu);
+  auto best = g_idle.end();
+  for (auto it = g_idle.begin(); it != g_idle.end(); ++it)
+    if (it->device == device && it->bytes >= bytes && it->bytes - bytes <= bytes / 4 && (best == g_idle.end() || it->bytes < best->bytes))
+      best = it;
+  if (best == g_idle.end()) return nullptr;
+  void* p = best->p;
+  *got = best->bytes;
+  g_idle.erase(best);
+  return p;
+}
+size_t idle_bytes(int device) {
+  std::lock_guard<std::mutex> lk(g_idle_mu);
+  size_t held = 0;
+  for (const IdleBlock& b : g_idle)
+    if (b.device == device) held += b.bytes;
+  return held;
+}
+
+// hipMalloc, giving idle plan memory back when the device has none left
+hipError_t device_malloc(int device, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && idle_release(device, 0) > 0) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 int dalloc(blb_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) return BLB_OK;
   if (c->budget && c->dev_bytes + bytes > c->budget) return BLB_ENOMEM;
-  if (hipMalloc(p, bytes) != hipSuccess) {
+  if (c->budget && c->dev_bytes + idle_bytes(c->device) + bytes > c->budget) (void)idle_release(c->device, 0);
+  if (device_malloc(c->device, p, bytes) != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
     return BLB_ENOMEM;
@@ -98,6 +162,32 @@ void dfree(blb_ctx* c, void* p, size_t bytes) {
   if (!p) return;
   (void)hipFree(p);
   c->dev_bytes -= bytes;
+}
+
+// A plan's plaintexts: an idle block of about the size, else a new one.  *held: the block's bytes
+// (dev_bytes counts the plan's own).
+int plan_mem_alloc(blb_ctx* c, void** p, size_t bytes, size_t* held) {
+  *p = nullptr;
+  if (c->budget && c->dev_bytes + bytes > c->budget) return BLB_ENOMEM;
+  if ((*p = idle_take(c->device, bytes, held))) {
+    c->dev_bytes += bytes;
+    return BLB_OK;
+  }
+  *held = bytes;
+  return dalloc(c, p, bytes);
+}
+// (the caller has synchronised the streams that used it)
+void plan_mem_free(blb_ctx* c, void* p, size_t bytes, size_t held) {
+  if (!p) return;
+  c->dev_bytes -= bytes;
+  int cur = -1;
+  if (held > c->idle_cap || hipGetDevice(&cur) != hipSuccess || cur != c->device || hipDeviceSynchronize() != hipSuccess) {
+    (void)hipFree(p);
+    return;
+  }
+  (void)idle_release(c->device, c->idle_cap - held);
+  std::lock_guard<std::mutex> lk(g_idle_mu);
+  g_idle.push_back(IdleBlock{c->device, p, held});
 }
 
 // ------------------------------------------------------------------------------------------
@@ -137,7 +227,7 @@ void stack_fit(blb_ctx* c, Workspace* w) {
     (void)hipGetLastError();
     hipMemPool_t pool;
     if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
-    ok = hipMalloc((void**)&w->base, cap) == hipSuccess;
+    ok = device_malloc(c->device, (void**)&w->base, cap) == hipSuccess;
   }
   if (!ok) {
     (void)hipGetLastError();
@@ -207,8 +297,11 @@ struct Tmp {
     }
     if (hipMallocAsync(&p, bytes, c->stream) != hipSuccess) {
       (void)hipGetLastError();
-      failed = true;
-      return nullptr;
+      if (idle_release(c->device, 0) == 0 || hipMallocAsync(&p, bytes, c->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        failed = true;
+        return nullptr;
+      }
     }
     ptrs.push_back(p);
     return (T*)p;
@@ -791,8 +884,15 @@ int blb_ctx_create(const blb_params* prm, blb_ctx** out) {
   blb_ctx* c = new (std::nothrow) blb_ctx();
   if (!c) return BLB_ENOMEM;
   {
+    std::lock_guard<std::mutex> lk(g_idle_mu);
+    ++g_ctx_count[prm->device];
+  }
+  {
     hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, prm->device) == hipSuccess && prop.multiProcessorCount > 0) c->n_cu = prop.multiProcessorCount;
+    if (hipGetDeviceProperties(&prop, prm->device) == hipSuccess && prop.multiProcessorCount > 0) {
+      c->n_cu = prop.multiProcessorCount;
+      c->idle_cap = prop.totalGlobalMem / 32;
+    }
   }
   c->log_n = prm->log_n;
   c->n = 1 << prm->log_n;
@@ -906,6 +1006,12 @@ void blb_ctx_destroy(blb_ctx* c) {
   dfree(c, c->d_slot_inv, sizeof(int32_t) * (c->n / 2));
   dfree(c, c->d_flag, 256);
   for (int l = 0; l < BLB_MAXQ; ++l) dfree(c, c->d_kc[l], sizeof(KsLevelConst));
+  bool last;
+  {
+    std::lock_guard<std::mutex> lk(g_idle_mu);
+    last = --g_ctx_count[c->device] == 0;
+  }
+  if (last) (void)idle_release(c->device, 0);
   delete c;
 }
 
@@ -927,6 +1033,7 @@ int blb_ctx_trim(blb_ctx* c) {
     }
   hipMemPool_t pool;
   if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+  (void)idle_release(c->device, 0);
   return BLB_OK;
 }
 
@@ -1495,7 +1602,7 @@ int cp_plan_create(blb_ctx* c, const double* W, int d_in, int d_out, int L, int 
   if (mem) {
     P->pt = mem;
     P->owns_pt = false;
-  } else if ((rc = dalloc(c, (void**)&P->pt, P->bytes))) {
+  } else if ((rc = plan_mem_alloc(c, (void**)&P->pt, P->bytes, &P->held))) {
     delete P;
     return rc;
   }
@@ -1611,7 +1718,10 @@ int blb_plan_matmul_cp_diag_cplx(blb_ctx* c, const double* W, int n_heads, int d
 void blb_plan_destroy(blb_plan* P) {
   if (!P) return;
   (void)hipStreamSynchronize(P->ctx->stream);
-  if (P->owns_pt) dfree(P->ctx, P->pt, P->bytes);
+  if (P->owns_pt) {
+    if (P->kind == 1) plan_mem_free(P->ctx, P->pt, P->bytes, P->held);
+    else dfree(P->ctx, P->pt, P->bytes);
+  }
   for (size_t i = 0; i < P->extra.size(); ++i) dfree(P->ctx, P->extra[i], P->extra_bytes[i]);
   delete P;
 }

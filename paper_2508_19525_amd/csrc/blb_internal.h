@@ -244,6 +244,7 @@ struct blb_ctx {
   hipStream_t stream;
   uint64_t budget;
   uint64_t dev_bytes = 0;
+  size_t idle_cap = 0;  // most bytes of destroyed plans' memory kept for new plans (whole device)
   uint64_t mod[BLB_MAXM];
   ModTable mt;
   uint64_t* d_mods = nullptr;
@@ -318,6 +319,7 @@ struct blb_plan {
                  // matmul_cc: [2][T][limb][N] step-2 masks M^lo_t, M^hi_t (level, scale q_level 2^10),
                  // T = L' (plain schedule) or B (BSGS: baby steps only)
   size_t bytes;
+  size_t held = 0;  // matmul_cp: bytes of the block pt is in (at least `bytes`)
   // matmul_cc
   int heads, L, d, Lp, n_ct, n_out;
   int sched = 0;        // 0: an inner rotation of every B'_a per t; 1: BSGS (giant steps postponed into step 3)

@@ -711,6 +711,57 @@ def test_rotate_sum_overlapping_outputs(c1, n_blocks, direction, mask):
     B.blb_keys_destroy(keys)
 
 
+@pytest.mark.parametrize("d_out,d_out2", [(96, 96), (96, 80), (96, 32)])
+def test_plan_memory_is_reused_and_given_back(c1, d_out, d_out2):
+    """A plan made in a destroyed plan's memory (the same size, a little smaller, too small to take it)
+    gives the words of one in fresh memory; blb_ctx_device_bytes counts the plan's own bytes either
+    way, and blb_ctx_trim returns what is kept to the device."""
+    B = c1.B
+    rng = np.random.default_rng(1805)
+    L, d_in, level = 16, 64, 1
+    W, W2 = rng.normal(0, 0.02, (d_in, d_out)), rng.normal(0, 0.02, (d_in, d_out2))
+    mods = B.blb_ctx_moduli(c1.h, c1.n_q + c1.n_sp)[: level + 1]
+    keys = X = None
+
+    def product(plan):
+        nonlocal keys, X
+        g = B.blb_plan_info(plan)
+        if keys is None:
+            keys = B.blb_keygen(c1.h, 1806, [i * g["Lp"] for i in range(1, g["B"])] + [j * g["B"] * g["Lp"] for j in range(1, g["G"])])
+            X = [c1.ct(level) for _ in range(g["n_in"])]
+            for x in X:
+                B.blb_import(c1.h, np.stack([np.stack([rng.integers(0, int(q), c1.n, dtype=np.uint64) for q in mods]) for _ in range(2)]), x)
+                x.scale = 2.0 ** 30
+        Y = [c1.ct(level - 1) for _ in range(g["n_out"])]
+        B.blb_matmul_cp(c1.h, keys, plan, X, Y)
+        return [c1.export(y) for y in Y]
+
+    def bytes_of(plan):
+        g = B.blb_plan_info(plan)
+        return g["n_out"] * g["G"] * g["n_in"] * g["B"] * (level + 1) * c1.n * 8
+
+    B.blb_ctx_trim(c1.h)
+    plan = B.blb_plan_matmul_cp(c1.h, W2, L, level)  # fresh memory
+    want = product(plan)
+    B.blb_plan_destroy(plan)
+    B.blb_ctx_trim(c1.h)
+    free0 = torch.cuda.mem_get_info()[0]
+    first = B.blb_plan_matmul_cp(c1.h, W, L, level)
+    size = bytes_of(first)
+    product(first)
+    B.blb_plan_destroy(first)
+    held = B.blb_ctx_device_bytes(c1.h)
+    plan = B.blb_plan_matmul_cp(c1.h, W2, L, level)  # in the first plan's memory where it fits
+    assert B.blb_ctx_device_bytes(c1.h) - held == bytes_of(plan)
+    got = product(plan)
+    assert all(np.array_equal(a, b) for a, b in zip(want, got))
+    B.blb_plan_destroy(plan)
+    assert B.blb_ctx_device_bytes(c1.h) == held
+    B.blb_ctx_trim(c1.h)
+    assert torch.cuda.mem_get_info()[0] >= free0 - (size // 2 if size > (64 << 20) else 0)
+    B.blb_keys_destroy(keys)
+
+
 # --------------------------------------------------------------------------------------
 # the batched transform on its own
 # --------------------------------------------------------------------------------------
