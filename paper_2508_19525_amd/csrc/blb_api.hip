@@ -482,7 +482,8 @@ void copy_words(blb_ctx* c, uint64_t* dst, const uint64_t* src, size_t words) {
 }
 
 // descriptor batches can exceed the ring: split into chunks
-void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind) {
+// (most: source limbs of a base-conversion prologue; group: descriptors in a row that read the same words)
+void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind, int most = 1, int group = 1) {
   const size_t chunk = 16384;
   for (size_t off = 0; off < d.size(); off += chunk) {
     const size_t cnt = std::min(chunk, d.size() - off);
@@ -494,12 +495,13 @@ void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind) {
       case 0: launch_ntt(c, dd, (int)cnt, true); break;
       case 1: launch_ntt(c, dd, (int)cnt, false); break;
       case 2: launch_ntt_rescale(c, dd, (int)cnt); break;
-      case 3: launch_ntt_moddown(c, dd, (int)cnt); break;
+      case 3: launch_ntt_moddown(c, dd, (int)cnt, most, group); break;
       case 4: launch_ntt_addto(c, dd, (int)cnt); break;
+      case 5: launch_ntt_modup(c, dd, (int)cnt, most, group); break;
     }
   }
 }
-enum { NTT_FWD = 0, NTT_INV = 1, NTT_RESCALE = 2, NTT_MODDOWN = 3, NTT_ADDTO = 4 };
+enum { NTT_FWD = 0, NTT_INV = 1, NTT_RESCALE = 2, NTT_MODDOWN = 3, NTT_ADDTO = 4, NTT_MODUP = 5 };
 
 // in-place transform of count limb-polys stored back to back ([item][nl][N]); no table upload
 void ntt_regular(blb_ctx* c, uint64_t* base, size_t count, int nl, bool fwd) {
@@ -517,7 +519,8 @@ PolyDesc pd(const uint64_t* src, uint64_t* dst, int mod, int log_n) {
   memset(&d, 0, sizeof(d));
   d.src = src;
   d.dst = dst;
-  d.mod = mod;
+  d.mod = (int16_t)mod;
+  d.n_src = 1;
   d.log_n = log_n;
   return d;
 }
@@ -555,6 +558,7 @@ void build_ks_level(blb_ctx* c, int level, KsLevelConst* k) {
       for (int i2 = lo; i2 < hi; ++i2)
         if (i2 != i) prod = h_mul(prod, ext[i2] % ext[i], ext[i]);
       k->qhat_inv[j][i - lo] = (double)h_inv(prod, ext[i]);
+      k->qhat_scale[j][i - lo] = prod == 1 ? 0.0 : (double)h_mul(h_inv(prod, ext[i]), (uint64_t)k->ext[i].ninv, ext[i]);
       for (int e = 0; e < k->n_ext; ++e) {
         uint64_t pm = 1;
         for (int i2 = lo; i2 < hi; ++i2)
@@ -569,6 +573,7 @@ void build_ks_level(blb_ctx* c, int level, KsLevelConst* k) {
     for (int t2 = 0; t2 < c->n_sp; ++t2)
       if (t2 != t) prod = h_mul(prod, ext[nl + t2] % p, p);
     k->phat_inv[t] = (double)h_inv(prod, p);
+    k->phat_scale[t] = prod == 1 ? 0.0 : (double)h_mul(h_inv(prod, p), (uint64_t)k->ext[nl + t].ninv, p);
     for (int i = 0; i < nl; ++i) {
       uint64_t pm = 1;
       for (int t2 = 0; t2 < c->n_sp; ++t2)
@@ -607,6 +612,7 @@ struct KsReq {
   const uint64_t* add0;    // added to output poly 0 (permuted by add0_gal), may be null
   uint32_t add0_gal;
   const uint64_t* add1;    // added to output poly 1, may be null
+  bool both = false;       // add0 is added to output poly 0 unpermuted as well
 };
 
 // All sources are evaluation-form polys [nl][N] at `level`.  Each request writes
@@ -622,23 +628,29 @@ int ks_modup(blb_ctx* c, int level, const std::vector<const uint64_t*>& srcs, ui
   if (tmp.failed) return BLB_ENOMEM;
   std::vector<PolyDesc> d;
   d.reserve((size_t)S * nl);
+  // d_i N^-1 [Qhat_i^-1]_{q_i}: the inverse transforms leave y_i
   for (int s = 0; s < S; ++s)
-    for (int i = 0; i < nl; ++i) d.push_back(pd(srcs[s] + (size_t)i * n, dcoef + ((size_t)s * nl + i) * n, i, c->log_n));
+    for (int j = 0; j < nd; ++j)
+      for (int i = kc.dlo[j]; i < kc.dhi[j]; ++i) {
+        d.push_back(pd(srcs[s] + (size_t)i * n, dcoef + ((size_t)s * nl + i) * n, i, c->log_n));
+        d.back().aux2 = kc.qhat_scale[j][i - kc.dlo[j]];
+      }
   ntt_descs(c, d, NTT_INV);
   c->counters[6] += S;
-  {
-    Span sp(c, BLB_T_MODUP, (double)S * nd * n);
-    launch_modup(c, dcoef, X, c->d_kc[level], S, nl, n_ext, nd);
-  }
   d.clear();
+  int most = 1;
   for (int s = 0; s < S; ++s)
     for (int j = 0; j < nd; ++j)
       for (int e = 0; e < n_ext; ++e) {
         if (e >= kc.dlo[j] && e < kc.dhi[j]) continue;
-        uint64_t* p = X + (((size_t)s * nd + j) * n_ext + e) * n;
-        d.push_back(pd(p, p, e < nl ? e : c->n_q + (e - nl), c->log_n));
+        PolyDesc x = pd(dcoef + ((size_t)s * nl + kc.dlo[j]) * n, X + (((size_t)s * nd + j) * n_ext + e) * n,
+                        e < nl ? e : c->n_q + (e - nl), c->log_n);
+        x.n_src = (int16_t)(kc.dhi[j] - kc.dlo[j]);
+        x.cst = &c->d_kc[level]->qhat_mod[j][0][e];  // a device address, not read here
+        most = std::max(most, (int)x.n_src);
+        d.push_back(x);
       }
-  ntt_descs(c, d, NTT_FWD);
+  ntt_descs(c, d, NTT_MODUP, most, n_ext - most);
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
 size_t ks_modup_words(const blb_ctx* c, int level, int n_src) {
@@ -655,7 +667,6 @@ int ks_apply(blb_ctx* c, int level, const std::vector<const uint64_t*>& srcs, co
   const int O = (int)reqs.size();
   Tmp tmp(c);
   uint64_t* U = tmp.get<uint64_t>((size_t)O * 2 * n_ext * n);
-  uint64_t* corr = tmp.get<uint64_t>((size_t)O * 2 * nl * n);
   if (tmp.failed) return BLB_ENOMEM;
   std::vector<KsOut> ko(O);
   for (int o = 0; o < O; ++o) {
@@ -701,25 +712,25 @@ int ks_apply(blb_ctx* c, int level, const std::vector<const uint64_t*>& srcs, co
       for (int t = 0; t < c->n_sp; ++t) {
         uint64_t* ptr = U + (((size_t)o * 2 + p) * n_ext + nl + t) * n;
         d.push_back(pd(ptr, ptr, c->n_q + t, c->log_n));
+        d.back().aux2 = kc.phat_scale[t];
       }
   ntt_descs(c, d, NTT_INV);
-  {
-    Span sp(c, BLB_T_MODDOWN, (double)O * 2 * n);
-    launch_moddown_conv(c, U, corr, c->d_kc[level], O, nl, n_ext);
-  }
   d.clear();
   for (int o = 0; o < O; ++o)
     for (int p = 0; p < 2; ++p)
       for (int i = 0; i < nl; ++i) {
-        PolyDesc x = pd(corr + (((size_t)o * 2 + p) * nl + i) * n, reqs[o].dst + ((size_t)p * nl + i) * n, i, c->log_n);
+        PolyDesc x = pd(U + (((size_t)o * 2 + p) * n_ext + nl) * n, reqs[o].dst + ((size_t)p * nl + i) * n, i, c->log_n);
+        x.n_src = (int16_t)c->n_sp;
+        x.cst = &c->d_kc[level]->phat_mod[0][i];  // a device address, not read here
         x.src2 = U + (((size_t)o * 2 + p) * n_ext + i) * n;
         x.aux2 = kc.p_inv[i];
         const uint64_t* add = p == 0 ? reqs[o].add0 : reqs[o].add1;
         x.src3 = add ? add + (size_t)i * n : nullptr;
         x.gal = p == 0 ? reqs[o].add0_gal : 0;
+        x.flags = p == 0 && reqs[o].both ? kAddBoth : 0;
         d.push_back(x);
       }
-  ntt_descs(c, d, NTT_MODDOWN);
+  ntt_descs(c, d, NTT_MODDOWN, c->n_sp, nl);
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
 
@@ -3336,7 +3347,6 @@ static int rotate_sum_call(blb_ctx* c, const blb_keys* K, const blb_ct* in, int 
   const size_t ctw = (size_t)2 * nl * n;
   Tmp tmp(c);
   uint64_t* cur = tmp.get<uint64_t>((size_t)n_ct * ctw);
-  uint64_t* rot = tmp.get<uint64_t>((size_t)n_ct * ctw);
   uint64_t* mpt = mask ? tmp.get<uint64_t>((size_t)nl * n) : nullptr;
   if (tmp.failed) return BLB_ENOMEM;
   int rc = BLB_OK;
@@ -3345,28 +3355,19 @@ static int rotate_sum_call(blb_ctx* c, const blb_keys* K, const blb_ct* in, int 
   // the last sums go straight to the outputs unless a mask follows; a single step's sums read the
   // inputs, which outputs may overlap in another order, so they stay in `cur` too
   const bool direct = !mask && keys.size() >= 2;
-  // m^i = m^{i-1} + Rot^{2^{i-1} block}(m^{i-1}): one batch of n_ct key switches, then an add
+  // m^i = m^{i-1} + Rot^{2^{i-1} block}(m^{i-1}): one batch of n_ct key switches that add m^{i-1}
   for (size_t s = 0; s < keys.size(); ++s) {
     std::vector<const uint64_t*> srcs;
     std::vector<KsReq> reqs;
     for (int t = 0; t < n_ct; ++t) {
       const uint64_t* x = s == 0 ? in[t].data : cur + (size_t)t * ctw;
+      uint64_t* dst = direct && s + 1 == keys.size() ? out[t].data : cur + (size_t)t * ctw;
       srcs.push_back(x + (size_t)nl * n);
-      reqs.push_back(KsReq{t, keys[s], gals[s], rot + (size_t)t * ctw, x, gals[s], nullptr});
+      // sigma(x) + x: the key switch adds x to both output polys (in place from the second step on:
+      // each limb's transform reads its addend whole before it writes)
+      reqs.push_back(KsReq{t, keys[s], gals[s], dst, x, gals[s], x + (size_t)nl * n, true});
     }
     if ((rc = ks_batch(c, level, srcs, reqs))) return rc;
-    std::vector<const uint64_t*> terms;
-    std::vector<uint64_t*> dsts;
-    for (int t = 0; t < n_ct; ++t) {
-      terms.push_back(s == 0 ? in[t].data : cur + (size_t)t * ctw);
-      terms.push_back(rot + (size_t)t * ctw);
-      dsts.push_back(direct && s + 1 == keys.size() ? out[t].data : cur + (size_t)t * ctw);
-    }
-    const uint64_t* const* t_dev = upload_vec(c, terms);
-    uint64_t* const* d_dev = (uint64_t* const*)upload(c, dsts.data(), dsts.size() * sizeof(uint64_t*));
-    if (!t_dev || !d_dev) return BLB_EDEVICE;
-    Span sp(c, BLB_T_EW, (double)n_ct * ctw);
-    launch_sum_cts(c, t_dev, d_dev, n_ct, 2, nl);
   }
   std::vector<const uint64_t*> rin;
   std::vector<uint64_t*> rout;

@@ -81,6 +81,9 @@ struct KsLevelConst {
   double phat_inv[BLB_MAXSP];                     // [(P/p_t)^-1]_{p_t}
   double phat_mod[BLB_MAXSP][BLB_MAXQ];           // [P/p_t]_{q_i}
   double p_inv[BLB_MAXQ];                         // [P^-1]_{q_i}
+  // inverse-transform scales: N^-1 times qhat_inv / phat_inv (0 where that factor is 1: plain N^-1)
+  double qhat_scale[BLB_MAXQ][BLB_MAXALPHA];
+  double phat_scale[BLB_MAXSP];
 };
 
 // One key-switch output of a batch: source index (into the ModUp buffer), the source's c1
@@ -369,12 +372,10 @@ struct LimbVals {
 void launch_rlwe_combine(blb_ctx* c, uint64_t* out0, const uint64_t* a, const uint64_t* s, const uint64_t* e, const uint64_t* extra,
                          LimbVals extra_mul, int n_limbs, ModMap map);
 void launch_automorph(blb_ctx* c, uint64_t* out, const uint64_t* in, int count, uint32_t g);
-void launch_modup(blb_ctx* c, const uint64_t* dcoef, uint64_t* X, const KsLevelConst* kc_dev, int n_src, int nl, int n_ext, int n_digits);
 void launch_ks_inner(blb_ctx* c, const KsOut* outs_dev, int n_out, const uint64_t* X, const KsLevelConst* kc_dev, uint64_t* U, int nl,
                      int n_ext, int n_digits);
 void launch_ks_inner_grouped(blb_ctx* c, const KsOut* outs_dev, const int* ord_dev, const KsGroup* groups_dev, int n_groups,
                              const uint64_t* X, const KsLevelConst* kc_dev, uint64_t* U, int nl, int n_ext, int n_digits);
-void launch_moddown_conv(blb_ctx* c, const uint64_t* U, uint64_t* Corr, const KsLevelConst* kc_dev, int n_out, int nl, int n_ext);
 void launch_cp_mac(blb_ctx* c, const uint64_t* pt, const uint64_t* const* rx_tab, uint64_t* inner, int nl, int n_ai, int n_bj, int variant,
                    int p50);
 void launch_sum_cts(blb_ctx* c, const uint64_t* const* srcs, uint64_t* const* dsts, int n_out, int n_terms, int nl);

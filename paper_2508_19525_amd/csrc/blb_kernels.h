@@ -9,13 +9,19 @@ struct PolyDesc {
   uint64_t* dst;
   const uint64_t* src2;
   const uint64_t* src3;
-  double aux;   // prologue constant (e.g. the modulus whose residues are lifted)
-  double aux2;  // epilogue constant (e.g. q_l^-1 or P^-1 mod this modulus)
-  int32_t mod;  // modulus index of this poly
+  union {
+    double aux;         // prologue constant (e.g. the modulus whose residues are lifted)
+    const double* cst;  // base-conversion prologue: [Q_D / q_i] mod this modulus, one per source limb
+  };
+  double aux2;  // epilogue constant (e.g. q_l^-1 or P^-1 mod this modulus); inverse transforms: the
+                // scale that takes N^-1's place (0: N^-1)
+  int16_t mod;  // modulus index of this poly
+  int16_t n_src;  // base-conversion prologue: source limbs, stored back to back from src
   uint32_t gal; // Galois element applied to src3 (0 = none)
   int32_t log_n;
-  int32_t pad;
+  int32_t flags;  // kAddBoth: src3 is added as it is too, not only under the Galois element
 };
+constexpr int32_t kAddBoth = 1;
 
 // Bit-reversal of j over log_n bits
 __device__ __forceinline__ uint32_t brv_bits(uint32_t j, int log_n) { return __brev(j) >> (32 - log_n); }
@@ -31,7 +37,11 @@ __device__ __forceinline__ uint32_t gal_perm(uint32_t j, uint32_t g, int log_n) 
 
 void launch_ntt(blb_ctx* c, const PolyDesc* d_descs, int count, bool fwd);
 void launch_ntt_rescale(blb_ctx* c, const PolyDesc* d_descs, int count);
-void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count);
+// ModUp: source limbs of a digit (y_i = [d_i Qhat_i^-1]_{q_i}, coefficient form) -> evaluation form of
+// their base conversion; n_src <= most.  The descriptors of each `group` share their sources.
+void launch_ntt_modup(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group);
+// ModDown: special limbs (y_t = [u_t Phat_t^-1]_{p_t}, coefficient form) -> (u_i - conversion) P^-1 + addend
+void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group);
 void launch_ntt_addto(blb_ctx* c, const PolyDesc* d_descs, int count);
 // in-place transform of `count` limb-polys stored back to back at base ([item][nl][N]), no
 // descriptor table

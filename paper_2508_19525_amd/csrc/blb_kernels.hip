@@ -155,35 +155,6 @@ void launch_automorph(blb_ctx* c, uint64_t* out, const uint64_t* in, int count, 
 // ---------------------------------------------------------------------------------------
 // Key switching
 // ---------------------------------------------------------------------------------------
-// ModUp: fast basis conversion (no centring) of digit j of each source, coefficient form.
-//   x_m = sum_{i in D} [d_i * Qhat_i^-1]_{q_i} * [Qhat_i]_m  (mod m), for every extended
-//   modulus m outside the digit.  Writes X[s][j][e][k] for those e.
-// Thread per (s, j, k).
-__global__ void k_modup(const uint64_t* dcoef, uint64_t* X, const KsLevelConst* kc, int n, int nl, int n_ext, int n_digits) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = blockIdx.y % n_digits;
-  const int s = blockIdx.y / n_digits;
-  if (k >= n) return;
-  const int lo = kc->dlo[j], hi = kc->dhi[j];
-  double y[8];
-#pragma unroll 4
-  for (int i = lo; i < hi; ++i) {
-    const ModEntry mq = kc->ext[i];
-    y[i - lo] = canon(mulmod_s(u2d(dcoef[((size_t)s * nl + i) * n + k]), kc->qhat_inv[j][i - lo], mq.q, mq.qinv), mq.q);
-  }
-  for (int e = 0; e < n_ext; ++e) {
-    if (e >= lo && e < hi) continue;
-    const ModEntry mm = kc->ext[e];
-    double acc = 0.0;
-    for (int i = lo; i < hi; ++i) acc += mulmod_s(y[i - lo], kc->qhat_mod[j][i - lo][e], mm.q, mm.qinv);
-    X[(((size_t)s * n_digits + j) * n_ext + e) * n + k] = d2u(canon_full(acc, mm.q, mm.qinv));
-  }
-}
-void launch_modup(blb_ctx* c, const uint64_t* dcoef, uint64_t* X, const KsLevelConst* kc_dev, int n_src, int nl, int n_ext, int n_digits) {
-  dim3 grid((c->n + 255) / 256, n_src * n_digits);
-  emit(c, [=, stream = c->stream] { k_modup<<<grid, 256, 0, stream>>>(dcoef, X, kc_dev, c->n, nl, n_ext, n_digits); });
-}
-
 // Operands reached through descriptors in memory are addressed as global memory explicitly
 // (global, not flat, loads and stores: a flat access also counts against the LDS / scalar wait
 // counter and takes a 64-bit vector address).
@@ -309,29 +280,6 @@ void launch_ks_inner_grouped(blb_ctx* c, const KsOut* outs_dev, const int* ord_d
                              const uint64_t* X, const KsLevelConst* kc_dev, uint64_t* U, int nl, int n_ext, int n_digits) {
   dim3 grid((c->n / 2 + 255) / 256, n_groups * n_ext);
   emit(c, [=, stream = c->stream] { k_ks_inner_grp<<<grid, 256, 0, stream>>>(outs_dev, ord_dev, groups_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, n_digits, c->n_q); });
-}
-
-// ModDown conversion: corr_i = sum_t [u_{p_t} * Phat_t^-1]_{p_t} * [Phat_t]_{q_i}  (coefficient
-// form; U's special limbs must already be in coefficient form).  Thread per (o, poly, k).
-__global__ void k_moddown_conv(const uint64_t* U, uint64_t* Corr, const KsLevelConst* kc, int n, int nl, int n_ext, int n_sp) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const int op = blockIdx.y;  // o * 2 + poly
-  if (k >= n) return;
-  double y[4];
-  for (int t = 0; t < n_sp; ++t) {
-    const ModEntry mp = kc->ext[nl + t];
-    y[t] = canon(mulmod_s(u2d(U[((size_t)op * n_ext + nl + t) * n + k]), kc->phat_inv[t], mp.q, mp.qinv), mp.q);
-  }
-  for (int i = 0; i < nl; ++i) {
-    const ModEntry mq = kc->ext[i];
-    double acc = 0.0;
-    for (int t = 0; t < n_sp; ++t) acc += mulmod_s(y[t], kc->phat_mod[t][i], mq.q, mq.qinv);
-    Corr[((size_t)op * nl + i) * n + k] = d2u(canon_full(acc, mq.q, mq.qinv));
-  }
-}
-void launch_moddown_conv(blb_ctx* c, const uint64_t* U, uint64_t* Corr, const KsLevelConst* kc_dev, int n_out, int nl, int n_ext) {
-  dim3 grid((c->n + 255) / 256, n_out * 2);
-  emit(c, [=, stream = c->stream] { k_moddown_conv<<<grid, 256, 0, stream>>>(U, Corr, kc_dev, c->n, nl, n_ext, c->n_sp); });
 }
 
 // ---------------------------------------------------------------------------------------

@@ -30,7 +30,18 @@ struct NttSrc {
   uint64_t* base;
   int nl;
   int log_n;
-  __device__ __forceinline__ PolyDesc get(int p) const {
+  int group = 1;  // runs of this many descriptors read the same words
+  int count = 0;
+  // Workgroup w of the launch takes descriptor at(w): workgroups go round-robin over the 8 XCDs, so the
+  // `group` descriptors of a run are given to workgroups 8 apart and meet in one XCD's L2.
+  __device__ __forceinline__ int at(int w) const {
+    if (group <= 1) return w;
+    const int span = 8 * group, base = w / span * span;
+    if (base + span > count) return w;
+    return base + (w - base) % 8 * group + (w - base) / 8;
+  }
+  __device__ __forceinline__ PolyDesc get(int w) const {
+    const int p = at(w);
     if (descs) {
       // scalar loads (the table is read-only while the kernel runs): they do not join the
       // in-order vector-memory counter, so fetching a descriptor never waits for the stores
@@ -53,10 +64,11 @@ struct NttSrc {
     d.src3 = nullptr;
     d.aux = 0.0;
     d.aux2 = 0.0;
-    d.mod = p % nl;
+    d.mod = (int16_t)(p % nl);
+    d.n_src = 1;
     d.gal = 0;
     d.log_n = log_n;
-    d.pad = 0;
+    d.flags = 0;
     return d;
   }
 };
@@ -315,7 +327,7 @@ __global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_e
   double x[PT];
   ntt_load<LOGN, PT, FWD>(x, d, ld, q, qi, tid);
   ntt_core<LOGN, PT, FWD>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid);
-  ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, mt.m[d.mod].ninv, tid, lds);
+  ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
 }
 
 // Persistent, software-pipelined variant: a grid of resident workgroups walks the descriptor
@@ -371,7 +383,7 @@ __global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_e
       for (int i = 0; i < PF; ++i) nx[i] = ld.raw(dn, First::idx(tid, i));
     };
     ntt_core<LOGN, PT, FWD>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid, prefetch);
-    ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, mt.m[d.mod].ninv, tid, lds);
+    ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
     p = pn;
     if (p >= count) break;
   }
@@ -381,7 +393,7 @@ template <int PT, bool FWD, class LoadOp, class StoreOp>
 void launch_ntt_pt(blb_ctx* c, NttSrc d_descs, int count, LoadOp ld, StoreOp st) {
   const double* tw = FWD ? c->d_tw_fwd : c->d_tw_inv;
   const int threads = c->n / PT;
-  if constexpr (StoreOp::kPersistent) {
+  if constexpr (StoreOp::kPersistent && LoadOp::kPersistent) {
     if (c->ntt_variant == 1) {
       // resident workgroups: LDS per workgroup is 8.5 N bytes of 160 KiB per CU
       const int per_cu = std::max(1, (160 * 1024) / (int)((c->n + c->n / 16) * sizeof(double)));
@@ -421,7 +433,9 @@ __device__ __forceinline__ uint64_t gld(const uint64_t* p, int j) { return ((con
 __device__ __forceinline__ void gst(uint64_t* p, int j, uint64_t v) { ((gu64*)p)[j] = v; }
 
 // Loads: raw(d, j) fetches word j, cvt() turns it into this pass's double operand.
+// kPersistent: whether the persistent kernel, which prefetches one raw word per value, may run it.
 struct LdPlain {
+  static constexpr bool kPersistent = true;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
   __device__ double cvt(const PolyDesc&, uint64_t u, double, double) const { return u2d(u); }
   __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
@@ -443,6 +457,7 @@ struct StPlain {
 // load a residue of another modulus (aux = that modulus as double) and lift it centred into
 // this modulus: used by rescale (last limb -> limb i)
 struct LdCentredLift {
+  static constexpr bool kPersistent = true;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
   __device__ double cvt(const PolyDesc& d, uint64_t u, double q, double qi) const {
     const double v = u2d(u);
@@ -451,6 +466,31 @@ struct LdCentredLift {
     return reduce_s(t, q, qi);
   }
   __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
+};
+// Base conversion (no centring) of n_src limbs into this modulus, sum_i y_i cst_i with y_i < q_i of
+// limb i: the ModUp of a digit and the ModDown of the special limbs, done while the transform reads
+// its operands instead of in a pass of its own that wrote every converted limb and had it read
+// back (the conversions' write and read were a third of a key switch's ModDown traffic).  A single
+// limb's constant is 1 and its words, below 2^50, are operands as they are.
+// MOST: bound on n_src (1: one limb always); STRIDE: distance of the constants.
+template <int MOST, int STRIDE>
+struct LdConv {
+  static constexpr bool kPersistent = MOST == 1;
+  __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
+  __device__ double cvt(const PolyDesc&, uint64_t u, double, double) const { return u2d(u); }
+  __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const {
+    if constexpr (MOST == 1) return u2d(gld(d.src, j));
+    typedef __attribute__((address_space(4))) const double kdouble;
+    uint64_t u[MOST];
+#pragma unroll
+    for (int i = 0; i < MOST; ++i)
+      if (i < d.n_src) u[i] = gld(d.src + ((size_t)i << d.log_n), j);
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < MOST; ++i)  // |acc| < 8 x 0.875 q
+      if (i < d.n_src) acc += mulmod_s(u2d(u[i]), ((const kdouble*)d.cst)[i * STRIDE], q, qi);
+    return reduce_s(acc, q, qi);
+  }
 };
 // rescale epilogue: dst[j] <- (c_i[j] - v) * q_l^-1 mod q_i, c_i = d.src2, aux2 = q_l^-1 mod q_i
 struct StRescale {
@@ -466,7 +506,7 @@ struct StRescale {
   }
 };
 // ModDown epilogue: dst[j] <- (u_i[j] - v) * P^-1 (+ add[j] if src3), u_i = src2 (u64).
-// For a rotation add = sigma_g(c0), a permuted read of src3.  src3 is staged in LDS with
+// For a rotation add = sigma_g(c0), a permuted read of src3 (kAddBoth: sigma_g(c0) + c0).  src3 is staged in LDS with
 // coalesced reads (then read there, at the permuted index for a rotation), which keeps the
 // epilogue's global loads to one word per output.
 struct StModDown {
@@ -491,6 +531,10 @@ struct StModDown {
     if (d.src3) {
       r += lds[pad_idx(d.gal ? (int)gal_perm((uint32_t)j, d.gal, d.log_n) : j)];
       r = r >= q ? r - q : r;
+      if (d.flags & kAddBoth) {
+        r += lds[pad_idx(j)];
+        r = r >= q ? r - q : r;
+      }
     }
     gst(d.dst, j, d2u(r));
   }
@@ -568,8 +612,20 @@ void launch_ntt(blb_ctx* c, const PolyDesc* d_descs, int count, bool fwd) {
 void launch_ntt_rescale(blb_ctx* c, const PolyDesc* d_descs, int count) {
   launch_ntt_generic<true>(c, table(c, d_descs), count, LdCentredLift{}, StRescale{});
 }
-void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count) {
-  launch_ntt_generic<true>(c, table(c, d_descs), count, LdPlain{}, StModDown{});
+static NttSrc grouped(blb_ctx* c, const PolyDesc* d_descs, int count, int group) {
+  return NttSrc{d_descs, nullptr, 1, c->log_n, group, count};
+}
+void launch_ntt_modup(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group) {
+  const NttSrc src = grouped(c, d_descs, count, group);
+  if (most <= 1) launch_ntt_generic<true>(c, src, count, LdConv<1, BLB_MAXM>{}, StPlain{});
+  else if (most <= 2) launch_ntt_generic<true>(c, src, count, LdConv<2, BLB_MAXM>{}, StPlain{});
+  else launch_ntt_generic<true>(c, src, count, LdConv<BLB_MAXALPHA, BLB_MAXM>{}, StPlain{});
+}
+void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group) {
+  const NttSrc src = grouped(c, d_descs, count, group);
+  if (most <= 1) launch_ntt_generic<true>(c, src, count, LdConv<1, BLB_MAXQ>{}, StModDown{});
+  else if (most <= 2) launch_ntt_generic<true>(c, src, count, LdConv<2, BLB_MAXQ>{}, StModDown{});
+  else launch_ntt_generic<true>(c, src, count, LdConv<BLB_MAXSP, BLB_MAXQ>{}, StModDown{});
 }
 void launch_ntt_regular(blb_ctx* c, uint64_t* base, int count, int nl, bool fwd) {
   const NttSrc src{nullptr, base, nl, c->log_n};
