@@ -35,6 +35,8 @@ uint64_t h_pow(uint64_t a, uint64_t e, uint64_t m) {
 }
 uint64_t h_inv(uint64_t a, uint64_t p) { return h_pow(a % p, p - 2, p); }
 
+// the representative in (-m/2, m/2) (factors of the FP64 modular product: half the size, half its error)
+double h_centred(uint64_t a, uint64_t m) { return a > m / 2 ? -(double)(m - a) : (double)a; }
 bool h_is_prime(uint64_t n) {
   if (n < 2) return false;
   const uint64_t small[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};
@@ -558,7 +560,7 @@ void build_ks_level(blb_ctx* c, int level, KsLevelConst* k) {
       for (int i2 = lo; i2 < hi; ++i2)
         if (i2 != i) prod = h_mul(prod, ext[i2] % ext[i], ext[i]);
       k->qhat_inv[j][i - lo] = (double)h_inv(prod, ext[i]);
-      k->qhat_scale[j][i - lo] = prod == 1 ? 0.0 : (double)h_mul(h_inv(prod, ext[i]), (uint64_t)k->ext[i].ninv, ext[i]);
+      k->qhat_scale[j][i - lo] = prod == 1 ? 0.0 : h_centred(h_inv(h_mul(prod, (uint64_t)c->n, ext[i]), ext[i]), ext[i]);
       for (int e = 0; e < k->n_ext; ++e) {
         uint64_t pm = 1;
         for (int i2 = lo; i2 < hi; ++i2)
@@ -573,7 +575,7 @@ void build_ks_level(blb_ctx* c, int level, KsLevelConst* k) {
     for (int t2 = 0; t2 < c->n_sp; ++t2)
       if (t2 != t) prod = h_mul(prod, ext[nl + t2] % p, p);
     k->phat_inv[t] = (double)h_inv(prod, p);
-    k->phat_scale[t] = prod == 1 ? 0.0 : (double)h_mul(h_inv(prod, p), (uint64_t)k->ext[nl + t].ninv, p);
+    k->phat_scale[t] = prod == 1 ? 0.0 : h_centred(h_inv(h_mul(prod, (uint64_t)c->n, p), p), p);
     for (int i = 0; i < nl; ++i) {
       uint64_t pm = 1;
       for (int t2 = 0; t2 < c->n_sp; ++t2)
@@ -929,12 +931,12 @@ int blb_ctx_create(const blb_params* prm, blb_ctx** out) {
     const uint64_t q = c->mod[m];
     c->mt.m[m].q = (double)q;
     c->mt.m[m].qinv = 1.0 / (double)q;
-    c->mt.m[m].ninv = (double)h_inv((uint64_t)n, q);
+    c->mt.m[m].ninv = h_centred(h_inv((uint64_t)n, q), q);
     const uint64_t psi = h_root_2n(q, c->log_n), ipsi = h_inv(psi, q);
     for (int k = 0; k < n; ++k) {
       const uint32_t e = h_brv((uint32_t)k, c->log_n);
-      tw_f[(size_t)m * n + k] = (double)h_pow(psi, e, q);
-      tw_i[(size_t)m * n + k] = (double)h_pow(ipsi, e, q);
+      tw_f[(size_t)m * n + k] = h_centred(h_pow(psi, e, q), q);
+      tw_i[(size_t)m * n + k] = h_centred(h_pow(ipsi, e, q), q);
     }
   }
   int rc = BLB_OK;

@@ -51,6 +51,13 @@ __device__ __forceinline__ double reduce_s(double x, double q, double qinv) {
 }
 // signed-lazy (|x| < q) -> canonical [0, q)
 __device__ __forceinline__ double canon(double x, double q) { return x < 0.0 ? x + q : x; }
+// |x| <= 2q -> canonical.  floor(x / q) from fma(x, fl(1/q), 2^-51): at x = k q the estimate is at least k
+// (its errors, |k| 2^-53 and half an ulp, are below 2^-51 together), and at x = k q - 1 it is below k - 2^-52
+// (1/q > 2^-50), so the remainder is in [0, q) for every integer x.
+__device__ __forceinline__ double canon2(double x, double q, double qinv) {
+  const double t = __builtin_floor(__builtin_fma(x, qinv, 0x1p-51));
+  return __builtin_fma(-t, q, x);
+}
 // any |x| < 2^52 -> canonical
 __device__ __forceinline__ double canon_full(double x, double q, double qinv) { return canon(reduce_s(x, q, qinv), q); }
 
@@ -60,7 +67,7 @@ __device__ __forceinline__ double canon_full(double x, double q, double qinv) { 
 struct ModEntry {
   double q;
   double qinv;  // fl(1/q)
-  double ninv;  // N^-1 mod q
+  double ninv;  // N^-1 mod q, centred (|ninv| < q/2)
 };
 struct ModTable {
   ModEntry m[BLB_MAXM];

@@ -75,6 +75,40 @@ struct NttSrc {
 
 __host__ __device__ constexpr int pad_idx(int j) { return j + (j >> 4); }
 
+// Bounds (in units of q) of the GS = 2^R_LOG slots of a Gentleman-Sande pass whose operands are below
+// `in`: pre[u][k] marks the operands of stage u to reduce first (a sum would pass 8 otherwise),
+// post[k] the slots that leave the pass above `out`.
+template <int R_LOG>
+struct GsBounds {
+  static constexpr int GS = 1 << R_LOG;
+  bool pre[R_LOG][GS] = {};
+  bool post[GS] = {};
+  constexpr GsBounds(double in, double out) {
+    double b[GS] = {};
+    for (int k = 0; k < GS; ++k) b[k] = in;
+    for (int u = R_LOG - 1; u >= 0; --u) {
+      const int t = GS >> (u + 1);
+      for (int k = 0; k < GS; ++k) {
+        if (k & t) continue;
+        double &x = b[k], &y = b[k + t];
+        if (x + y > 8.0) {  // the larger one first
+          const bool first = x >= y;
+          (first ? x : y) = 0.5;
+          pre[u][first ? k : k + t] = true;
+        }
+        if (x + y > 8.0) {
+          x = y = 0.5;
+          pre[u][k] = pre[u][k + t] = true;
+        }
+        const double sum = x + y;
+        x = sum;
+        y = 0.5 + 0.1875 * sum;
+      }
+    }
+    for (int k = 0; k < GS; ++k) post[k] = b[k] > out;
+  }
+};
+
 // One pass of R_LOG radix-2 stages starting at global stage S0.  Work-item `tid` holds
 // PT values in registers: GPT groups of GS = 2^R_LOG values each, group h being the
 // butterfly group g = tid + h T (T = N / PT) whose members sit TL = N >> (S0 + R_LOG)
@@ -104,8 +138,24 @@ struct Pass {
   static constexpr int lds_off(int i) { return pad_idx(idx(0, i)) - pad_idx(idx(0, 0)); }
 
   // FWD: Cooley-Tukey stages in increasing order; else Gentleman-Sande in decreasing order.
-  template <bool FWD>
-  __device__ static __forceinline__ void run(double (&x)[PT], const double* __restrict__ tw, double q, double qi, int tid) {
+  // mid() runs after the first executed stage, when every operand has been read; sink(i) after
+  // register slot i has its last value, so that what follows (the exchange's LDS writes) is issued
+  // between the last stage's arithmetic instead of after it.  FIRST / LAST: the executed first /
+  // last pass of the transform.
+  template <bool FWD, bool FIRST, bool LAST, class Mid, class Sink>
+  __device__ static __forceinline__ void run(double (&x)[PT], const double* __restrict__ tw, double q, double qi, int tid, const Mid& mid,
+                                             const Sink& sink) {
+    // Lazy reduction.  Twiddles are centred (|w| <= q/2), so for |b| <= B q a product is below q/2 +
+    // 0.1875 B q (the quotient estimate is off by < B 2^-53 q, the dropped low part of b w is below
+    // that too), and every FP64 sum and product step is exact up to 8 q < 2^53.
+    // Forward: B' = 1.1875 B + 1/2.  From 1 (canonical words) six stages stay below 7.62, from 1/2
+    // (reduced) six below 6.22 and two below 1.8: values are reduced after stage (log2 N - 2) / 2 and
+    // after stage log2 N - 2, and come out below 1.8 q (canon2 makes them canonical).
+    // Inverse: a + b adds the bounds; GsBounds tracks each slot's through the pass and reduces only
+    // the operands whose sum could pass 8 (the all-sum slots) and, at the end of a pass, slots above 2.
+    // Against a reduction of every value each fourth (second, inverse) stage this is 10 % fewer
+    // instructions a transform.
+    constexpr GsBounds<R_LOG> gs(FIRST ? 1.0 : 2.0, LAST ? 8.0 : 2.0);
 #pragma unroll
     for (int uu = 0; uu < R_LOG; ++uu) {
       const int u = FWD ? uu : (R_LOG - 1 - uu);
@@ -124,27 +174,30 @@ struct Pass {
           const double w = tw[widx];
           double& a = x[h * GS + k];
           double& b = x[h * GS + k + t_loc];
-          // lazy reduction.  For |b| <= B, mulmod_s returns |v| < q/2 + 1.5 B q 2^-52
-          // < q/2 + 0.375 B (the quotient estimate is off by < B 2^-52, the dropped low part
-          // of b w is < B q 2^-53), so in the forward (Cooley-Tukey) butterfly the bound grows
-          // as B' = 1.375 B + q/2: from |x| <= q at the start of a pass, four stages stay below
-          // 7.01 q < 2^53, where every FP64 sum and product step is exact (a fifth would reach
-          // 10.1 q > 2^53); values are reduced after the fourth stage and at the end of the
-          // pass.  In the inverse (Gentleman-Sande) butterfly a + b can double, so it reduces
-          // after every second stage and at the end of the pass.
-          const bool red = FWD ? (u == R_LOG - 1 || u == 3) : ((u & 1) || (u == R_LOG - 1));
           if (FWD) {
+            const bool red = S0 + u + 1 == (LOGN - 2) / 2 || S0 + u + 1 == LOGN - 2;
             const double v = mulmod_s(b, w, q, qi);
             const double sum = a + v, dif = a - v;
             a = red ? reduce_s(sum, q, qi) : sum;
             b = red ? reduce_s(dif, q, qi) : dif;
           } else {
+            if (gs.pre[u][k]) a = reduce_s(a, q, qi);
+            if (gs.pre[u][k + t_loc]) b = reduce_s(b, q, qi);
             const double sum = a + b, dif = a - b;
-            a = red ? reduce_s(sum, q, qi) : sum;
+            a = sum;
             b = mulmod_s(dif, w, q, qi);
+            if (uu == R_LOG - 1) {
+              if (gs.post[k]) a = reduce_s(a, q, qi);
+              if (gs.post[k + t_loc]) b = reduce_s(b, q, qi);
+            }
+          }
+          if (uu == R_LOG - 1) {
+            sink(h * GS + k);
+            sink(h * GS + k + t_loc);
           }
         }
       }
+      if (uu == 0) mid();
     }
   }
 };
@@ -159,19 +212,26 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Move the register values from the layout of pass PA to the layout of pass PB through LDS.
-// The leading barrier keeps the writes behind every read of the previous exchange (also of
-// the previous polynomial in the persistent kernel).
-template <class PA, class PB, int PT>
-__device__ __forceinline__ void relayout(double* lds, double (&x)[PT], int tid) {
-  double* la = lds + pad_idx(PA::idx(tid, 0));
+// Slot i's LDS word for the writer (pass PA's layout) and all slots read in PB's layout.  The exchange
+// needs a barrier before the writes (behind every read of the previous exchange, also of the
+// previous polynomial in the persistent kernel): it stands inside pass PA, after its first stage.
+template <class P, int PT>
+struct LdsSink {
+  double* base;
+  const double (&x)[PT];
+  __device__ void operator()(int i) const { base[P::lds_off(i)] = x[i]; }
+};
+template <class PB, bool FWD, int PT>
+__device__ __forceinline__ void read_layout(const double* lds, double (&x)[PT], int tid) {
   const double* lb = lds + pad_idx(PB::idx(tid, 0));
   lds_barrier();
+  // in the order the next pass's first stage takes them: (k, k + GS/2) forward, (k, k + 1) inverse
 #pragma unroll
-  for (int i = 0; i < PT; ++i) la[PA::lds_off(i)] = x[i];
-  lds_barrier();
-#pragma unroll
-  for (int i = 0; i < PT; ++i) x[i] = lb[PB::lds_off(i)];
+  for (int i = 0; i < PT; ++i) {
+    const int h = i / PB::GS, r = i % PB::GS;
+    const int slot = FWD ? h * PB::GS + (r >> 1) + (r & 1) * (PB::GS / 2) : i;
+    x[slot] = lb[PB::lds_off(slot)];
+  }
 }
 
 // lds_off(i) is the same for every work-item of pass P
@@ -225,12 +285,22 @@ struct NoIssue {
   __device__ void operator()() const {}
 };
 
+struct LdsMid {
+  __device__ void operator()() const { lds_barrier(); }
+};
+struct NoMid {
+  __device__ void operator()() const {}
+};
+struct NoSink {
+  __device__ void operator()(int) const {}
+};
 // x holds the first pass's operands on entry and the last pass's results on exit.  issue()
 // enqueues the persistent kernel's prefetch of the next polynomial.  Vector loads complete in
 // issue order, so a per-lane twiddle load issued after the prefetch is waited for only once
 // the whole prefetch has arrived: issue() runs after the leading passes that load per-lane
-// twiddles (before the first pass when it has none).
-template <int LOGN, int PT, bool FWD, class Issue = NoIssue>
+// twiddles (before the first pass when it has none).  REUSED: the LDS may still be read by the
+// previous polynomial's last exchange (persistent kernel), so the first exchange needs its barrier too.
+template <int LOGN, int PT, bool FWD, bool REUSED, class Issue = NoIssue>
 __device__ __forceinline__ void ntt_core(double* lds, double (&x)[PT], const double* tw, double q, double qi, int tid,
                                          const Issue& issue = Issue()) {
   using S = Sched<LOGN, PT>;
@@ -238,37 +308,44 @@ __device__ __forceinline__ void ntt_core(double* lds, double (&x)[PT], const dou
   using P1 = typename S::P1;
   using P2 = typename S::P2;
   using P3 = typename S::P3;
+  using FirstMid = std::conditional_t<REUSED, LdsMid, NoMid>;
   constexpr int at = S::template issue_after<FWD>();  // passes run before issue()
+  auto sink = [&](auto pass) { return LdsSink<decltype(pass), PT>{lds + pad_idx(decltype(pass)::idx(tid, 0)), x}; };
   if constexpr (FWD) {
     if constexpr (at == 0) issue();
-    P0::template run<true>(x, tw, q, qi, tid);
+    P0::template run<true, true, false>(x, tw, q, qi, tid, FirstMid(), sink(P0()));
     if constexpr (at == 1) issue();
-    relayout<P0, P1>(lds, x, tid);
-    P1::template run<true>(x, tw, q, qi, tid);
+    read_layout<P1, true>(lds, x, tid);
+    P1::template run<true, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P1()));
     if constexpr (at == 2) issue();
-    relayout<P1, P2>(lds, x, tid);
-    P2::template run<true>(x, tw, q, qi, tid);
-    if constexpr (at == 3) issue();
+    read_layout<P2, true>(lds, x, tid);
     if constexpr (S::HAS3) {
-      relayout<P2, P3>(lds, x, tid);
-      P3::template run<true>(x, tw, q, qi, tid);
+      P2::template run<true, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P2()));
+      if constexpr (at == 3) issue();
+      read_layout<P3, true>(lds, x, tid);
+      P3::template run<true, false, true>(x, tw, q, qi, tid, NoMid(), NoSink());
       if constexpr (at == 4) issue();
+    } else {
+      P2::template run<true, false, true>(x, tw, q, qi, tid, NoMid(), NoSink());
+      if constexpr (at == 3) issue();
     }
   } else {
     // pass k of the inverse runs Pass index NP - 1 - k
     if constexpr (at == 0) issue();
     if constexpr (S::HAS3) {
-      P3::template run<false>(x, tw, q, qi, tid);
+      P3::template run<false, true, false>(x, tw, q, qi, tid, FirstMid(), sink(P3()));
       if constexpr (at == 1) issue();
-      relayout<P3, P2>(lds, x, tid);
+      read_layout<P2, false>(lds, x, tid);
+      P2::template run<false, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P2()));
+    } else {
+      P2::template run<false, true, false>(x, tw, q, qi, tid, FirstMid(), sink(P2()));
     }
-    P2::template run<false>(x, tw, q, qi, tid);
     if constexpr (at == S::NP - 2) issue();
-    relayout<P2, P1>(lds, x, tid);
-    P1::template run<false>(x, tw, q, qi, tid);
+    read_layout<P1, false>(lds, x, tid);
+    P1::template run<false, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P1()));
     if constexpr (at == S::NP - 1) issue();
-    relayout<P1, P0>(lds, x, tid);
-    P0::template run<false>(x, tw, q, qi, tid);
+    read_layout<P0, false>(lds, x, tid);
+    P0::template run<false, false, true>(x, tw, q, qi, tid, NoMid(), NoSink());
     if constexpr (at == S::NP) issue();
   }
 }
@@ -279,8 +356,9 @@ __device__ __forceinline__ void ntt_load(double (&x)[PT], const PolyDesc& d, con
   for (int i = 0; i < PT; ++i) x[i] = ld(d, FirstPass<LOGN, PT, FWD>::idx(tid, i), q, qi);
 }
 
-// canonical results of the last pass to global memory (the inverse applies N^-1 here; the
-// lazy passes leave |x| below ~2.5 q, which canon_full brings into [0, q))
+// results of the last pass to global memory, canonical unless the epilogue multiplies them anyway
+// (kLazy: it takes |v| < 1.8 q).  The inverse applies its scale (N^-1) here: |x| <= 8 q comes out of the
+// product below 2 q.
 template <int LOGN, int PT, bool FWD, class StoreOp>
 __device__ __forceinline__ void ntt_store(double (&x)[PT], const PolyDesc& d, const StoreOp& st, double q, double qi, double ninv, int tid,
                                           double* lds) {
@@ -290,7 +368,7 @@ __device__ __forceinline__ void ntt_store(double (&x)[PT], const PolyDesc& d, co
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
       j[i] = LastPass<LOGN, PT, FWD>::idx(tid, i);
-      v[i] = FWD ? canon(x[i], q) : canon_full(mulmod_s(x[i], ninv, q, qi), q, qi);
+      v[i] = canon2(FWD ? x[i] : mulmod_s(x[i], ninv, q, qi), q, qi);
     }
     st.template put_all<LOGN, PT>(d, j, v, lds, tid);
     return;
@@ -305,7 +383,8 @@ __device__ __forceinline__ void ntt_store(double (&x)[PT], const PolyDesc& d, co
 #pragma unroll
   for (int i = 0; i < PT; ++i) {
     const int j = LastPass<LOGN, PT, FWD>::idx(tid, i);
-    const double v = FWD ? canon(x[i], q) : canon_full(mulmod_s(x[i], ninv, q, qi), q, qi);
+    const double y = FWD ? x[i] : mulmod_s(x[i], ninv, q, qi);
+    const double v = FWD && StoreOp::kLazy ? y : canon2(y, q, qi);
     st.put(d, j, v, e[i], q, qi, lds);
   }
 }
@@ -326,7 +405,7 @@ __global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_e
   const int tid = threadIdx.x;
   double x[PT];
   ntt_load<LOGN, PT, FWD>(x, d, ld, q, qi, tid);
-  ntt_core<LOGN, PT, FWD>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid);
+  ntt_core<LOGN, PT, FWD, false>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid);
   ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
 }
 
@@ -382,7 +461,7 @@ __global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_e
 #pragma unroll
       for (int i = 0; i < PF; ++i) nx[i] = ld.raw(dn, First::idx(tid, i));
     };
-    ntt_core<LOGN, PT, FWD>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid, prefetch);
+    ntt_core<LOGN, PT, FWD, true>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid, prefetch);
     ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
     p = pn;
     if (p >= count) break;
@@ -393,17 +472,13 @@ template <int PT, bool FWD, class LoadOp, class StoreOp>
 void launch_ntt_pt(blb_ctx* c, NttSrc d_descs, int count, LoadOp ld, StoreOp st) {
   const double* tw = FWD ? c->d_tw_fwd : c->d_tw_inv;
   const int threads = c->n / PT;
+  // The persistent grid pays at N = 16384, where one polynomial fills a CU's LDS and nothing else hides
+  // its loads, from the third round of polynomials on (2048 of them: 125-135 us against 137-144 one per
+  // workgroup; 512: equal; 256: 23 against 21).  At N = 4096 / 8192 four / two workgroups per CU overlap
+  // by themselves: one polynomial each is faster at every count (1024 at N = 8192: 34 us against 38-40).
   if constexpr (StoreOp::kPersistent && LoadOp::kPersistent) {
-    if (c->ntt_variant == 1) {
-      // resident workgroups: LDS per workgroup is 8.5 N bytes of 160 KiB per CU
-      const int per_cu = std::max(1, (160 * 1024) / (int)((c->n + c->n / 16) * sizeof(double)));
-      const int grid = std::min(count, c->n_cu * per_cu);
-      switch (c->log_n) {
-        case 12: emit(c, [=, stream = c->stream] { k_ntt_pipe<12, PT, FWD><<<grid, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st, count); }); break;
-        case 13: emit(c, [=, stream = c->stream] { k_ntt_pipe<13, PT, FWD><<<grid, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st, count); }); break;
-        case 14: emit(c, [=, stream = c->stream] { k_ntt_pipe<14, PT, FWD><<<grid, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st, count); }); break;
-        default: break;
-      }
+    if (c->ntt_variant == 1 && c->log_n == 14 && count > 2 * c->n_cu) {
+      emit(c, [=, stream = c->stream] { k_ntt_pipe<14, PT, FWD><<<c->n_cu, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st, count); });
       return;
     }
   }
@@ -446,6 +521,7 @@ struct LdPlain {
 // stages an operand through registers into LDS; next to a register prefetch of the following
 // polynomial that no longer fits 128 VGPRs, so it always runs one polynomial per workgroup.
 struct StPlain {
+  static constexpr bool kLazy = false;
   static constexpr bool kPersistent = true;
   static constexpr bool kPack = false;
   struct Operand {};
@@ -494,6 +570,7 @@ struct LdConv {
 };
 // rescale epilogue: dst[j] <- (c_i[j] - v) * q_l^-1 mod q_i, c_i = d.src2, aux2 = q_l^-1 mod q_i
 struct StRescale {
+  static constexpr bool kLazy = true;
   static constexpr bool kPersistent = true;
   static constexpr bool kPack = false;
   using Operand = uint64_t;
@@ -501,8 +578,8 @@ struct StRescale {
   __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc& d, int j) const { return gld(d.src2, j); }
   __device__ void put(const PolyDesc& d, int j, double v, Operand ci, double q, double qi, const double*) const {
-    const double r = mulmod_s(u2d(ci) - v, d.aux2, q, qi);
-    gst(d.dst, j, d2u(canon(r, q)));
+    const double r = mulmod_s(u2d(ci) - v, d.aux2, q, qi);  // |c_i - v| < 2.8 q: |r| < 1.6 q
+    gst(d.dst, j, d2u(canon2(r, q, qi)));
   }
 };
 // ModDown epilogue: dst[j] <- (u_i[j] - v) * P^-1 (+ add[j] if src3), u_i = src2 (u64).
@@ -510,6 +587,7 @@ struct StRescale {
 // coalesced reads (then read there, at the permuted index for a rotation), which keeps the
 // epilogue's global loads to one word per output.
 struct StModDown {
+  static constexpr bool kLazy = true;
   static constexpr bool kPersistent = false;
   static constexpr bool kPack = false;
   using Operand = uint64_t;
@@ -527,7 +605,7 @@ struct StModDown {
   }
   __device__ Operand fetch(const PolyDesc& d, int j) const { return gld(d.src2, j); }
   __device__ void put(const PolyDesc& d, int j, double v, Operand ui, double q, double qi, const double* lds) const {
-    double r = canon(mulmod_s(u2d(ui) - v, d.aux2, q, qi), q);
+    double r = canon2(mulmod_s(u2d(ui) - v, d.aux2, q, qi), q, qi);  // |u_i - v| < 2.8 q: |product| < 1.6 q
     if (d.src3) {
       r += lds[pad_idx(d.gal ? (int)gal_perm((uint32_t)j, d.gal, d.log_n) : j)];
       r = r >= q ? r - q : r;
@@ -545,6 +623,7 @@ struct StModDown {
 // pt50_bytes(N), the poly index recovered from the batch's source address.  The top-bit codes
 // are gathered in LDS (free after the last pass), then each u32 of 16 codes written once.
 struct StPack50 {
+  static constexpr bool kLazy = false;
   static constexpr bool kPersistent = false;
   static constexpr bool kPack = true;
   struct Operand {};
@@ -588,6 +667,7 @@ struct StPack50 {
 
 // add-into epilogue: dst[j] <- src2[j] + v mod q  (mask added to c0 in evaluation form)
 struct StAddTo {
+  static constexpr bool kLazy = false;
   static constexpr bool kPersistent = true;
   static constexpr bool kPack = false;
   using Operand = uint64_t;

@@ -809,3 +809,31 @@ def test_ntt_matches_oracle(request, name, n_polys, variant, radix):
     with pytest.raises(B.BlbError):
         B.blb_ntt(c.h, dev, 1, nl + 1)
     B.blb_ntt(c.h, dev, 0, 1)
+
+
+@pytest.mark.parametrize("n_polys", [85, 86, 130])
+def test_ntt_persistent_grid(c3s, n_polys):
+    """The persistent grid (N = 16384, more than two limb-polys per compute unit: 86 and 130 polys of 6 limbs
+    on 256 of them; 85 is one workgroup each) gives the words of one workgroup per limb-poly in both
+    directions, and the inverse returns the input; the extreme residues 0 and q - 1 are among them."""
+    B = c3s.B
+    mods = B.blb_ctx_moduli(c3s.h, c3s.n_q + c3s.n_sp)
+    rng = np.random.default_rng(1807 + n_polys)
+    one = np.stack([rng.integers(0, int(q), c3s.n, dtype=np.uint64) for q in mods])
+    one[:, :64] = 0
+    one[:, 64:128] = (mods - 1)[:, None]
+    words = np.stack([np.roll(one, 37 * p, axis=1) for p in range(n_polys)])
+    words[-1] = (mods - 1)[:, None]
+    out = []
+    for variant in (0, 1):
+        B.blb_ctx_set_knob(c3s.h, B.BLB_KNOB_NTT_VARIANT, variant)
+        t = torch.from_numpy(words.view(np.int64).reshape(-1).copy()).cuda()
+        B.blb_ntt(c3s.h, t, n_polys, len(mods))
+        torch.cuda.synchronize()
+        fwd = t.cpu().numpy().copy()
+        B.blb_ntt(c3s.h, t, n_polys, len(mods), True)
+        torch.cuda.synchronize()
+        assert np.array_equal(t.cpu().numpy().view(np.uint64).reshape(words.shape), words)
+        out.append(fwd)
+    B.blb_ctx_set_knob(c3s.h, B.BLB_KNOB_NTT_VARIANT, 1)
+    assert np.array_equal(out[0], out[1])
