@@ -781,19 +781,24 @@ int check_ct(const blb_ctx* c, const blb_ct* ct) {
   return BLB_OK;
 }
 
-// encode `count` dense slot vectors (device, [count][n_vals]) into coefficient residues
-int encode_dense_dev(blb_ctx* c, const double* d_vals, int n_vals, int count, double scale, int level, uint64_t* out) {
-  const int M = c->n / 2;
+// encode `count` dense slot vectors (device, [count][n_vals]) into integer coefficients coef[count][N]
+int encode_dense_dev(blb_ctx* c, const double* d_vals, int n_vals, int count, double scale, uint64_t* coef) {
   Tmp tmp(c);
-  double* a = tmp.get<double>((size_t)count * M * 4);
-  double* b = tmp.get<double>((size_t)count * M * 4);
+  double* z = tmp.get<double>((size_t)count * (c->n / 2) * 4);
   if (tmp.failed) return BLB_ENOMEM;
   (void)hipMemsetAsync(c->d_flag, 0, sizeof(int), c->stream);
-  run_encode_dense(c, d_vals, n_vals, count, a, b, scale, level + 1, out, c->d_flag);
+  run_encode_dense(c, d_vals, n_vals, count, z, scale, coef, c->d_flag);
   int flag = 0;
   (void)hipMemcpyAsync(&flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream);
   if (hipStreamSynchronize(c->stream) != hipSuccess) return BLB_EDEVICE;
   return flag ? BLB_EINVAL : BLB_OK;
+}
+
+// evaluation-form limbs of `count` plaintexts' integer coefficients
+void ntt_plan(blb_ctx* c, const uint64_t* coef, uint8_t* out, int count, int nl, int p50) {
+  Span sp(c, BLB_T_NTT, (double)count * nl);
+  c->counters[1] += (int64_t)count * nl;
+  launch_ntt_plan(c, coef, out, count, nl, p50);
 }
 
 }  // namespace
@@ -1284,7 +1289,12 @@ int blb_encode(blb_ctx* c, const double* v, int64_t n_vals, double scale, int le
   double* dv = tmp.get<double>((size_t)std::max<int64_t>(n_vals, 1));
   if (tmp.failed) return BLB_ENOMEM;
   if (n_vals > 0 && hipMemcpyAsync(dv, v, n_vals * 8, hipMemcpyHostToDevice, c->stream) != hipSuccess) return BLB_EDEVICE;
-  return encode_dense_dev(c, dv, (int)n_vals, 1, scale, level, pt_dev);
+  uint64_t* coef = tmp.get<uint64_t>((size_t)c->n);
+  if (tmp.failed) return BLB_ENOMEM;
+  const int rc = encode_dense_dev(c, dv, (int)n_vals, 1, scale, coef);
+  if (rc) return rc;
+  launch_coef_residues(c, coef, pt_dev, 1, level + 1);
+  return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
 
 int blb_encrypt(blb_ctx* c, const blb_keys* K, const uint64_t* pt_dev, int level, double scale, uint64_t seed, uint32_t ct_id,
@@ -1624,10 +1634,9 @@ int cp_plan_create(blb_ctx* c, const double* W, int d_in, int d_out, int L, int 
   {
     Tmp tmp(c);
     const double* dW = W_dev;
-    double* a = tmp.get<double>((size_t)chunk * M * 4);
-    double* b = tmp.get<double>((size_t)chunk * M * 4);
-    // 50-bit format: a chunk of plaintexts is encoded here, then transformed and packed into the plan
-    uint64_t* raw = P->p50 ? tmp.get<uint64_t>((size_t)chunk * nl * n) : nullptr;
+    double* z = tmp.get<double>((size_t)(g.cplx ? chunk : chunk / 2) * M * 4);
+    // a chunk's integer coefficients, transformed (and packed, in the 50-bit format) into the plan
+    uint64_t* coef = tmp.get<uint64_t>((size_t)chunk * n);
     if (!dW) {
       double* w = tmp.get<double>((size_t)d_in * d_out);
       if (w && hipMemcpyAsync(w, W, (size_t)d_in * d_out * 8, hipMemcpyHostToDevice, c->stream) != hipSuccess) {
@@ -1652,15 +1661,8 @@ int cp_plan_create(blb_ctx* c, const double* W, int d_in, int d_out, int L, int 
     const double scale = (double)c->mod[level] / BLB_NOISE_BOOST;
     for (size_t p0 = 0; p0 < n_pt; p0 += chunk) {
       const int cnt = (int)std::min<size_t>(chunk, n_pt - p0);
-      uint64_t* dst = P->p50 ? raw : P->pt + p0 * nl * n;
-      run_encode_cp(c, dW, g, (int)p0, cnt, a, b, scale, nl, dst, c->d_flag, dg);
-      if (P->p50) {
-        Span sp(c, BLB_T_NTT, (double)cnt * nl);
-        c->counters[1] += (int64_t)cnt * nl;
-        launch_ntt_pack50(c, raw, (uint8_t*)P->pt + p0 * nl * pt50_bytes(n), cnt * nl, nl);
-      } else {
-        ntt_regular(c, dst, (size_t)cnt * nl, nl, true);
-      }
+      run_encode_cp(c, dW, g, (int)p0, cnt, z, scale, coef, c->d_flag, dg);
+      ntt_plan(c, coef, (uint8_t*)P->pt + p0 * nl * pt_poly_bytes(n, P->p50), cnt, nl, P->p50);
     }
     if (flag_host) {
       if (hipMemcpyAsync(flag_host, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess) {
@@ -1971,21 +1973,15 @@ int encode_vectors_ntt(blb_ctx* c, const std::vector<double>& vecs, int count, d
   const int chunk = 256;
   Tmp tmp(c);
   double* dv = tmp.get<double>((size_t)chunk * S);
+  uint64_t* coef = tmp.get<uint64_t>((size_t)chunk * n);
   if (tmp.failed) return BLB_ENOMEM;
   for (int p0 = 0; p0 < count; p0 += chunk) {
     const int cnt = std::min(chunk, count - p0);
     if (hipMemcpyAsync(dv, vecs.data() + (size_t)p0 * S, (size_t)cnt * S * 8, hipMemcpyHostToDevice, c->stream) != hipSuccess)
       return BLB_EDEVICE;
-    uint64_t* dst = out + (size_t)p0 * nl * n;
-    int rc = encode_dense_dev(c, dv, S, cnt, scale, level, dst);
+    const int rc = encode_dense_dev(c, dv, S, cnt, scale, coef);
     if (rc) return rc;
-    std::vector<PolyDesc> d;
-    for (int p = 0; p < cnt; ++p)
-      for (int i = 0; i < nl; ++i) {
-        uint64_t* x = dst + ((size_t)p * nl + i) * n;
-        d.push_back(pd(x, x, i, c->log_n));
-      }
-    ntt_descs(c, d, NTT_FWD);
+    ntt_plan(c, coef, (uint8_t*)(out + (size_t)p0 * nl * n), cnt, nl, 0);
   }
   return hipStreamSynchronize(c->stream) == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
@@ -3380,10 +3376,11 @@ static int rotate_sum_call(blb_ctx* c, const blb_keys* K, const blb_ct* in, int 
   if (mask) {
     // keep the first block: mask [1 x block, 0, ...] at scale q_level, then rescale
     // (coefficients of a 0/1 vector are at most the scale: the encoder cannot overflow)
-    double* buf = tmp.get<double>((size_t)2 * S * 4);
+    double* z = tmp.get<double>((size_t)S * 4);
+    uint64_t* coef = tmp.get<uint64_t>((size_t)n);
     if (tmp.failed) return BLB_ENOMEM;
-    run_encode_block(c, block, buf, buf + (size_t)S * 4, (double)c->mod[level], nl, mpt, c->d_flag);
-    ntt_regular(c, mpt, nl, nl, true);
+    run_encode_block(c, block, z, (double)c->mod[level], coef, c->d_flag);
+    ntt_plan(c, coef, (uint8_t*)mpt, 1, nl, 0);
     std::vector<CcPair> pairs;
     for (int t = 0; t < n_ct; ++t) pairs.push_back(CcPair{cur + (size_t)t * ctw, mpt, nullptr, nullptr, cur + (size_t)t * ctw});
     const CcPair* p_dev = upload_vec(c, pairs);

@@ -58,6 +58,10 @@ __device__ __forceinline__ double canon2(double x, double q, double qinv) {
   const double t = __builtin_floor(__builtin_fma(x, qinv, 0x1p-51));
   return __builtin_fma(-t, q, x);
 }
+// a signed 64-bit integer (|v| < 2^62, two's complement in u) mod q, |result| < q/2 + 2^33
+__device__ __forceinline__ double i64_mod(uint64_t u, double q, double qinv) {
+  return mulmod_s((double)(int32_t)(u >> 32), 4294967296.0, q, qinv) + (double)(uint32_t)u;
+}
 // any |x| < 2^52 -> canonical
 __device__ __forceinline__ double canon_full(double x, double q, double qinv) { return canon(reduce_s(x, q, qinv), q); }
 
@@ -389,9 +393,10 @@ void launch_sum_cts(blb_ctx* c, const uint64_t* const* srcs, uint64_t* const* ds
 void launch_mask_pair(blb_ctx* c, const CcPair* pairs_dev, int n_pairs, int nl);
 int batch_mac_shape(int variant, int* tb, int* ib, int* cpt);
 void launch_cp_mac_batch(blb_ctx* c, const MacGroup* groups, const MacItem* items, int n_items, int variant, int grid, int p50);
-// forward NTT of count limb-polys stored back to back at base ([item][nl][N]); the results go
-// to out in the 50-bit plan format (base is left as it was)
-void launch_ntt_pack50(blb_ctx* c, const uint64_t* base, uint8_t* out, int count, int nl);
+// forward NTT of `count` plaintexts' integer coefficients coef[count][N] (int64) into every limb of
+// out[count][nl]: evaluation-form words, or the 50-bit plan format (p50)
+void launch_ntt_plan(blb_ctx* c, const uint64_t* coef, uint8_t* out, int count, int nl, int p50);
+void launch_coef_residues(blb_ctx* c, const uint64_t* coef, uint64_t* out, int count, int nl);
 void launch_sum_var(blb_ctx* c, const uint64_t* const* srcs, const int* off, uint64_t* const* dsts, int n_out, int nl);
 // out[t] ([2][nl][N]) = k * (the first nl limbs of each poly of in[t], stored with nl_in >= nl limbs)
 void launch_scale_cts(blb_ctx* c, const uint64_t* const* in, uint64_t* out, int count, int nl, double k, int nl_in = 0);
@@ -407,9 +412,9 @@ void launch_masked_acc(blb_ctx* c, const CcTerm* terms, const int* off, uint64_t
 void launch_mask_sample(blb_ctx* c, uint64_t* r_out, uint64_t* share, int n_ct, int tl, uint64_t seed, const uint64_t* seed_dev, uint32_t tag);
 void launch_set_u64(blb_ctx* c, uint64_t* dst, uint64_t value);
 void launch_zero(blb_ctx* c, uint64_t* dst, size_t words);
-// paired: the buffers hold (count + 1) / 2 complex vectors, each packing two real inputs
-int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
-                     int* d_overflow);
-int run_encode_block(blb_ctx* c, int block, double* bufA, double* bufB, double scale, int nl, uint64_t* out, int* d_overflow);
-int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
-                  int* d_overflow, CpDiag dg = CpDiag{nullptr, 0, 0, 0});
+// Encoders: integer coefficients coef[count][N] (int64 in 64-bit words); zbuf: 32 bytes x N/2 per complex
+// vector ((count + 1) / 2 of them for run_encode_cp without g.cplx, which packs two real inputs in each)
+int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow);
+int run_encode_block(blb_ctx* c, int block, double* zbuf, double scale, uint64_t* coef, int* d_overflow);
+int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow,
+                  CpDiag dg = CpDiag{nullptr, 0, 0, 0});

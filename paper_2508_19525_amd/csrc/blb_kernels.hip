@@ -768,8 +768,8 @@ struct EncSrcCp {
 // more into radix-8 DFTs held in registers (M1 = 8 R2 with R2 = 2, 4 or 8; M2 = 8 x 16), with one
 // exchange through LDS in between.
 constexpr int kEncM2 = 128;
-constexpr int kEncCB = 16;     // columns (n2) per workgroup in the column pass
-constexpr int kEncRB = 8;      // rows (k1) per workgroup in the row pass
+constexpr int kEncThreads = 128;  // work-items of a column-pass workgroup
+constexpr int kEncRB = 8;         // rows (k1) per workgroup in the row pass
 
 // e^(-2 pi i e / M), 0 <= e < M, from the table of eta^k = e^(2 pi i k / M), k < M/2
 __device__ __forceinline__ cdd enc_twiddle(const double* tw, int e, int M) {
@@ -820,22 +820,24 @@ __device__ __forceinline__ void dft_small(cdd (&a)[R], cdd w8) {
   for (int k = 0; k < R; ++k) a[k] = t[k];
 }
 
-// Column pass: kEncCB columns n2 of complex vector p; writes Z[p][k1][n2] (rows of M2).
+// Column pass: CB columns n2 of complex vector p; writes Z[p][k1][n2] (rows of M2).
 // M1 = 8 R2: n1 = na + R2 nb, k1 = kb + 8 ka,
 //   X[kb + 8 ka] = sum_na e^(-2 pi i na ka / R2) e^(-2 pi i na kb / M1) DFT8_nb(x[na + R2 nb])[kb].
-// Step 1 (work-item (c, na), na < R2): the DFT8 over nb and its twiddle, into LDS S[kb][na][c];
-// step 2 (work-item (c, kb)): the DFT of size R2 over na, the four-step twiddle, the store.
+// Step 1 (work-item (c, na)): the DFT8 over nb and its twiddle, into LDS S[kb][na][c]; step 2
+// (work-item (c, kb), 8 / R2 values of kb each): the DFT of size R2 over na, the four-step twiddle, the
+// store.  CB = 128 / R2, so every work-item has a DFT8 of its own (with 16 columns at every size half
+// of them had none at N = 8192 and three quarters at N = 4096).
 template <class Src, int R2>
-__global__ __launch_bounds__(kEncCB * 8) void k_enc_cols(Src src, double* zbuf, const double* tw, int M) {
-  constexpr int M1 = 8 * R2;
-  __shared__ cdd S[8 * R2 * kEncCB];
-  const int n2_0 = blockIdx.x * kEncCB;
+__global__ __launch_bounds__(kEncThreads) void k_enc_cols(Src src, double* zbuf, const double* tw, int M) {
+  constexpr int M1 = 8 * R2, CB = kEncThreads / R2;
+  __shared__ cdd S[8 * R2 * CB];
+  const int n2_0 = blockIdx.x * CB;
   const int p = blockIdx.y;
   const int t = threadIdx.x;
-  const int c = t % kEncCB, q = t / kEncCB;  // q: na in step 1, kb in step 2
+  const int c = t % CB, q = t / CB;  // q: na in step 1, kb mod R2 in step 2
   const cdd w8 = enc_twiddle(tw, M / 8, M);
   const auto ctx = src.begin(p);
-  if (q < R2) {
+  {
     cdd a[8];
 #pragma unroll
     for (int nb = 0; nb < 8; ++nb) a[nb] = src(ctx, kEncM2 * (q + R2 * nb) + n2_0 + c);
@@ -843,39 +845,79 @@ __global__ __launch_bounds__(kEncCB * 8) void k_enc_cols(Src src, double* zbuf, 
 #pragma unroll
     for (int kb = 0; kb < 8; ++kb) {
       const cdd v = kb == 0 || q == 0 ? a[kb] : cdd_mul(a[kb], enc_twiddle(tw, q * kb * (M / M1), M));
-      S[(kb * R2 + q) * kEncCB + c] = v;
+      S[(kb * R2 + q) * CB + c] = v;
     }
   }
   __syncthreads();
-  cdd b[R2];
-#pragma unroll
-  for (int na = 0; na < R2; ++na) b[na] = S[(q * R2 + na) * kEncCB + c];
-  dft_small<R2>(b, w8);
   const int n2 = n2_0 + c;
 #pragma unroll
-  for (int ka = 0; ka < R2; ++ka) {
-    const int k1 = q + 8 * ka;
-    const cdd z = cdd_mul(b[ka], enc_twiddle(tw, n2 * k1, M));  // n2 k1 < M2 M1 = M
-    st_cdd(zbuf + ((size_t)p * M + (size_t)k1 * kEncM2 + n2) * 4, z);
+  for (int i = 0; i < 8 / R2; ++i) {
+    const int kb = q + R2 * i;
+    cdd b[R2];
+#pragma unroll
+    for (int na = 0; na < R2; ++na) b[na] = S[(kb * R2 + na) * CB + c];
+    dft_small<R2>(b, w8);
+#pragma unroll
+    for (int ka = 0; ka < R2; ++ka) {
+      const int k1 = kb + 8 * ka;
+      const cdd z = cdd_mul(b[ka], enc_twiddle(tw, n2 * k1, M));  // n2 k1 < M2 M1 = M
+      st_cdd(zbuf + ((size_t)p * M + (size_t)k1 * kEncM2 + n2) * 4, z);
+    }
   }
 }
 
-// Row pass: kEncRB rows k1 of vector p; writes Y[p][k1 + M1 k2].  M2 = 128: n2 = na + 16 nb,
+__device__ __forceinline__ long long rhaz_dd(dd x, int* overflow) {
+  const bool neg = x.hi < 0.0;
+  if (neg) x = dd_neg(x);
+  if (!(x.hi < 4.0e18)) { *overflow = 1; return 0; }
+  const double f = floor(x.hi);
+  const double frac = (x.hi - f) + x.lo;
+  long long r = (long long)f + (long long)floor(frac + 0.5);
+  return neg ? -r : r;
+}
+
+// rounding of one transformed value y_k: w = zeta^-k y_k (Delta / M), coefficients k and k + M of the
+// plaintext are RHAZ(Re w) and RHAZ(Im w) (|.| < 4e18, else *overflow is set)
+__device__ __forceinline__ void enc_round(cdd y, cdd twist, double scale_over_m, long long* out_k, int M, int* overflow) {
+  const cdd w = cdd_mul(y, twist);
+  int of = 0;
+  const long long pr = rhaz_dd(dd_mul_d(w.re, scale_over_m), &of);
+  const long long pi = rhaz_dd(dd_mul_d(w.im, scale_over_m), &of);
+  if (of) atomicOr(overflow, 1);
+  out_k[0] = pr;
+  out_k[M] = pi;
+}
+
+// Row pass and rounding: kEncRB rows k1 of vector p.  M2 = 128: n2 = na + 16 nb,
 // k2 = kb + 8 ka (na, ka < 16; nb, kb < 8),
 //   X[kb + 8 ka] = DFT16_na(s_kb)[ka],  s_kb[na] = e^(-2 pi i na kb / 128) DFT8_nb(x[na + 16 nb])[kb].
 // Step 1 (work-item (na, r)): the DFT8 over nb and its twiddle, into LDS; step 2 (work-item
 // (r, kb, h)): the first decimation-in-frequency stage of the DFT16 (h = 0: s[n] + s[n + 8] for the
 // even ka; h = 1: (s[n] - s[n + 8]) e^(-2 pi i n / 16) for the odd ka), then a DFT8.
+// The transformed values y_k, k = k1 + M1 k2, are rounded to the plaintext's integer coefficients
+// out[p][N] here (a pass of its own read them back, and wrote every limb's residues, which the
+// plaintext's transforms now take from the integers).
+// PAIRED: vector pp holds FFT(x_{2pp} + i x_{2pp+1}) of two real inputs, whose transforms are
+// X1_k = (Y_k + conj Y_{M-k}) / 2 and X2_k = (Y_k - conj Y_{M-k}) / (2i).  M - k lies in row M1 - k1, so a
+// workgroup takes four rows and their mirrors (rows 0 and M1/2 are their own) and exchanges the
+// values through LDS.
 constexpr int kEncRowPad = kEncRB + 1;  // LDS row stride (in cdd) of S[kb][na][r]
-__global__ __launch_bounds__(kEncRB * 16) void k_enc_rows(const double* zbuf, double* ybuf, const double* tw, int M, int M1) {
+template <bool PAIRED>
+__global__ __launch_bounds__(kEncRB * 16) void k_enc_rows(const double* zbuf, const double* tw, const double* twist, double scale_over_m,
+                                                          long long* out, int count, int* overflow, int M, int M1) {
   __shared__ cdd S[8 * 16 * kEncRowPad];
-  const int k1_0 = blockIdx.x * kEncRB;
   const int p = blockIdx.y;
   const int t = threadIdx.x;
   const cdd w8 = enc_twiddle(tw, M / 8, M);
+  auto row_of = [&](int r) {
+    if (!PAIRED) return (int)blockIdx.x * kEncRB + r;
+    const int a = (int)blockIdx.x * (kEncRB / 2) + (r & (kEncRB / 2 - 1));
+    if (r < kEncRB / 2) return a;
+    return a == 0 ? M1 / 2 : M1 - a;
+  };
   {
     const int na = t % 16, r = t / 16;
-    const double* row = zbuf + ((size_t)p * M + (size_t)(k1_0 + r) * kEncM2) * 4;
+    const double* row = zbuf + ((size_t)p * M + (size_t)row_of(r) * kEncM2) * 4;
     cdd a[8];
 #pragma unroll
     for (int nb = 0; nb < 8; ++nb) a[nb] = ld_cdd(row + (size_t)(na + 16 * nb) * 4);
@@ -896,116 +938,87 @@ __global__ __launch_bounds__(kEncRB * 16) void k_enc_rows(const double* zbuf, do
     b[n] = h == 0 ? cdd_add(s0, s8) : (n == 0 ? cdd_sub(s0, s8) : cdd_mul(cdd_sub(s0, s8), enc_twiddle(tw, n * (M / 16), M)));
   }
   dft_small<8>(b, w8);
-  const int k1 = k1_0 + r;
+  const int k1 = row_of(r);
+  if constexpr (!PAIRED) {
 #pragma unroll
-  for (int kp = 0; kp < 8; ++kp) {
-    const int k2 = kb + 8 * (2 * kp + h);
-    st_cdd(ybuf + ((size_t)p * M + k1 + (size_t)M1 * k2) * 4, b[kp]);
+    for (int kp = 0; kp < 8; ++kp) {
+      const int k = k1 + M1 * (kb + 8 * (2 * kp + h));
+      enc_round(b[kp], ld_cdd(twist + (size_t)k * 4), scale_over_m, out + (size_t)p * 2 * M + k, M, overflow);
+    }
+  } else {
+    __syncthreads();  // every work-item is past its reads of S
+#pragma unroll
+    for (int kp = 0; kp < 8; ++kp) S[(kb + 8 * (2 * kp + h)) * kEncRowPad + r] = b[kp];
+    __syncthreads();
+    // the mirror of (k1, k2): row M1 - k1, M2 - 1 - k2; of row 0: M2 - k2 (mod M2)
+    const int rm = k1 == 0 || k1 == M1 / 2 ? r : r ^ (kEncRB / 2);
+#pragma unroll
+    for (int kp = 0; kp < 8; ++kp) {
+      const int k2 = kb + 8 * (2 * kp + h), k = k1 + M1 * k2;
+      const int k2m = k1 == 0 ? (kEncM2 - k2) % kEncM2 : kEncM2 - 1 - k2;
+      const cdd y = b[kp], yc = S[k2m * kEncRowPad + rm];
+      const dd half_re1 = dd_add(y.re, yc.re), half_im1 = dd_add(y.im, dd_neg(yc.im));  // Y + conj(Yc)
+      const dd half_re2 = dd_add(y.im, yc.im), half_im2 = dd_add(yc.re, dd_neg(y.re));  // (Y - conj(Yc)) / i
+      const cdd x1 = cdd{dd_mul_d(half_re1, 0.5), dd_mul_d(half_im1, 0.5)};
+      const cdd x2 = cdd{dd_mul_d(half_re2, 0.5), dd_mul_d(half_im2, 0.5)};
+      const cdd tws = ld_cdd(twist + (size_t)k * 4);
+      enc_round(x1, tws, scale_over_m, out + (size_t)(2 * p) * 2 * M + k, M, overflow);
+      if (2 * p + 1 < count) enc_round(x2, tws, scale_over_m, out + (size_t)(2 * p + 1) * 2 * M + k, M, overflow);
+    }
   }
 }
 
-__device__ __forceinline__ long long rhaz_dd(dd x, int* overflow) {
-  const bool neg = x.hi < 0.0;
-  if (neg) x = dd_neg(x);
-  if (!(x.hi < 4.0e18)) { *overflow = 1; return 0; }
-  const double f = floor(x.hi);
-  const double frac = (x.hi - f) + x.lo;
-  long long r = (long long)f + (long long)floor(frac + 0.5);
-  return neg ? -r : r;
-}
-
-// finalize: w_k = zeta^-k * y_k * (Delta / M); p_k = RHAZ(Re w_k), p_{k+M} = RHAZ(Im w_k);
-// residues into limbs 0..level of out[p][limb][N]
-// r mod q for |r| < 2^62 without a 64-bit division: quotient from FP64 (off by at most one),
-// exact remainder in integers, one correction
-__device__ __forceinline__ uint64_t mod_i64(long long r, long long q, double qinv) {
-  const long long t = (long long)rint((double)r * qinv);
-  long long m = r - t * q;
-  if (m < 0) m += q;
-  if (m >= q) m -= q;
-  return (uint64_t)m;
-}
-
-// rounding and residues of one transformed value y_k: w = zeta^-k y_k (Delta / M),
-// p_k = RHAZ(Re w), p_{k+M} = RHAZ(Im w) into limbs 0..nl-1 of out_p[limb][N]
-__device__ __forceinline__ void enc_round_store(cdd y, const double* twist, double scale_over_m, int M, int k, int nl, const ModTable& mt,
-                                                const uint64_t* mods, uint64_t* out_p, int* overflow) {
-  const cdd w = cdd_mul(y, ld_cdd(twist + (size_t)k * 4));
-  int of = 0;
-  const long long pr = rhaz_dd(dd_mul_d(w.re, scale_over_m), &of);
-  const long long pi = rhaz_dd(dd_mul_d(w.im, scale_over_m), &of);
-  if (of) atomicOr(overflow, 1);
-  const int n = 2 * M;
-  for (int i = 0; i < nl; ++i) {
-    const long long q = (long long)mods[i];
-    const double qinv = mt.m[i].qinv;
-    out_p[(size_t)i * n + k] = mod_i64(pr, q, qinv);
-    out_p[(size_t)i * n + k + M] = mod_i64(pi, q, qinv);
-  }
-}
-
-// finalize: w_k = zeta^-k * y_k * (Delta / M); p_k = RHAZ(Re w_k), p_{k+M} = RHAZ(Im w_k);
-// residues into limbs 0..level of out[p][limb][N]
-__global__ void k_enc_final(const double* ybuf, const double* twist /* [M][4] zeta^-k */, double scale_over_m, int M, int nl,
-                            ModTable mt, const uint64_t* mods, uint64_t* out, int* overflow) {
+// integer coefficients -> coefficient-form residues out[p][limb][N] (blb_encode's result; plaintexts
+// that go to evaluation form are reduced by their transforms)
+__global__ void k_coef_residues(const long long* __restrict__ coef, uint64_t* __restrict__ out, int n, int nl, ModTable mt) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   const int p = blockIdx.y;
-  if (k >= M) return;
-  const cdd y = ld_cdd(ybuf + ((size_t)p * M + k) * 4);
-  enc_round_store(y, twist, scale_over_m, M, k, nl, mt, mods, out + (size_t)p * nl * 2 * M, overflow);
+  if (k >= n) return;
+  const uint64_t u = (uint64_t)coef[(size_t)p * n + k];
+  for (int i = 0; i < nl; ++i) {
+    const ModEntry me = mt.m[i];
+    out[((size_t)p * nl + i) * n + k] = d2u(canon_full(i64_mod(u, me.q, me.qinv), me.q, me.qinv));
+  }
+}
+void launch_coef_residues(blb_ctx* c, const uint64_t* coef, uint64_t* out, int count, int nl) {
+  dim3 grid((c->n + 255) / 256, count);
+  emit(c, [=, stream = c->stream] { k_coef_residues<<<grid, 256, 0, stream>>>((const long long*)coef, out, c->n, nl, c->mt); });
 }
 
-// paired finalize: buffer pp holds FFT(x_{2pp} + i x_{2pp+1}) of two real inputs; their
-// transforms are X1_k = (Y_k + conj Y_{M-k}) / 2 and X2_k = (Y_k - conj Y_{M-k}) / (2i)
-__global__ void k_enc_final_pair(const double* ybuf, const double* twist, double scale_over_m, int M, int nl, ModTable mt,
-                                 const uint64_t* mods, uint64_t* out, int count, int* overflow) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const int pp = blockIdx.y;
-  if (k >= M) return;
-  const cdd y = ld_cdd(ybuf + ((size_t)pp * M + k) * 4);
-  const cdd yc = ld_cdd(ybuf + ((size_t)pp * M + (k == 0 ? 0 : M - k)) * 4);
-  const dd half_re1 = dd_add(y.re, yc.re), half_im1 = dd_add(y.im, dd_neg(yc.im));  // Y + conj(Yc)
-  const dd half_re2 = dd_add(y.im, yc.im), half_im2 = dd_add(yc.re, dd_neg(y.re));  // (Y - conj(Yc)) / i
-  const cdd x1 = cdd{dd_mul_d(half_re1, 0.5), dd_mul_d(half_im1, 0.5)};
-  const cdd x2 = cdd{dd_mul_d(half_re2, 0.5), dd_mul_d(half_im2, 0.5)};
-  const size_t stride = (size_t)nl * 2 * M;
-  enc_round_store(x1, twist, scale_over_m, M, k, nl, mt, mods, out + (size_t)(2 * pp) * stride, overflow);
-  if (2 * pp + 1 < count) enc_round_store(x2, twist, scale_over_m, M, k, nl, mt, mods, out + (size_t)(2 * pp + 1) * stride, overflow);
-}
-
-// Encodes `count` plaintexts into coefficient-form residues out[count][nl][N] (the DFT of the
-// slot values from src, then twist, scale, rounding and residues).  bufA, bufB: [count][M][4].
+// Encodes `count` plaintexts into integer coefficients coef[count][N] (int64; the DFT of the slot
+// values from src, then twist, scale and rounding).  zbuf: [complex vectors][M][4].
 template <class Src>
-int encode_with(blb_ctx* c, const Src& src, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out, int* d_overflow,
-                bool paired) {
+int encode_with(blb_ctx* c, const Src& src, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow, bool paired) {
   const int M = c->n / 2, M1 = M / kEncM2;
   if (M1 != 16 && M1 != 32 && M1 != 64) return BLB_EINVAL;  // M1 = 8 R2, R2 = 2, 4, 8; M1 >= kEncRB
   const int n_vec = paired ? (count + 1) / 2 : count;  // complex vectors transformed
-  const dim3 gc(kEncM2 / kEncCB, n_vec);
-  if (M1 == 64) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 8><<<gc, kEncCB * 8, 0, stream>>>(src, bufB, c->d_enc_tw, M); });
-  else if (M1 == 32) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 4><<<gc, kEncCB * 8, 0, stream>>>(src, bufB, c->d_enc_tw, M); });
-  else emit(c, [=, stream = c->stream] { k_enc_cols<Src, 2><<<gc, kEncCB * 8, 0, stream>>>(src, bufB, c->d_enc_tw, M); });
-  emit(c, [=, stream = c->stream] { k_enc_rows<<<dim3(M1 / kEncRB, n_vec), kEncRB * 16, 0, stream>>>(bufB, bufA, c->d_enc_tw, M, M1); });
-  dim3 grid((M + 255) / 256, n_vec);
+  const dim3 gc(kEncM2 * (M1 / 8) / kEncThreads, n_vec), gr(M1 / kEncRB, n_vec);
+  if (M1 == 64) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 8><<<gc, kEncThreads, 0, stream>>>(src, zbuf, c->d_enc_tw, M); });
+  else if (M1 == 32) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 4><<<gc, kEncThreads, 0, stream>>>(src, zbuf, c->d_enc_tw, M); });
+  else emit(c, [=, stream = c->stream] { k_enc_cols<Src, 2><<<gc, kEncThreads, 0, stream>>>(src, zbuf, c->d_enc_tw, M); });
+  const double sm = scale / (double)M;
+  long long* out = (long long*)coef;
   if (paired)
-    emit(c, [=, stream = c->stream] { k_enc_final_pair<<<grid, 256, 0, stream>>>(bufA, c->d_enc_twist, scale / (double)M, M, nl, c->mt, c->d_mods, out, count, d_overflow); });
+    emit(c, [=, stream = c->stream] {
+      k_enc_rows<true><<<gr, kEncRB * 16, 0, stream>>>(zbuf, c->d_enc_tw, c->d_enc_twist, sm, out, count, d_overflow, M, M1);
+    });
   else
-    emit(c, [=, stream = c->stream] { k_enc_final<<<grid, 256, 0, stream>>>(bufA, c->d_enc_twist, scale / (double)M, M, nl, c->mt, c->d_mods, out, d_overflow); });
+    emit(c, [=, stream = c->stream] {
+      k_enc_rows<false><<<gr, kEncRB * 16, 0, stream>>>(zbuf, c->d_enc_tw, c->d_enc_twist, sm, out, count, d_overflow, M, M1);
+    });
   return BLB_OK;
 }
-int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
-                     int* d_overflow) {
-  return encode_with(c, EncSrcDense{vals, n_vals, c->d_slot_inv}, count, bufA, bufB, scale, nl, out, d_overflow, false);
+int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow) {
+  return encode_with(c, EncSrcDense{vals, n_vals, c->d_slot_inv}, count, zbuf, scale, coef, d_overflow, false);
 }
-int run_encode_block(blb_ctx* c, int block, double* bufA, double* bufB, double scale, int nl, uint64_t* out, int* d_overflow) {
-  return encode_with(c, EncSrcBlock{block, c->d_slot_inv}, 1, bufA, bufB, scale, nl, out, d_overflow, false);
+int run_encode_block(blb_ctx* c, int block, double* zbuf, double scale, uint64_t* coef, int* d_overflow) {
+  return encode_with(c, EncSrcBlock{block, c->d_slot_inv}, 1, zbuf, scale, coef, d_overflow, false);
 }
-int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* bufA, double* bufB, double scale, int nl, uint64_t* out,
-                  int* d_overflow, CpDiag dg) {
+int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow,
+                  CpDiag dg) {
   int lLp = 0;
   while ((1 << lLp) < g.Lp) ++lLp;
-  return encode_with(c, EncSrcCp{W, g, p0, count, c->n / 2, lLp, c->d_slot_inv, dg}, count, bufA, bufB, scale, nl, out, d_overflow,
-                     !g.cplx);
+  return encode_with(c, EncSrcCp{W, g, p0, count, c->n / 2, lLp, c->d_slot_inv, dg}, count, zbuf, scale, coef, d_overflow, !g.cplx);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -24,7 +24,9 @@ constexpr int kPT16 = 16, kPT32 = 32;
 
 // Where a launch finds its polynomials: a descriptor table, or (descs == null) a regular
 // batch of `count` limb-polys stored back to back at `base`, transformed in place, poly p
-// taken modulo prime p mod nl (the [item][limb][N] layout of ciphertexts and plaintexts).
+// taken modulo prime p mod nl (the [item][limb][N] layout of ciphertexts and plaintexts), or
+// (coef set) a plan batch: poly p reads the integer coefficients of plaintext p / nl and goes to
+// base + p x out_bytes.
 struct NttSrc {
   const PolyDesc* descs;
   uint64_t* base;
@@ -32,6 +34,8 @@ struct NttSrc {
   int log_n;
   int group = 1;  // runs of this many descriptors read the same words
   int count = 0;
+  const uint64_t* coef = nullptr;
+  size_t out_bytes = 0;
   // Workgroup w of the launch takes descriptor at(w): workgroups go round-robin over the 8 XCDs, so the
   // `group` descriptors of a run are given to workgroups 8 apart and meet in one XCD's L2.
   __device__ __forceinline__ int at(int w) const {
@@ -58,8 +62,8 @@ struct NttSrc {
       return r.d;
     }
     PolyDesc d;
-    d.src = base + ((size_t)p << log_n);
-    d.dst = base + ((size_t)p << log_n);
+    d.src = coef ? coef + ((size_t)(p / nl) << log_n) : base + ((size_t)p << log_n);
+    d.dst = coef ? (uint64_t*)((uint8_t*)base + (size_t)p * out_bytes) : base + ((size_t)p << log_n);
     d.src2 = nullptr;
     d.src3 = nullptr;
     d.aux = 0.0;
@@ -370,7 +374,7 @@ __device__ __forceinline__ void ntt_store(double (&x)[PT], const PolyDesc& d, co
       j[i] = LastPass<LOGN, PT, FWD>::idx(tid, i);
       v[i] = canon2(FWD ? x[i] : mulmod_s(x[i], ninv, q, qi), q, qi);
     }
-    st.template put_all<LOGN, PT>(d, j, v, lds, tid);
+    st.template put_all<LOGN, PT, LastPass<LOGN, PT, FWD>::GS>(d, j, v, lds, tid);
     return;
   }
   st.template prepare<PT>(d, lds, tid);  // the epilogue may stage an operand in LDS (free after the last pass)
@@ -530,6 +534,13 @@ struct StPlain {
   __device__ Operand fetch(const PolyDesc&, int) const { return {}; }
   __device__ void put(const PolyDesc& d, int j, double v, Operand, double, double, const double*) const { gst(d.dst, j, d2u(v)); }
 };
+// load an integer coefficient (int64) and reduce it into this modulus: plan transforms
+struct LdCoef {
+  static constexpr bool kPersistent = true;
+  __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
+  __device__ double cvt(const PolyDesc&, uint64_t u, double q, double qi) const { return i64_mod(u, q, qi); }
+  __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
+};
 // load a residue of another modulus (aux = that modulus as double) and lift it centred into
 // this modulus: used by rescale (last limb -> limb i)
 struct LdCentredLift {
@@ -618,34 +629,52 @@ struct StModDown {
   }
 };
 
-// Plan epilogue: canonical results of a regular batch written in the 50-bit plan format (low
-// 32 bits, next 16, top 2 in u32 words of 16; see pt50_bytes) at out + (poly index) x
-// pt50_bytes(N), the poly index recovered from the batch's source address.  The top-bit codes
-// are gathered in LDS (free after the last pass), then each u32 of 16 codes written once.
+// Plan epilogue: canonical results in the 50-bit plan format (low 32 bits, next 16, top 2 in u32
+// words of 16; see pt50_bytes) at dst.  A work-item holds runs of GS consecutive words (the last
+// pass's groups), so its top-bit codes fill whole words (GS = 16), whole bytes (GS = 4) or half a byte
+// (GS = 2: the neighbour lane's half joins it); passes of other sizes gather the codes in LDS (free
+// after the last pass).
 struct StPack50 {
   static constexpr bool kLazy = false;
-  static constexpr bool kPersistent = false;
+  static constexpr bool kPersistent = true;
   static constexpr bool kPack = true;
   struct Operand {};
-  const uint64_t* base;  // source of the regular batch (poly p at base + p N)
-  uint8_t* out;          // packed destination of poly 0
-  template <int LOGN, int PT>
+  template <int LOGN, int PT, int GS>
   __device__ void put_all(const PolyDesc& d, const int (&j)[PT], const double (&v)[PT], double* lds, int tid) const {
     constexpr int N = 1 << LOGN, T = N / PT;
-    const size_t p = (size_t)(d.src - base) >> LOGN;
-    uint8_t* o = out + p * pt50_bytes(N);
-    uint32_t* lo = (uint32_t*)o;
-    uint16_t* mid = (uint16_t*)(o + (size_t)4 * N);
-    uint32_t* top = (uint32_t*)(o + (size_t)6 * N);
-    uint8_t* codes = (uint8_t*)lds;
-    lds_barrier();  // every work-item is past its reads of the last exchange
+    typedef __attribute__((address_space(1))) uint32_t g32;
+    typedef __attribute__((address_space(1))) uint16_t g16;
+    typedef __attribute__((address_space(1))) uint8_t g8;
+    g32* lo = (g32*)(uint8_t*)d.dst;
+    g16* mid = (g16*)((uint8_t*)d.dst + (size_t)4 * N);
+    uint8_t* top = (uint8_t*)d.dst + (size_t)6 * N;
+    uint32_t code[PT];
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
       const uint64_t w = d2u(v[i]);
       lo[j[i]] = (uint32_t)w;
       mid[j[i]] = (uint16_t)(w >> 32);
-      codes[j[i]] = (uint8_t)((w >> 48) & 3u);
+      code[i] = (uint32_t)(w >> 48);
     }
+    if constexpr (GS == 16 || GS == 4 || GS == 2) {
+#pragma unroll
+      for (int h = 0; h < PT / GS; ++h) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int k = 0; k < GS; ++k) bits |= code[h * GS + k] << (2 * k);
+        if constexpr (GS == 16) ((g32*)top)[j[h * GS] >> 4] = bits;
+        else if constexpr (GS == 4) ((g8*)top)[j[h * GS] >> 2] = (uint8_t)bits;
+        else {  // lanes t, t + 1 hold words 4m, 4m + 1 and 4m + 2, 4m + 3
+          const uint32_t other = __shfl_xor(bits, 1);
+          if ((tid & 1) == 0) ((g8*)top)[j[h * GS] >> 2] = (uint8_t)(bits | (other << 4));
+        }
+      }
+      return;
+    }
+    uint8_t* codes = (uint8_t*)lds;
+    lds_barrier();  // every work-item is past its reads of the last exchange
+#pragma unroll
+    for (int i = 0; i < PT; ++i) codes[j[i]] = (uint8_t)code[i];
     lds_barrier();
     for (int t = tid; t < N / 16; t += T) {
       const uint32_t* c4 = (const uint32_t*)(codes + 16 * t);
@@ -656,7 +685,7 @@ struct StPack50 {
         const uint32_t c = (x & 3u) | ((x >> 6) & 0xCu) | ((x >> 12) & 0x30u) | ((x >> 18) & 0xC0u);
         word |= c << (8 * b);
       }
-      top[t] = word;
+      ((g32*)top)[t] = word;
     }
   }
   template <int PT>
@@ -712,7 +741,10 @@ void launch_ntt_regular(blb_ctx* c, uint64_t* base, int count, int nl, bool fwd)
   if (fwd) launch_ntt_generic<true>(c, src, count, LdPlain{}, StPlain{});
   else launch_ntt_generic<false>(c, src, count, LdPlain{}, StPlain{});
 }
-void launch_ntt_pack50(blb_ctx* c, const uint64_t* base, uint8_t* out, int count, int nl) {
-  const NttSrc src{nullptr, (uint64_t*)base, nl, c->log_n};
-  launch_ntt_generic<true>(c, src, count, LdPlain{}, StPack50{base, out});
+void launch_ntt_plan(blb_ctx* c, const uint64_t* coef, uint8_t* out, int count, int nl, int p50) {
+  NttSrc src{nullptr, (uint64_t*)out, nl, c->log_n, nl, count * nl};  // a plaintext's limbs read the same words
+  src.coef = coef;
+  src.out_bytes = pt_poly_bytes(c->n, p50);
+  if (p50) launch_ntt_generic<true>(c, src, count * nl, LdCoef{}, StPack50{});
+  else launch_ntt_generic<true>(c, src, count * nl, LdCoef{}, StPlain{});
 }
