@@ -3162,7 +3162,7 @@ static int batch_matmul_cp_call(blb_ctx* c, const blb_cp_instance* inst, int n_i
   }
   int rc = ks_batch(c, level, srcs, reqs);
   if (rc) return rc;
-  // MACs: one persistent launch over all plan groups
+  // MACs: by size (batch variant 0), or one persistent launch of a fixed shape over all plan groups
   {
     std::vector<const blb_plan*> plans;
     std::vector<std::vector<int>> members;
@@ -3177,10 +3177,15 @@ static int batch_matmul_cp_call(blb_ctx* c, const blb_cp_instance* inst, int n_i
       }
       members[gi].push_back(i);
     }
+    const bool by_size = c->batch_variant == 0;
+    const int variant = by_size ? 1 : c->batch_variant;  // by size: the shape the small single instances share
     int tb, ib, cpt;
-    batch_mac_shape(c->batch_variant, &tb, &ib, &cpt);
+    batch_mac_shape(variant, &tb, &ib, &cpt);
     std::vector<MacGroup> groups;
     std::vector<MacItem> items;
+    std::vector<MacSeg> segs[5];  // by instances per run
+    int blocks[5] = {};
+    std::vector<std::pair<int, int>> alone;  // (group, instance)
     for (size_t gi = 0; gi < plans.size(); ++gi) {
       const CpGeom& g = plans[gi]->g;
       const int n_ai = g.n_in * g.B, n_bj = g.n_out * g.G;
@@ -3201,21 +3206,52 @@ static int batch_matmul_cp_call(blb_ctx* c, const blb_cp_instance* inst, int n_i
       mg.n_inst = (int)members[gi].size();
       groups.push_back(mg);
       c->counters[2] += (int64_t)n_ai * n_bj * mg.n_inst;
-      c->counters[7] += (int64_t)n_ai * n_bj * nl * (int64_t)pt_poly_bytes(n, plans[gi]->p50) * ((mg.n_inst + ib - 1) / ib);
+      const int64_t plan_bytes = (int64_t)n_ai * n_bj * nl * (int64_t)pt_poly_bytes(n, plans[gi]->p50);
+      int i0 = 0;
+      if (by_size) {
+        // runs of 2..4 instances of near equal size; a single instance whose product fills the GPU runs
+        // the ordinary MAC, smaller ones share a launch
+        const int runs = (mg.n_inst + 3) / 4;
+        if (mg.n_inst > 1 || mac_waves(n, nl, n_bj) >= 1024)
+          for (int r = 0; r < runs; ++r) {
+            const int k = mg.n_inst / runs + (r < mg.n_inst % runs ? 1 : 0);
+            if (k == 1) {
+              alone.push_back({(int)gi, i0});
+            } else {
+              const int tiles = (n_bj + mac_multi_rows(k) - 1) / mac_multi_rows(k);
+              segs[k].push_back(MacSeg{blocks[k], (int)gi, i0});
+              blocks[k] += n / 256 * nl * tiles;
+            }
+            c->counters[7] += plan_bytes;
+            i0 += k;
+          }
+      }
+      c->counters[7] += plan_bytes * ((mg.n_inst - i0 + ib - 1) / ib);
       const int n_kb = n / (256 * cpt);
       const int lg = c->batch_limbs > 0 ? std::min(c->batch_limbs, nl) : nl;  // limbs per work item
-      for (int i0 = 0; i0 < mg.n_inst; i0 += ib)
+      for (; i0 < mg.n_inst; i0 += ib)
         for (int limb = 0; limb < nl; limb += lg)
           for (int kb = 0; kb < n_kb; ++kb)
             for (int t = 0; t * tb < n_bj; ++t) items.push_back(MacItem{(int)gi, i0, t, kb, limb, std::min(lg, nl - limb)});
     }
     const MacGroup* g_dev = upload_vec(c, groups);
-    const MacItem* it_dev = upload_vec(c, items);
-    if (!g_dev || !it_dev) return BLB_EDEVICE;
+    const MacItem* it_dev = items.empty() ? nullptr : upload_vec(c, items);
+    if (!g_dev || (!items.empty() && !it_dev)) return BLB_EDEVICE;
+    const MacSeg* seg_dev[5] = {};
+    for (int k = 2; k <= 4; ++k)
+      if (!segs[k].empty() && !(seg_dev[k] = upload_vec(c, segs[k]))) return BLB_EDEVICE;
     double units = 0;
     for (int i = 0; i < n_inst; ++i) units += (double)inst[i].plan->g.n_out * inst[i].plan->g.G * nl * n;
     Span sp(c, BLB_T_CP_MAC, units);
-    launch_cp_mac_batch(c, g_dev, it_dev, (int)items.size(), c->batch_variant, c->batch_grid, inst[0].plan->p50);
+    for (int k = 4; k >= 2; --k)
+      if (!segs[k].empty() && !launch_cp_mac_multi(c, g_dev, seg_dev[k], (int)segs[k].size(), blocks[k], k, inst[0].plan->p50))
+        return BLB_EINVAL;
+    for (const auto& a : alone) {
+      const MacGroup& mg = groups[a.first];
+      launch_cp_mac(c, mg.pt, mg.rx + (size_t)a.second * mg.n_ai, inner[members[a.first][a.second]], nl, mg.n_ai, mg.n_bj, c->mac_variant,
+                    inst[0].plan->p50);
+    }
+    launch_cp_mac_batch(c, g_dev, it_dev, (int)items.size(), variant, c->batch_grid, inst[0].plan->p50);
   }
   // giant steps of every instance in one key-switch batch
   srcs.clear();

@@ -142,6 +142,9 @@ struct MacGroup {
   uint64_t* const* inner;       // [instance] -> [n_bj][2][nl][N]
   int n_ai, n_bj, nl, n_inst;
 };
+struct MacSeg {  // workgroups first .. next segment's first - 1: instances inst0 .. of one group
+  int first, group, inst0;
+};
 struct MacItem {
   int group, inst0, tile, kb, limb, n_limb;  // limbs limb .. limb + n_limb - 1 (limb grouping)
 };
@@ -392,6 +395,11 @@ void launch_cp_mac(blb_ctx* c, const uint64_t* pt, const uint64_t* const* rx_tab
 void launch_sum_cts(blb_ctx* c, const uint64_t* const* srcs, uint64_t* const* dsts, int n_out, int n_terms, int nl);
 void launch_mask_pair(blb_ctx* c, const CcPair* pairs_dev, int n_pairs, int nl);
 int batch_mac_shape(int variant, int* tb, int* ib, int* cpt);
+// segments of exactly ib (2..4) instances each; returns false for another ib
+bool launch_cp_mac_multi(blb_ctx* c, const MacGroup* groups, const MacSeg* segs, int n_seg, int blocks, int ib, int p50);
+int mac_multi_rows(int ib);
+// waves of the ordinary MAC at 8 outputs x 2 coefficients per work-item
+int64_t mac_waves(int n, int nl, int n_bj);
 void launch_cp_mac_batch(blb_ctx* c, const MacGroup* groups, const MacItem* items, int n_items, int variant, int grid, int p50);
 // forward NTT of `count` plaintexts' integer coefficients coef[count][N] (int64) into every limb of
 // out[count][nl]: evaluation-form words, or the 50-bit plan format (p50)

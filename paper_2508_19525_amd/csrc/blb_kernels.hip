@@ -509,6 +509,7 @@ constexpr MacShape kMacShapes[BLB_MAC_VARIANTS] = {
 // {4,4,1,1} 370; 2304: {6,4,1,1} 561, {4,4,1,1} 643, {8,4,1,4} 753 and 1728: {4,4,1,4} 418, {4,4,1,1} 438, {6,4,1,1} 465
 // (both inside the operator); 960: {4,4,2,2} 119, {4,4,1,1} 154; 384: {4,2,4,4} 15.4, {4,4,2,2} 22; 128:
 // {2,2,4,4} 12.6, {4,2,4,4} 14.2.  12 rows only where they pad the outputs by little.
+int64_t mac_waves(int n, int nl, int n_bj) { return (int64_t)n * nl / 128 * ((n_bj + 7) / 8); }
 MacShape mac_shape_for(int n, int nl, int n_bj, int p50) {
   const int64_t cols = (int64_t)n * nl;
   if (p50) {
@@ -519,7 +520,7 @@ MacShape mac_shape_for(int n, int nl, int n_bj, int p50) {
     if (waves >= 640) return kMacShapes[8];
     return kMacShapes[waves >= 256 ? 4 : 5];
   }
-  const int64_t waves = cols / 128 * ((n_bj + 7) / 8);
+  const int64_t waves = mac_waves(n, nl, n_bj);
   const int pad12 = (n_bj + 11) / 12 * 12, pad8 = (n_bj + 7) / 8 * 8;
   if (waves >= 2048 && pad12 * 16 <= pad8 * 17) return kMacShapes[1];
   if (waves >= 1536) return kMacShapes[2];
@@ -1243,9 +1244,124 @@ __global__ __launch_bounds__(256) void k_cp_mac_batch(const MacGroup* __restrict
   }
 }
 
+// The MAC of IB instances that share a plan, each plaintext word loaded once for all of them:
+// TB outputs x IB instances x one coefficient per work-item.  Bound by FP64 issue from three
+// instances on (7.4 instructions per product: 5.9e9 products of 4 instances take 2.6 ms, 2.8 T/s),
+// by HBM with two (12 outputs: 5.2 TB/s of plan words).  A group's instances are split into runs of
+// 2..4 of near equal size, each size its own launch, so no work-item computes an instance that is
+// not there (the run-time tail of a fixed 4 x 2 shape did: 5 instances ran as 6, at 2.1 T/s).
+template <int TB, int IB, bool P50>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_cp_mac_multi(const MacGroup* __restrict__ groups,
+                                                                                              const MacSeg* __restrict__ segs, int n_seg,
+                                                                                              int n, int n_kblk, ModTable mt) {
+  typedef __attribute__((address_space(1))) const uint64_t gu64c;
+  typedef __attribute__((address_space(1))) uint64_t gu64;
+  typedef __attribute__((address_space(4))) const uint64_t ku64;
+  int s = 0;
+  while (s + 1 < n_seg && (int)blockIdx.x >= segs[s + 1].first) ++s;
+  const MacSeg seg = segs[s];
+  const MacGroup gr = groups[seg.group];
+  const int nl = gr.nl, n_ai = gr.n_ai, n_bj = gr.n_bj;
+  const int b = blockIdx.x - seg.first;
+  const int kb = b % n_kblk, limb = (b / n_kblk) % nl, bj0 = b / (n_kblk * nl) * TB;
+  const int k0 = kb * 256 + threadIdx.x;
+  const ModEntry me = mt.m[limb];
+  const double q = me.q, qi = me.qinv;
+  const Pt50Off off50 = pt50_off(n, k0);
+  const size_t pb = pt_poly_bytes(n, P50);
+  const size_t term = (size_t)nl * pb;  // bytes per (bj, ai) plaintext
+  const uint8_t* pt[TB];                // rows past the last re-read it (not stored)
+#pragma unroll
+  for (int t = 0; t < TB; ++t) pt[t] = (const uint8_t*)gr.pt + (size_t)min(bj0 + t, n_bj - 1) * n_ai * term + (size_t)limb * pb;
+  const ku64* rxtab[IB];
+#pragma unroll
+  for (int u = 0; u < IB; ++u) rxtab[u] = (const ku64*)(gr.rx + (size_t)(seg.inst0 + u) * n_ai);
+  Pt50Raw<1> w50[TB];
+  uint64_t w64[TB], r0[IB], r1[IB];
+  auto fetch = [&](int ai) {
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      const uint8_t* poly = pt[t] + (size_t)ai * term;
+      if constexpr (P50) pt50_fetch<1>(poly, off50, w50[t]);
+      else w64[t] = __builtin_nontemporal_load((gu64c*)poly + k0);
+    }
+#pragma unroll
+    for (int u = 0; u < IB; ++u) {
+      gu64c* x = (gu64c*)rxtab[u][ai];
+      r0[u] = x[(size_t)limb * n + k0];
+      r1[u] = x[(size_t)(nl + limb) * n + k0];
+    }
+  };
+  double a0[IB][TB], a1[IB][TB];
+#pragma unroll
+  for (int u = 0; u < IB; ++u)
+#pragma unroll
+    for (int t = 0; t < TB; ++t) a0[u][t] = a1[u][t] = 0.0;
+  fetch(0);
+  for (int ai = 0; ai < n_ai; ++ai) {
+    double w[TB], x0[IB], x1[IB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      if constexpr (P50) {
+        double v[1];
+        pt50_cvt<1>(w50[t], k0, v);
+        w[t] = v[0];
+      } else {
+        w[t] = u2d(w64[t]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < IB; ++u) {
+      x0[u] = u2d(r0[u]);
+      x1[u] = u2d(r1[u]);
+    }
+    fetch(min(ai + 1, n_ai - 1));  // the last term re-reads itself
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int u = 0; u < IB; ++u) {
+        a0[u][t] += mulmod_s(w[t], x0[u], q, qi);
+        a1[u][t] += mulmod_s(w[t], x1[u], q, qi);
+      }
+    if ((ai & 7) == 7) {  // 8 products below 0.875 q on |acc| <= q/2: |acc| < 7.5 q < 2^53
+#pragma unroll
+      for (int u = 0; u < IB; ++u)
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+          a0[u][t] = reduce_s(a0[u][t], q, qi);
+          a1[u][t] = reduce_s(a1[u][t], q, qi);
+        }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < IB; ++u) {
+    gu64* out = (gu64*)gr.inner[seg.inst0 + u];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      if (bj0 + t < n_bj) {
+        out[(((size_t)(bj0 + t) * 2 + 0) * nl + limb) * n + k0] = d2u(canon_full(a0[u][t], q, qi));
+        out[(((size_t)(bj0 + t) * 2 + 1) * nl + limb) * n + k0] = d2u(canon_full(a1[u][t], q, qi));
+      }
+    }
+  }
+}
+int mac_multi_rows(int ib) { return ib == 2 ? 12 : 8; }
+bool launch_cp_mac_multi(blb_ctx* c, const MacGroup* groups, const MacSeg* segs, int n_seg, int blocks, int ib, int p50) {
+#define MULTI(tb_, ib_)                                                                                                        \
+  if (ib == ib_) {                                                                                                             \
+    if (p50) emit(c, [=, stream = c->stream] { k_cp_mac_multi<tb_, ib_, true><<<blocks, 256, 0, stream>>>(groups, segs, n_seg, c->n, c->n / 256, c->mt); }); \
+    else emit(c, [=, stream = c->stream] { k_cp_mac_multi<tb_, ib_, false><<<blocks, 256, 0, stream>>>(groups, segs, n_seg, c->n, c->n / 256, c->mt); }); \
+    return true;                                                                                                               \
+  }
+  MULTI(12, 2)
+  MULTI(8, 3)
+  MULTI(8, 4)
+#undef MULTI
+  return false;
+}
+
 int batch_mac_shape(int variant, int* tb, int* ib, int* cpt) {
   switch (variant) {
-    case 1: *tb = 4; *ib = 1; *cpt = 2; break;
     case 2: *tb = 2; *ib = 4; *cpt = 2; break;
     case 3: *tb = 4; *ib = 4; *cpt = 1; break;
     case 4: *tb = 8; *ib = 2; *cpt = 1; break;
@@ -1253,7 +1369,7 @@ int batch_mac_shape(int variant, int* tb, int* ib, int* cpt) {
     case 6: *tb = 4; *ib = 8; *cpt = 1; break;
     case 7: *tb = 4; *ib = 4; *cpt = 2; break;
     case 8: *tb = 8; *ib = 2; *cpt = 2; break;
-    default: *tb = 4; *ib = 2; *cpt = 2; break;
+    default: *tb = 4; *ib = 1; *cpt = 2; break;
   }
   return 0;
 }
@@ -1268,15 +1384,14 @@ void launch_cp_mac_batch(blb_ctx* c, const MacGroup* groups, const MacItem* item
     if (p50) emit(c, [=, stream = c->stream] { k_cp_mac_batch<a, b, d, true><<<blocks, 256, 0, stream>>>(groups, items, n_items, c->n, c->mt); });  \
     else emit(c, [=, stream = c->stream] { k_cp_mac_batch<a, b, d, false><<<blocks, 256, 0, stream>>>(groups, items, n_items, c->n, c->mt); }); \
   } while (0)
-  if (tb == 4 && ib == 1) MB(4, 1, 2);
-  else if (tb == 2 && ib == 4) MB(2, 4, 2);
+  if (tb == 2 && ib == 4) MB(2, 4, 2);
   else if (tb == 4 && ib == 4 && cpt == 1) MB(4, 4, 1);
   else if (tb == 8 && ib == 2 && cpt == 1) MB(8, 2, 1);
   else if (tb == 8 && ib == 4) MB(8, 4, 1);
   else if (tb == 4 && ib == 8) MB(4, 8, 1);
   else if (tb == 4 && ib == 4) MB(4, 4, 2);
   else if (tb == 8 && ib == 2) MB(8, 2, 2);
-  else MB(4, 2, 2);
+  else MB(4, 1, 2);
 #undef MB
 }
 

@@ -255,3 +255,50 @@ def test_batched_c4_geometry_against_oracle(env, orc):
     for I in inst:
         B.blb_keys_destroy(I["keys"])
         B.blb_plan_destroy(I["plan"])
+
+
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("runs,L,d_out", [(1, 100, 40), (2, 100, 40), (3, 100, 200), (4, 16, 100), (5, 100, 40), (9, 40, 70), (1, 100, 1400)])
+def test_batched_runs_of_instances(env, runs, L, d_out, fmt):
+    """`runs` instances that share a plan (runs of 2, 3 and 4 instances and single ones, output counts
+    that are no multiple of a run's rows) beside one instance on a plan of its own: the words of
+    per-instance calls, any residues as inputs."""
+    B, wl, ctx = env
+    n, level, d_in = 8192, 2, 40
+    rng = np.random.default_rng(2000 + runs + d_out)
+    mods = [int(q) for q in B.blb_ctx_moduli(ctx, 4)][: level + 1]
+    B.blb_ctx_set_knob(ctx, B.BLB_KNOB_PLAN_FORMAT, fmt)
+    try:
+        plans = [B.blb_plan_matmul_cp(ctx, rng.normal(0, 0.02, (d_in, d)), L, level) for d in (d_out, 24)]
+    finally:
+        B.blb_ctx_set_knob(ctx, B.BLB_KNOB_PLAN_FORMAT, 0)
+    keep, inst, keys = [], [], []
+    for i in range(runs + 1):
+        plan = plans[0] if i < runs else plans[1]
+        g = B.blb_plan_info(plan)
+        keys.append(B.blb_keygen(ctx, 2100 + i, [k * g["Lp"] for k in range(1, g["B"])] + [j * g["B"] * g["Lp"] for j in range(1, g["G"])]))
+        cts = []
+        for count, lv in ((g["n_in"], level), (g["n_out"], level - 1), (g["n_out"], level - 1)):
+            cts.append([])
+            for _ in range(count):
+                ct, t = B.new_ct(n, lv)
+                keep.append(t)
+                cts[-1].append(ct)
+        for x in cts[0]:
+            w = np.stack([np.stack([rng.integers(0, q, n, dtype=np.uint64) for q in mods]) for _ in range(2)])
+            B.blb_import(ctx, w, x)
+            x.scale = 2.0 ** 40
+        inst.append(dict(keys=keys[-1], plan=plan, X=cts[0], Y=cts[1], Y2=cts[2]))
+    arr, hold = _abi_instances(B, inst)
+    B.blb_batch_matmul_cp(ctx, arr)
+    for I in inst:
+        B.blb_matmul_cp(ctx, I["keys"], I["plan"], I["X"], I["Y2"])
+    torch.cuda.synchronize()
+    for k, I in enumerate(inst):
+        for b in range(len(I["Y"])):
+            got = B.blb_export(ctx, B.blb_ct.from_address(arr[k].Y + b * B.C.sizeof(B.blb_ct)), n)
+            assert np.array_equal(got, B.blb_export(ctx, I["Y2"][b], n)), f"instance {k} output {b}"
+    for h in plans:
+        B.blb_plan_destroy(h)
+    for h in keys:
+        B.blb_keys_destroy(h)
