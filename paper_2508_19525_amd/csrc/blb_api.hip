@@ -2521,22 +2521,25 @@ int cc_steps23_bsgs_dev(blb_ctx* c, const blb_keys* K, const blb_plan* P, const 
   std::vector<char> used((size_t)g.n_out * (G > 1 ? G - 1 : 0) * 2, 0);
   for (int t0 = 0; t0 < lp; t0 += TC) {
     const int nt = std::min(TC, lp - t0);
-    std::vector<const uint64_t*> a_tab, r_tab;
-    for (int tt = 0; tt < nt; ++tt) {
-      const int t = t0 + tt, j = t / Bb, i = t % Bb;
-      for (int a = 0; a < m; ++a) {
-        a_tab.push_back(Ap + ((size_t)j * m + a) * w2);
-        r_tab.push_back(Y + ((size_t)i * m + a) * w2);
-      }
-    }
     {
-      const uint64_t* const* a_dev = upload_vec(c, a_tab);
-      const uint64_t* const* r_dev = upload_vec(c, r_tab);
-      if (!a_dev || !r_dev) return BLB_EDEVICE;
       Span sp(c, BLB_T_CC_TENSOR, (double)nt * nl2 * n);
       c->counters[3] += (int64_t)nt * m;
       c->counters[4] += nt;
-      launch_tensor_sum(c, a_dev, r_dev, T3, nt, m, nl2, nl2, true);
+      // t0 and nt are multiples of Bb: whole rows of giant steps
+      if (!launch_tensor_tile(c, Ap + (size_t)(t0 / Bb) * m * w2, Y, T3, m, nt / Bb, Bb, nl2)) {
+        std::vector<const uint64_t*> a_tab, r_tab;
+        for (int tt = 0; tt < nt; ++tt) {
+          const int t = t0 + tt, j = t / Bb, i = t % Bb;
+          for (int a = 0; a < m; ++a) {
+            a_tab.push_back(Ap + ((size_t)j * m + a) * w2);
+            r_tab.push_back(Y + ((size_t)i * m + a) * w2);
+          }
+        }
+        const uint64_t* const* a_dev = upload_vec(c, a_tab);
+        const uint64_t* const* r_dev = upload_vec(c, r_tab);
+        if (!a_dev || !r_dev) return BLB_EDEVICE;
+        launch_tensor_sum(c, a_dev, r_dev, T3, nt, m, nl2, nl2, true);
+      }
     }
     std::vector<const uint64_t*> rs;
     std::vector<KsReq> rr;

@@ -416,6 +416,7 @@ void launch_scale_cts(blb_ctx* c, const uint64_t* const* in, uint64_t* out, int 
 // a_per_t: A_tab holds one operand per (t, a) ([n_t][n_ct]) instead of one per a
 void launch_tensor_sum(blb_ctx* c, const uint64_t* const* A_tab, const uint64_t* const* R_tab, uint64_t* T3, int n_t, int n_ct, int nlA,
                        int nl2, bool a_per_t = false);
+bool launch_tensor_tile(blb_ctx* c, const uint64_t* A, const uint64_t* Y, uint64_t* T3, int m, int nj, int Bb, int nl);
 void launch_masked_acc(blb_ctx* c, const CcTerm* terms, const int* off, uint64_t* const* outs, int n_out, int nl, bool accumulate);
 void launch_mask_sample(blb_ctx* c, uint64_t* r_out, uint64_t* share, int n_ct, int tl, uint64_t seed, const uint64_t* seed_dev, uint32_t tag);
 void launch_set_u64(blb_ctx* c, uint64_t* dst, uint64_t value);

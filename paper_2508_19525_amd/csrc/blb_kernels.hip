@@ -1079,6 +1079,86 @@ void launch_tensor_sum(blb_ctx* c, const uint64_t* const* A_tab, const uint64_t*
   emit(c, [=, stream = c->stream] { k_tensor_sum<<<grid, 256, 0, stream>>>(A_tab, R_tab, T3, n_ct, nlA, nl2, c->n, c->mt, a_per_t ? 1 : 0); });
 }
 
+// The same sums for the BSGS schedule, where A'_{j,a} depends on the giant step only and Y_{a,i} on the
+// baby step only: t = j Bb + i is a matrix of outputs, and a work-item takes TJ x TI of them, loading
+// 2 (TJ + TI) words per a instead of 2 words of each operand per output.  One output at a time was
+// bound by the operands' L2 traffic (9 TB/s); 4 x 4 outputs are bound by FP64 issue.  12 heads, 128 tokens,
+// N = 16384, four limbs, 16 ciphertexts per operand: 348 us one at a time.
+// A: [nj][m][2][nl][N] from the chunk's first giant step, Y: [Bb][m][2][nl][N], T3: [nj Bb][3][nl][N].
+template <int TJ, int TI>
+__global__ __launch_bounds__(256) void k_tensor_tile(const uint64_t* __restrict__ A, const uint64_t* __restrict__ Y,
+                                                     uint64_t* __restrict__ T3, int m, int Bb, int nl, int n, ModTable mt) {
+  typedef __attribute__((address_space(1))) const uint64_t gu64;
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  const int limb = blockIdx.y % nl;
+  const int tile = blockIdx.y / nl, i0 = tile % (Bb / TI) * TI, j0 = tile / (Bb / TI) * TJ;
+  const ModEntry me = mt.m[limb];
+  const double q = me.q, qi = me.qinv;
+  const size_t poly = (size_t)nl * n, ct = 2 * poly;
+  gu64* ap = (gu64*)(A + (size_t)j0 * m * ct + (size_t)limb * n);
+  gu64* yp = (gu64*)(Y + (size_t)i0 * m * ct + (size_t)limb * n);
+  double d0[TJ][TI], d1[TJ][TI], d2[TJ][TI];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j)
+#pragma unroll
+    for (int i = 0; i < TI; ++i) d0[j][i] = d1[j][i] = d2[j][i] = 0.0;
+  for (int a = 0; a < m; ++a) {
+    double a0[TJ], a1[TJ], r0[TI], r1[TI];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      gu64* x = ap + ((size_t)j * m + a) * ct;
+      a0[j] = u2d(x[k]);
+      a1[j] = u2d(x[poly + k]);
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      gu64* x = yp + ((size_t)i * m + a) * ct;
+      r0[i] = u2d(x[k]);
+      r1[i] = u2d(x[poly + k]);
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        d0[j][i] += mulmod_s(a0[j], r0[i], q, qi);
+        d1[j][i] += mulmod_s(a0[j], r1[i], q, qi) + mulmod_s(a1[j], r0[i], q, qi);
+        d2[j][i] += mulmod_s(a1[j], r1[i], q, qi);
+      }
+    if ((a & 3) == 3) {  // |d1| <= q/2 + 8 x 0.875 q = 7.5 q < 2^53
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+          d0[j][i] = reduce_s(d0[j][i], q, qi);
+          d1[j][i] = reduce_s(d1[j][i], q, qi);
+          d2[j][i] = reduce_s(d2[j][i], q, qi);
+        }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < TJ; ++j)
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      uint64_t* o = T3 + ((size_t)(j0 + j) * Bb + i0 + i) * 3 * poly + (size_t)limb * n + k;
+      o[0] = d2u(canon_full(d0[j][i], q, qi));
+      o[poly] = d2u(canon_full(d1[j][i], q, qi));
+      o[2 * poly] = d2u(canon_full(d2[j][i], q, qi));
+    }
+}
+// false: the step counts are no multiples of a tile (the caller runs k_tensor_sum)
+bool launch_tensor_tile(blb_ctx* c, const uint64_t* A, const uint64_t* Y, uint64_t* T3, int m, int nj, int Bb, int nl) {
+#define TILE(tj, ti)                                                                                                              \
+  if (nj % tj == 0 && Bb % ti == 0) {                                                                                             \
+    const dim3 grid(c->n / 256, nj / tj * (Bb / ti) * nl);                                                                        \
+    emit(c, [=, stream = c->stream] { k_tensor_tile<tj, ti><<<grid, 256, 0, stream>>>(A, Y, T3, m, Bb, nl, c->n, c->mt); });      \
+    return true;                                                                                                                  \
+  }
+  TILE(4, 4)
+  TILE(2, 2)
+#undef TILE
+  return false;
+}
+
 // out[o] (+)= sum over its terms of ct (.) mask, whole degree-1 ciphertexts at nl limbs
 __global__ void k_masked_acc(const CcTerm* __restrict__ terms, const int* __restrict__ off, uint64_t* const* __restrict__ outs, int nl,
                              int n, ModTable mt, int accumulate) {

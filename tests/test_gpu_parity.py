@@ -372,6 +372,20 @@ def _cc_case(c, heads, L, d, seed, outputs=None, prerot=True, schedule=0):
     return dict(Q=Q, Kt=Kt, keys_o=keys_o, keys_g=keys_g, plan=plan, info=info, A=A_g, B=B_g, C=Cd, want=want, level=level)
 
 
+@pytest.mark.parametrize("heads,L,d", [(512, 4, 12), (128, 8, 20), (256, 8, 5), (32, 16, 44)])
+def test_matmul_cc_tensor_tiles(c3s, heads, L, d):
+    """BSGS products whose step counts give tiles of 2 x 2 outputs (L' = 4: 2 x 2 steps; L' = 8: 4 x 2) and
+    the smallest of 4 x 4 (L' = 16), with sums of 1 to 9 ciphertexts (no multiple of the reduction's four):
+    word for word against the oracle."""
+    r = _cc_case(c3s, heads, L, d, 3 * heads + L, None, True, 1)
+    for O_want, outs, grp in r["want"]:
+        for o in range(grp["n_out"]):
+            got = c3s.export(r["C"][_out_index(r["info"], grp, o)])
+            assert np.array_equal(got, O_want[o]), f"group H={grp['H']} output {o}"
+    c3s.B.blb_plan_destroy(r["plan"])
+    c3s.B.blb_keys_destroy(r["keys_g"])
+
+
 @pytest.fixture(scope="module")
 def c5p(blb, orc):
     """five ciphertext primes at N = 16384 (two special, digits of two primes): room for step 1
