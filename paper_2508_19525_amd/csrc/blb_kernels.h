@@ -22,6 +22,7 @@ struct PolyDesc {
   int32_t flags;  // kAddBoth: src3 is added as it is too, not only under the Galois element
 };
 constexpr int32_t kAddBoth = 1;
+constexpr int32_t kUpperHalf = 2;  // set in a workgroup's own copy: it holds the polynomial's upper half
 
 // Bit-reversal of j over log_n bits
 __device__ __forceinline__ uint32_t brv_bits(uint32_t j, int log_n) { return __brev(j) >> (32 - log_n); }

@@ -44,8 +44,8 @@ struct NttSrc {
     if (base + span > count) return w;
     return base + (w - base) % 8 * group + (w - base) / 8;
   }
-  __device__ __forceinline__ PolyDesc get(int w) const {
-    const int p = at(w);
+  __device__ __forceinline__ PolyDesc get(int w) const { return desc(at(w)); }
+  __device__ __forceinline__ PolyDesc desc(int p) const {
     if (descs) {
       // scalar loads (the table is read-only while the kernel runs): they do not join the
       // in-order vector-memory counter, so fetching a descriptor never waits for the stores
@@ -146,9 +146,11 @@ struct Pass {
   // register slot i has its last value, so that what follows (the exchange's LDS writes) is issued
   // between the last stage's arithmetic instead of after it.  FIRST / LAST: the executed first /
   // last pass of the transform.
-  template <bool FWD, bool FIRST, bool LAST, class Mid, class Sink>
-  __device__ static __forceinline__ void run(double (&x)[PT], const double* __restrict__ tw, double q, double qi, int tid, const Mid& mid,
-                                             const Sink& sink) {
+  // SUB: this is a transform of half the ring's polynomial, whose first stage is done; `half` picks the
+  // half's twiddles (stage s has 2^(s+1) of them in the whole transform, the second half's after the first's).
+  template <bool FWD, bool FIRST, bool LAST, bool SUB, class Mid, class Sink>
+  __device__ static __forceinline__ void run(double (&x)[PT], const double* __restrict__ tw, double q, double qi, int tid, int half,
+                                             const Mid& mid, const Sink& sink) {
     // Lazy reduction.  Twiddles are centred (|w| <= q/2), so for |b| <= B q a product is below q/2 +
     // 0.1875 B q (the quotient estimate is off by < B 2^-53 q, the dropped low part of b w is below
     // that too), and every FP64 sum and product step is exact up to 8 q < 2^53.
@@ -174,7 +176,8 @@ struct Pass {
 #pragma unroll
         for (int k = 0; k < GS; ++k) {
           if (k & t_loc) continue;
-          const int widx = (1 << (S0 + u)) + (hi << u) + (k >> (R_LOG - u));
+          int widx = (1 << (S0 + u)) + (hi << u) + (k >> (R_LOG - u));
+          if constexpr (SUB) widx += (1 + half) << (S0 + u);
           const double w = tw[widx];
           double& a = x[h * GS + k];
           double& b = x[h * GS + k + t_loc];
@@ -304,9 +307,9 @@ struct NoSink {
 // the whole prefetch has arrived: issue() runs after the leading passes that load per-lane
 // twiddles (before the first pass when it has none).  REUSED: the LDS may still be read by the
 // previous polynomial's last exchange (persistent kernel), so the first exchange needs its barrier too.
-template <int LOGN, int PT, bool FWD, bool REUSED, class Issue = NoIssue>
+template <int LOGN, int PT, bool FWD, bool REUSED, bool SUB = false, class Issue = NoIssue>
 __device__ __forceinline__ void ntt_core(double* lds, double (&x)[PT], const double* tw, double q, double qi, int tid,
-                                         const Issue& issue = Issue()) {
+                                         const Issue& issue = Issue(), int half = 0) {
   using S = Sched<LOGN, PT>;
   using P0 = typename S::P0;
   using P1 = typename S::P1;
@@ -317,39 +320,39 @@ __device__ __forceinline__ void ntt_core(double* lds, double (&x)[PT], const dou
   auto sink = [&](auto pass) { return LdsSink<decltype(pass), PT>{lds + pad_idx(decltype(pass)::idx(tid, 0)), x}; };
   if constexpr (FWD) {
     if constexpr (at == 0) issue();
-    P0::template run<true, true, false>(x, tw, q, qi, tid, FirstMid(), sink(P0()));
+    P0::template run<true, true, false, SUB>(x, tw, q, qi, tid, half, FirstMid(), sink(P0()));
     if constexpr (at == 1) issue();
     read_layout<P1, true>(lds, x, tid);
-    P1::template run<true, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P1()));
+    P1::template run<true, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P1()));
     if constexpr (at == 2) issue();
     read_layout<P2, true>(lds, x, tid);
     if constexpr (S::HAS3) {
-      P2::template run<true, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P2()));
+      P2::template run<true, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P2()));
       if constexpr (at == 3) issue();
       read_layout<P3, true>(lds, x, tid);
-      P3::template run<true, false, true>(x, tw, q, qi, tid, NoMid(), NoSink());
+      P3::template run<true, false, true, SUB>(x, tw, q, qi, tid, half, NoMid(), NoSink());
       if constexpr (at == 4) issue();
     } else {
-      P2::template run<true, false, true>(x, tw, q, qi, tid, NoMid(), NoSink());
+      P2::template run<true, false, true, SUB>(x, tw, q, qi, tid, half, NoMid(), NoSink());
       if constexpr (at == 3) issue();
     }
   } else {
     // pass k of the inverse runs Pass index NP - 1 - k
     if constexpr (at == 0) issue();
     if constexpr (S::HAS3) {
-      P3::template run<false, true, false>(x, tw, q, qi, tid, FirstMid(), sink(P3()));
+      P3::template run<false, true, false, SUB>(x, tw, q, qi, tid, half, FirstMid(), sink(P3()));
       if constexpr (at == 1) issue();
       read_layout<P2, false>(lds, x, tid);
-      P2::template run<false, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P2()));
+      P2::template run<false, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P2()));
     } else {
-      P2::template run<false, true, false>(x, tw, q, qi, tid, FirstMid(), sink(P2()));
+      P2::template run<false, true, false, SUB>(x, tw, q, qi, tid, half, FirstMid(), sink(P2()));
     }
     if constexpr (at == S::NP - 2) issue();
     read_layout<P1, false>(lds, x, tid);
-    P1::template run<false, false, false>(x, tw, q, qi, tid, LdsMid(), sink(P1()));
+    P1::template run<false, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P1()));
     if constexpr (at == S::NP - 1) issue();
     read_layout<P0, false>(lds, x, tid);
-    P0::template run<false, false, true>(x, tw, q, qi, tid, NoMid(), NoSink());
+    P0::template run<false, false, true, SUB>(x, tw, q, qi, tid, half, NoMid(), NoSink());
     if constexpr (at == S::NP) issue();
   }
 }
@@ -377,7 +380,7 @@ __device__ __forceinline__ void ntt_store(double (&x)[PT], const PolyDesc& d, co
     st.template put_all<LOGN, PT, LastPass<LOGN, PT, FWD>::GS>(d, j, v, lds, tid);
     return;
   }
-  st.template prepare<PT>(d, lds, tid);  // the epilogue may stage an operand in LDS (free after the last pass)
+  st.template prepare<LOGN, PT>(d, lds, tid);  // the epilogue may stage an operand in LDS (free after the last pass)
   // Every operand load of the epilogue is issued before the first store: vector-memory
   // completion is tracked in issue order, so a load issued after a store could only be
   // consumed once that store had completed.
@@ -411,6 +414,39 @@ __global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_e
   ntt_load<LOGN, PT, FWD>(x, d, ld, q, qi, tid);
   ntt_core<LOGN, PT, FWD, false>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid);
   ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
+}
+
+// Half a polynomial per workgroup (forward, N = 2^(LOGN + 1)): the first stage, x_j +- w x_{j + N/2}, is
+// done while the words are read, and each half is a transform of its own.  At N = 16384 a whole
+// polynomial's exchange buffer leaves one workgroup per CU with nothing to run while it loads, stages or
+// stores; two halves fit a CU, and few polynomials spread over twice the CUs.  Both halves read all
+// words (the same XCD's L2 serves the second) and form the first stage's products.  Bound by FP64 issue
+// and LDS in turn; ModDown conversions of the attention output 2400 -> 2165 us in 10 launches, rescales
+// 629 -> 533 us in 7.
+template <int LOGN, int PT, class LoadOp, class StoreOp>
+__global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_eu(waves_per_eu<PT>()))) void k_ntt_half(
+    NttSrc descs, const double* __restrict__ tw_all, ModTable mt, LoadOp ld, StoreOp st) {
+  constexpr int H = 1 << LOGN;
+  __shared__ double lds[H + H / 16];
+  const int w = descs.at(blockIdx.x), half = w & 1;
+  PolyDesc d = descs.desc(w >> 1);
+  const double q = mt.m[d.mod].q, qi = mt.m[d.mod].qinv;
+  const int tid = threadIdx.x;
+  const double* tw = tw_all + (size_t)d.mod * 2 * H;
+  const double w1 = half ? -tw[1] : tw[1];
+  double x[PT];
+  const auto cst = ld.half_constants(d, w1, q, qi);
+#pragma unroll
+  for (int i = 0; i < PT; ++i) {
+    const int j = FirstPass<LOGN, PT, true>::idx(tid, i);
+    x[i] = ld.half(d, j, H, cst, q, qi);
+  }
+  ntt_core<LOGN, PT, true, false, true>(lds, x, tw, q, qi, tid, NoIssue(), half);
+  d.dst += half * H;
+  d.src2 += half * H;
+  if (d.src3) d.src3 += half * H;
+  d.flags |= half ? kUpperHalf : 0;
+  ntt_store<LOGN, PT, true>(x, d, st, q, qi, 0.0, tid, lds);
 }
 
 // Persistent, software-pipelined variant: a grid of resident workgroups walks the descriptor
@@ -476,6 +512,21 @@ template <int PT, bool FWD, class LoadOp, class StoreOp>
 void launch_ntt_pt(blb_ctx* c, NttSrc d_descs, int count, LoadOp ld, StoreOp st) {
   const double* tw = FWD ? c->d_tw_fwd : c->d_tw_inv;
   const int threads = c->n / PT;
+  // At N = 16384 the transforms that read scratch (base conversions, rescale) run as two halves: 12-head
+  // Q K^T 3558 -> 3321 us, attention output 7358 -> 6977 us, a rotate-and-sum over 1 / 24 / 64
+  // ciphertexts (4 primes + 2 special) 1154 / 1538 / 2889 -> 1033 / 1503 / 2793 us (with one special prime
+  // 953 / 1587 / 3291 -> 824 / 1468 / 2998 us).  Not plan transforms: their coefficients' reductions, which
+  // both halves would do, make them slower (145 us against the persistent grid's 130).
+  constexpr bool kHalf = FWD && LoadOp::kHalf;
+  if constexpr (kHalf) {
+    if (c->log_n == 14) {
+      NttSrc src = d_descs;
+      src.group = 2 * src.group;
+      src.count = 2 * count;
+      emit(c, [=, stream = c->stream] { k_ntt_half<13, PT><<<2 * count, threads / 2, 0, stream>>>(src, tw, c->mt, ld, st); });
+      return;
+    }
+  }
   // The persistent grid pays at N = 16384, where one polynomial fills a CU's LDS and nothing else hides
   // its loads, from the third round of polynomials on (2048 of them: 125-135 us against 137-144 one per
   // workgroup; 512: equal; 256: 23 against 21).  At N = 4096 / 8192 four / two workgroups per CU overlap
@@ -489,7 +540,10 @@ void launch_ntt_pt(blb_ctx* c, NttSrc d_descs, int count, LoadOp ld, StoreOp st)
   switch (c->log_n) {
     case 12: emit(c, [=, stream = c->stream] { k_ntt<12, PT, FWD><<<count, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st); }); break;
     case 13: emit(c, [=, stream = c->stream] { k_ntt<13, PT, FWD><<<count, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st); }); break;
-    case 14: emit(c, [=, stream = c->stream] { k_ntt<14, PT, FWD><<<count, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st); }); break;
+    case 14:
+      if constexpr (!kHalf)
+        emit(c, [=, stream = c->stream] { k_ntt<14, PT, FWD><<<count, threads, 0, stream>>>(d_descs, tw, c->mt, ld, st); });
+      break;
     default: break;
   }
 }
@@ -512,8 +566,12 @@ __device__ __forceinline__ uint64_t gld(const uint64_t* p, int j) { return ((con
 __device__ __forceinline__ void gst(uint64_t* p, int j, uint64_t v) { ((gu64*)p)[j] = v; }
 
 // Loads: raw(d, j) fetches word j, cvt() turns it into this pass's double operand.
+// kHalf: k_ntt_half may run it; half_constants() and half() then give the first forward stage's result
+// x_j + w x_{j + H} (w the twiddle, negated for the upper half), reduced.  Only for loads whose source
+// is scratch that nothing writes meanwhile: both halves read all of it.
 // kPersistent: whether the persistent kernel, which prefetches one raw word per value, may run it.
 struct LdPlain {
+  static constexpr bool kHalf = false;
   static constexpr bool kPersistent = true;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
   __device__ double cvt(const PolyDesc&, uint64_t u, double, double) const { return u2d(u); }
@@ -521,6 +579,7 @@ struct LdPlain {
 };
 // Stores: prepare() may stage an operand in LDS, fetch(d, j) loads the epilogue's global
 // operand for word j, put() writes word j.
+// In k_ntt_half the words at dst, src2 and src3 are the half's; kUpperHalf in the flags tells which.
 // kPersistent: whether the persistent kernel may run this epilogue.  The ModDown epilogue
 // stages an operand through registers into LDS; next to a register prefetch of the following
 // polynomial that no longer fits 128 VGPRs, so it always runs one polynomial per workgroup.
@@ -529,13 +588,14 @@ struct StPlain {
   static constexpr bool kPersistent = true;
   static constexpr bool kPack = false;
   struct Operand {};
-  template <int PT>
+  template <int LOGN, int PT>
   __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc&, int) const { return {}; }
   __device__ void put(const PolyDesc& d, int j, double v, Operand, double, double, const double*) const { gst(d.dst, j, d2u(v)); }
 };
 // load an integer coefficient (int64) and reduce it into this modulus: plan transforms
 struct LdCoef {
+  static constexpr bool kHalf = false;
   static constexpr bool kPersistent = true;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
   __device__ double cvt(const PolyDesc&, uint64_t u, double q, double qi) const { return i64_mod(u, q, qi); }
@@ -544,7 +604,8 @@ struct LdCoef {
 // load a residue of another modulus (aux = that modulus as double) and lift it centred into
 // this modulus: used by rescale (last limb -> limb i)
 struct LdCentredLift {
-  static constexpr bool kPersistent = true;
+  static constexpr bool kHalf = true;
+  static constexpr bool kPersistent = false;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
   __device__ double cvt(const PolyDesc& d, uint64_t u, double q, double qi) const {
     const double v = u2d(u);
@@ -553,6 +614,11 @@ struct LdCentredLift {
     return reduce_s(t, q, qi);
   }
   __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
+  __device__ double half_constants(const PolyDesc&, double w, double, double) const { return w; }
+  __device__ double half(const PolyDesc& d, int j, int H, double w, double q, double qi) const {
+    const uint64_t a = raw(d, j), b = raw(d, j + H);
+    return reduce_s(cvt(d, a, q, qi) + mulmod_s(cvt(d, b, q, qi), w, q, qi), q, qi);
+  }
 };
 // Base conversion (no centring) of n_src limbs into this modulus, sum_i y_i cst_i with y_i < q_i of
 // limb i: the ModUp of a digit and the ModDown of the special limbs, done while the transform reads
@@ -562,9 +628,8 @@ struct LdCentredLift {
 // MOST: bound on n_src (1: one limb always); STRIDE: distance of the constants.
 template <int MOST, int STRIDE>
 struct LdConv {
-  static constexpr bool kPersistent = MOST == 1;
-  __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
-  __device__ double cvt(const PolyDesc&, uint64_t u, double, double) const { return u2d(u); }
+  static constexpr bool kPersistent = false;
+  static constexpr bool kHalf = MOST <= 2;  // more: the stage's constants would not fit the registers
   __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const {
     if constexpr (MOST == 1) return u2d(gld(d.src, j));
     typedef __attribute__((address_space(4))) const double kdouble;
@@ -578,6 +643,42 @@ struct LdConv {
       if (i < d.n_src) acc += mulmod_s(u2d(u[i]), ((const kdouble*)d.cst)[i * STRIDE], q, qi);
     return reduce_s(acc, q, qi);
   }
+  // sum_i y_i[j] cst_i + y_i[j + H] (w cst_i): the stage's product costs no more than the conversion's
+  struct HalfConst {
+    double c[MOST], wc[MOST];
+  };
+  __device__ HalfConst half_constants(const PolyDesc& d, double w, double q, double qi) const {
+    typedef __attribute__((address_space(4))) const double kdouble;
+    HalfConst h;
+#pragma unroll
+    for (int i = 0; i < MOST; ++i) {
+      h.c[i] = MOST == 1 ? 1.0 : i < d.n_src ? ((const kdouble*)d.cst)[i * STRIDE] : 0.0;
+      h.wc[i] = MOST == 1 ? w : reduce_s(mulmod_s(h.c[i], w, q, qi), q, qi);
+    }
+    return h;
+  }
+  __device__ double half(const PolyDesc& d, int j, int H, const HalfConst& h, double q, double qi) const {
+    if constexpr (MOST == 1) {
+      const uint64_t a = gld(d.src, j), b = gld(d.src, j + H);
+      return reduce_s(u2d(a) + mulmod_s(u2d(b), h.wc[0], q, qi), q, qi);
+    } else {
+      uint64_t a[MOST], b[MOST];
+#pragma unroll
+      for (int i = 0; i < MOST; ++i)
+        if (i < d.n_src) {
+          a[i] = gld(d.src + ((size_t)i << d.log_n), j);
+          b[i] = gld(d.src + ((size_t)i << d.log_n), j + H);
+        }
+      double acc = 0.0;
+#pragma unroll
+      for (int i = 0; i < MOST; ++i)
+        if (i < d.n_src) {
+          if (i > 0 && (i & 3) == 0) acc = reduce_s(acc, q, qi);  // four limbs: |acc| < q/2 + 8 x 0.875 q
+          acc += mulmod_s(u2d(a[i]), h.c[i], q, qi) + mulmod_s(u2d(b[i]), h.wc[i], q, qi);
+        }
+      return reduce_s(acc, q, qi);
+    }
+  }
 };
 // rescale epilogue: dst[j] <- (c_i[j] - v) * q_l^-1 mod q_i, c_i = d.src2, aux2 = q_l^-1 mod q_i
 struct StRescale {
@@ -585,7 +686,7 @@ struct StRescale {
   static constexpr bool kPersistent = true;
   static constexpr bool kPack = false;
   using Operand = uint64_t;
-  template <int PT>
+  template <int LOGN, int PT>
   __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc& d, int j) const { return gld(d.src2, j); }
   __device__ void put(const PolyDesc& d, int j, double v, Operand ci, double q, double qi, const double*) const {
@@ -602,10 +703,10 @@ struct StModDown {
   static constexpr bool kPersistent = false;
   static constexpr bool kPack = false;
   using Operand = uint64_t;
-  template <int PT>
+  template <int LOGN, int PT>
   __device__ void prepare(const PolyDesc& d, double* lds, int tid) const {
     if (!d.src3) return;  // uniform over the workgroup (one descriptor)
-    const int T = (1 << d.log_n) / PT;
+    constexpr int T = (1 << LOGN) / PT;
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
@@ -618,7 +719,9 @@ struct StModDown {
   __device__ void put(const PolyDesc& d, int j, double v, Operand ui, double q, double qi, const double* lds) const {
     double r = canon2(mulmod_s(u2d(ui) - v, d.aux2, q, qi), q, qi);  // |u_i - v| < 2.8 q: |product| < 1.6 q
     if (d.src3) {
-      r += lds[pad_idx(d.gal ? (int)gal_perm((uint32_t)j, d.gal, d.log_n) : j)];
+      // (a rotation's element is 1 mod 4, so it keeps the exponents' bit that tells the halves apart)
+      const int up = d.flags & kUpperHalf ? 1 << (d.log_n - 1) : 0;
+      r += lds[pad_idx(d.gal ? (int)gal_perm((uint32_t)(j + up), d.gal, d.log_n) - up : j)];
       r = r >= q ? r - q : r;
       if (d.flags & kAddBoth) {
         r += lds[pad_idx(j)];
@@ -688,7 +791,7 @@ struct StPack50 {
       ((g32*)top)[t] = word;
     }
   }
-  template <int PT>
+  template <int LOGN, int PT>
   __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc&, int) const { return {}; }
   __device__ void put(const PolyDesc&, int, double, Operand, double, double, const double*) const {}
@@ -700,7 +803,7 @@ struct StAddTo {
   static constexpr bool kPersistent = true;
   static constexpr bool kPack = false;
   using Operand = uint64_t;
-  template <int PT>
+  template <int LOGN, int PT>
   __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc& d, int j) const { return gld(d.src2, j); }
   __device__ void put(const PolyDesc& d, int j, double v, Operand a, double q, double, const double*) const {

@@ -825,6 +825,41 @@ def test_ntt_matches_oracle(request, name, n_polys, variant, radix):
     B.blb_ntt(c.h, dev, 0, 1)
 
 
+@pytest.mark.parametrize("n_q,n_sp,dnum", [(3, 1, 3), (4, 2, 2), (3, 2, 3), (4, 3, 2)])
+@pytest.mark.parametrize("radix", [16, 32])
+def test_transforms_in_halves(blb, orc, n_q, n_sp, dnum, radix):
+    """N = 16384: the transforms that take half a polynomial per workgroup (base conversions from one or two
+    limbs, rescale) give the oracle's words, with a permuted operand added (its halves stay apart under the
+    Galois element) and, in the rotate-and-sum, with both; digits of one, of two and of
+    an uneven number of limbs, special primes of one to three (three: whole polynomials)."""
+    c = Ctx(blb, orc, 14, n_q, n_sp, dnum)
+    blb.blb_ctx_set_knob(c.h, blb.BLB_KNOB_NTT_RADIX, radix)
+    steps = [1, -7, 4096, -4096, 2048, -2048]
+    keys_o = orc.Keys(c.o, 77, sorted({c.o.galois_elt(s) for s in steps}))
+    keys_g = blb.blb_keygen(c.h, 77, steps)
+    rng = np.random.default_rng(14 + n_q)
+    for level in range(n_q - 1, -1, -1):
+        words = np.stack([np.stack([rng.integers(0, int(q), c.n, dtype=np.uint64) for q in c.o.q[: level + 1]]) for _ in range(2)])
+        words[0, :, :5] = (c.o.q[: level + 1] - 1)[:, None]
+        words[1, :, 9000:9005] = 0
+        for s in (1, -7):
+            ct, out = c.import_ct(words, level), c.ct(level)
+            blb.blb_rotate(c.h, keys_g, ct, s, out)
+            assert np.array_equal(c.export(out), keys_o.rotate(words, level, s)), f"rotation {s} at level {level}"
+        if level > 0:
+            ct, out = c.import_ct(words, level), c.ct(level - 1)
+            blb.blb_rescale(c.h, ct, out)
+            assert np.array_equal(c.export(out), c.o.rescale(words, level)), f"rescale at level {level}"
+    level = n_q - 1
+    words = [keys_o.encrypt(c.o.encode_rns(rng.uniform(-1, 1, c.n // 2), 2.0 ** 30, level), level, 12, t) for t in range(5)]
+    cts, outs = [c.import_ct(w, level) for w in words], [c.ct(level) for _ in words]
+    blb.blb_rotate_sum(c.h, keys_g, cts, outs, 2048, 4, 0, False)
+    for t, w in enumerate(words):
+        assert np.array_equal(c.export(outs[t]), keys_o.rotate_sum(w, level, 2048, 4, 0, False)), f"ct {t}"
+    blb.blb_keys_destroy(keys_g)
+    c.close()
+
+
 @pytest.mark.parametrize("n_polys", [85, 86, 130])
 def test_ntt_persistent_grid(c3s, n_polys):
     """The persistent grid (N = 16384, more than two limb-polys per compute unit: 86 and 130 polys of 6 limbs
