@@ -141,16 +141,48 @@ struct Pass {
   // needs one address per work-item and the slots become immediate offsets.
   static constexpr int lds_off(int i) { return pad_idx(idx(0, i)) - pad_idx(idx(0, 0)); }
 
+  // Twiddle k of group h in stage S0 + u.  SUB: this is a transform of half the ring's polynomial, whose
+  // first stage is done; `half` picks the half's twiddles (stage s has 2^(s+1) of them in the whole
+  // transform, the second half's after the first's).
+  template <bool SUB>
+  struct TwMem {
+    const double* __restrict__ tw;
+    int tid, half;
+    __device__ double operator()(int h, int u, int k) const {
+      // group index; compile-time when a pass spans whole columns (first pass), and uniform
+      // over the 64-lane wave when TL >= 64, so the twiddles come through scalar loads
+      int hi = (tid + h * T) / TL;
+      if constexpr (TL >= T) hi = (h * T) / TL;
+      else if constexpr (TL >= 64) hi = __builtin_amdgcn_readfirstlane(hi);
+      return tw[(1 << (S0 + u)) + (SUB ? (1 + half) << (S0 + u) : 0) + (hi << u) + k];
+    }
+  };
+  // the pass's twiddles in registers, loaded ahead of the pass
+  struct TwRegs {
+    double w[GPT][GS - 1];
+    template <bool FWD, class Mem>
+    __device__ void load(const Mem& mem) {  // in the order of use: loads complete in the order of issue
+#pragma unroll
+      for (int uu = 0; uu < R_LOG; ++uu)
+#pragma unroll
+        for (int h = 0; h < GPT; ++h)
+#pragma unroll
+          for (int k = 0; k < 1 << (FWD ? uu : R_LOG - 1 - uu); ++k) {
+            const int u = FWD ? uu : R_LOG - 1 - uu;
+            w[h][(1 << u) - 1 + k] = mem(h, u, k);
+          }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ double operator()(int h, int u, int k) const { return w[h][(1 << u) - 1 + k]; }
+  };
+
   // FWD: Cooley-Tukey stages in increasing order; else Gentleman-Sande in decreasing order.
   // mid() runs after the first executed stage, when every operand has been read; sink(i) after
   // register slot i has its last value, so that what follows (the exchange's LDS writes) is issued
   // between the last stage's arithmetic instead of after it.  FIRST / LAST: the executed first /
   // last pass of the transform.
-  // SUB: this is a transform of half the ring's polynomial, whose first stage is done; `half` picks the
-  // half's twiddles (stage s has 2^(s+1) of them in the whole transform, the second half's after the first's).
-  template <bool FWD, bool FIRST, bool LAST, bool SUB, class Mid, class Sink>
-  __device__ static __forceinline__ void run(double (&x)[PT], const double* __restrict__ tw, double q, double qi, int tid, int half,
-                                             const Mid& mid, const Sink& sink) {
+  template <bool FWD, bool FIRST, bool LAST, class Tw, class Mid, class Sink>
+  __device__ static __forceinline__ void run(double (&x)[PT], const Tw& tw, double q, double qi, const Mid& mid, const Sink& sink) {
     // Lazy reduction.  Twiddles are centred (|w| <= q/2), so for |b| <= B q a product is below q/2 +
     // 0.1875 B q (the quotient estimate is off by < B 2^-53 q, the dropped low part of b w is below
     // that too), and every FP64 sum and product step is exact up to 8 q < 2^53.
@@ -168,17 +200,10 @@ struct Pass {
       const int t_loc = GS >> (u + 1);
 #pragma unroll
       for (int h = 0; h < GPT; ++h) {
-        // group index; compile-time when a pass spans whole columns (first pass), and uniform
-        // over the 64-lane wave when TL >= 64, so the twiddles come through scalar loads
-        int hi = (tid + h * T) / TL;
-        if constexpr (TL >= T) hi = (h * T) / TL;
-        else if constexpr (TL >= 64) hi = __builtin_amdgcn_readfirstlane(hi);
 #pragma unroll
         for (int k = 0; k < GS; ++k) {
           if (k & t_loc) continue;
-          int widx = (1 << (S0 + u)) + (hi << u) + (k >> (R_LOG - u));
-          if constexpr (SUB) widx += (1 + half) << (S0 + u);
-          const double w = tw[widx];
+          const double w = tw(h, u, k >> (R_LOG - u));
           double& a = x[h * GS + k];
           double& b = x[h * GS + k + t_loc];
           if (FWD) {
@@ -318,41 +343,61 @@ __device__ __forceinline__ void ntt_core(double* lds, double (&x)[PT], const dou
   using FirstMid = std::conditional_t<REUSED, LdsMid, NoMid>;
   constexpr int at = S::template issue_after<FWD>();  // passes run before issue()
   auto sink = [&](auto pass) { return LdsSink<decltype(pass), PT>{lds + pad_idx(decltype(pass)::idx(tid, 0)), x}; };
+  auto mem = [&](auto pass) { return typename decltype(pass)::template TwMem<SUB>{tw, tid, half}; };
+  // One polynomial (or half) per workgroup: each pass's per-lane twiddles are loaded during the pass
+  // before it, so that no stage waits for its own (8192 limb-polys of N = 8192: 248 / 262 -> 234 / 238 us
+  // forward / inverse; of N = 4096, inverse: 99 -> 88-95 us; few limb-polys: equal).  Not forward at
+  // N = 4096, whose four workgroups per CU hide them (1024: 20.9 -> 21.7 us), nor in the persistent kernel,
+  // whose registers hold the next polynomial instead.
+  constexpr bool AHEAD = !REUSED && (LOGN == 13 || !FWD);
+  auto ahead = [&](auto pass, auto& regs) {
+    if constexpr (AHEAD && decltype(pass)::LANE_TW) regs.template load<FWD>(mem(pass));
+  };
+  auto use = [&](auto pass, const auto& regs) {
+    if constexpr (AHEAD && decltype(pass)::LANE_TW) return regs;
+    else return mem(pass);
+  };
+  typename P0::TwRegs t0;
+  typename P1::TwRegs t1;
+  typename P2::TwRegs t2;
+  typename S::Tail::TwRegs t3;
   if constexpr (FWD) {
     if constexpr (at == 0) issue();
-    P0::template run<true, true, false, SUB>(x, tw, q, qi, tid, half, FirstMid(), sink(P0()));
+    P0::template run<true, true, false>(x, mem(P0()), q, qi, [&] { FirstMid()(); ahead(P1(), t1); }, sink(P0()));
     if constexpr (at == 1) issue();
     read_layout<P1, true>(lds, x, tid);
-    P1::template run<true, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P1()));
+    P1::template run<true, false, false>(x, use(P1(), t1), q, qi, [&] { LdsMid()(); ahead(P2(), t2); }, sink(P1()));
     if constexpr (at == 2) issue();
     read_layout<P2, true>(lds, x, tid);
     if constexpr (S::HAS3) {
-      P2::template run<true, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P2()));
+      P2::template run<true, false, false>(x, use(P2(), t2), q, qi, [&] { LdsMid()(); ahead(P3(), t3); }, sink(P2()));
       if constexpr (at == 3) issue();
       read_layout<P3, true>(lds, x, tid);
-      P3::template run<true, false, true, SUB>(x, tw, q, qi, tid, half, NoMid(), NoSink());
+      P3::template run<true, false, true>(x, use(P3(), t3), q, qi, NoMid(), NoSink());
       if constexpr (at == 4) issue();
     } else {
-      P2::template run<true, false, true, SUB>(x, tw, q, qi, tid, half, NoMid(), NoSink());
+      P2::template run<true, false, true>(x, use(P2(), t2), q, qi, NoMid(), NoSink());
       if constexpr (at == 3) issue();
     }
   } else {
     // pass k of the inverse runs Pass index NP - 1 - k
     if constexpr (at == 0) issue();
     if constexpr (S::HAS3) {
-      P3::template run<false, true, false, SUB>(x, tw, q, qi, tid, half, FirstMid(), sink(P3()));
+      ahead(P3(), t3);
+      P3::template run<false, true, false>(x, use(P3(), t3), q, qi, [&] { FirstMid()(); ahead(P2(), t2); }, sink(P3()));
       if constexpr (at == 1) issue();
       read_layout<P2, false>(lds, x, tid);
-      P2::template run<false, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P2()));
+      P2::template run<false, false, false>(x, use(P2(), t2), q, qi, [&] { LdsMid()(); ahead(P1(), t1); }, sink(P2()));
     } else {
-      P2::template run<false, true, false, SUB>(x, tw, q, qi, tid, half, FirstMid(), sink(P2()));
+      ahead(P2(), t2);
+      P2::template run<false, true, false>(x, use(P2(), t2), q, qi, [&] { FirstMid()(); ahead(P1(), t1); }, sink(P2()));
     }
     if constexpr (at == S::NP - 2) issue();
     read_layout<P1, false>(lds, x, tid);
-    P1::template run<false, false, false, SUB>(x, tw, q, qi, tid, half, LdsMid(), sink(P1()));
+    P1::template run<false, false, false>(x, use(P1(), t1), q, qi, [&] { LdsMid()(); ahead(P0(), t0); }, sink(P1()));
     if constexpr (at == S::NP - 1) issue();
     read_layout<P0, false>(lds, x, tid);
-    P0::template run<false, false, true, SUB>(x, tw, q, qi, tid, half, NoMid(), NoSink());
+    P0::template run<false, false, true>(x, use(P0(), t0), q, qi, NoMid(), NoSink());
     if constexpr (at == S::NP) issue();
   }
 }
