@@ -414,30 +414,30 @@ __device__ __forceinline__ void ntt_load(double (&x)[PT], const PolyDesc& d, con
 template <int LOGN, int PT, bool FWD, class StoreOp>
 __device__ __forceinline__ void ntt_store(double (&x)[PT], const PolyDesc& d, const StoreOp& st, double q, double qi, double ninv, int tid,
                                           double* lds) {
-  if constexpr (StoreOp::kPack) {  // the epilogue takes all of a work-item's results at once
+  if constexpr (StoreOp::kAll) {  // the epilogue takes all of a work-item's results at once
     int j[PT];
     double v[PT];
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
       j[i] = LastPass<LOGN, PT, FWD>::idx(tid, i);
-      v[i] = canon2(FWD ? x[i] : mulmod_s(x[i], ninv, q, qi), q, qi);
+      const double y = FWD ? x[i] : mulmod_s(x[i], ninv, q, qi);
+      v[i] = FWD && StoreOp::kLazy ? y : canon2(y, q, qi);
     }
-    st.template put_all<LOGN, PT, LastPass<LOGN, PT, FWD>::GS>(d, j, v, lds, tid);
-    return;
-  }
-  st.template prepare<LOGN, PT>(d, lds, tid);  // the epilogue may stage an operand in LDS (free after the last pass)
-  // Every operand load of the epilogue is issued before the first store: vector-memory
-  // completion is tracked in issue order, so a load issued after a store could only be
-  // consumed once that store had completed.
-  typename StoreOp::Operand e[PT];
+    st.template put_all<LOGN, PT, LastPass<LOGN, PT, FWD>::GS>(d, j, v, q, qi, lds, tid);
+  } else {
+    // Every operand load of the epilogue is issued before the first store: vector-memory
+    // completion is tracked in issue order, so a load issued after a store could only be
+    // consumed once that store had completed.
+    typename StoreOp::Operand e[PT];
 #pragma unroll
-  for (int i = 0; i < PT; ++i) e[i] = st.fetch(d, LastPass<LOGN, PT, FWD>::idx(tid, i));
+    for (int i = 0; i < PT; ++i) e[i] = st.fetch(d, LastPass<LOGN, PT, FWD>::idx(tid, i));
 #pragma unroll
-  for (int i = 0; i < PT; ++i) {
-    const int j = LastPass<LOGN, PT, FWD>::idx(tid, i);
-    const double y = FWD ? x[i] : mulmod_s(x[i], ninv, q, qi);
-    const double v = FWD && StoreOp::kLazy ? y : canon2(y, q, qi);
-    st.put(d, j, v, e[i], q, qi, lds);
+    for (int i = 0; i < PT; ++i) {
+      const int j = LastPass<LOGN, PT, FWD>::idx(tid, i);
+      const double y = FWD ? x[i] : mulmod_s(x[i], ninv, q, qi);
+      const double v = FWD && StoreOp::kLazy ? y : canon2(y, q, qi);
+      st.put(d, j, v, e[i], q, qi);
+    }
   }
 }
 
@@ -622,21 +622,18 @@ struct LdPlain {
   __device__ double cvt(const PolyDesc&, uint64_t u, double, double) const { return u2d(u); }
   __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
 };
-// Stores: prepare() may stage an operand in LDS, fetch(d, j) loads the epilogue's global
-// operand for word j, put() writes word j.
+// Stores: fetch(d, j) loads the epilogue's global operand for word j, put() writes word j; or (kAll)
+// put_all() loads and writes all of a work-item's words.
 // In k_ntt_half the words at dst, src2 and src3 are the half's; kUpperHalf in the flags tells which.
-// kPersistent: whether the persistent kernel may run this epilogue.  The ModDown epilogue
-// stages an operand through registers into LDS; next to a register prefetch of the following
-// polynomial that no longer fits 128 VGPRs, so it always runs one polynomial per workgroup.
+// kPersistent: whether the persistent kernel may run this epilogue (the ModDown epilogue's operands do
+// not fit 128 VGPRs next to a prefetch of the following polynomial).
 struct StPlain {
   static constexpr bool kLazy = false;
   static constexpr bool kPersistent = true;
-  static constexpr bool kPack = false;
+  static constexpr bool kAll = false;
   struct Operand {};
-  template <int LOGN, int PT>
-  __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc&, int) const { return {}; }
-  __device__ void put(const PolyDesc& d, int j, double v, Operand, double, double, const double*) const { gst(d.dst, j, d2u(v)); }
+  __device__ void put(const PolyDesc& d, int j, double v, Operand, double, double) const { gst(d.dst, j, d2u(v)); }
 };
 // load an integer coefficient (int64) and reduce it into this modulus: plan transforms
 struct LdCoef {
@@ -729,51 +726,78 @@ struct LdConv {
 struct StRescale {
   static constexpr bool kLazy = true;
   static constexpr bool kPersistent = true;
-  static constexpr bool kPack = false;
+  static constexpr bool kAll = false;
   using Operand = uint64_t;
-  template <int LOGN, int PT>
-  __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc& d, int j) const { return gld(d.src2, j); }
-  __device__ void put(const PolyDesc& d, int j, double v, Operand ci, double q, double qi, const double*) const {
+  __device__ void put(const PolyDesc& d, int j, double v, Operand ci, double q, double qi) const {
     const double r = mulmod_s(u2d(ci) - v, d.aux2, q, qi);  // |c_i - v| < 2.8 q: |r| < 1.6 q
     gst(d.dst, j, d2u(canon2(r, q, qi)));
   }
 };
 // ModDown epilogue: dst[j] <- (u_i[j] - v) * P^-1 (+ add[j] if src3), u_i = src2 (u64).
-// For a rotation add = sigma_g(c0), a permuted read of src3 (kAddBoth: sigma_g(c0) + c0).  src3 is staged in LDS with
-// coalesced reads (then read there, at the permuted index for a rotation), which keeps the
-// epilogue's global loads to one word per output.
+// For a rotation add = sigma_g(c0), a permuted read of src3 (kAddBoth: sigma_g(c0) + c0).  g is odd, so
+// sigma_g keeps aligned runs of 2^k words together (their exponents differ in the top k bits only): a
+// wave's permuted read covers whole lines, and a pair of words is one load, swapped or not.  Against
+// staging src3 in LDS (two barriers, and two waits for memory in turn): ModDowns of the attention output
+// 2090-2185 -> 1984 us in 10 launches (N = 16384), of 24 rotate-and-sums 154 -> 146 us in 11 (N = 8192), of a
+// single rotation 7.8 -> 7.4 us (N = 4096).
 struct StModDown {
   static constexpr bool kLazy = true;
   static constexpr bool kPersistent = false;
-  static constexpr bool kPack = false;
-  using Operand = uint64_t;
-  template <int LOGN, int PT>
-  __device__ void prepare(const PolyDesc& d, double* lds, int tid) const {
-    if (!d.src3) return;  // uniform over the workgroup (one descriptor)
-    constexpr int T = (1 << LOGN) / PT;
-    lds_barrier();
+  static constexpr bool kAll = true;
+  typedef uint64_t pair __attribute__((ext_vector_type(2), aligned(8)));
+  typedef __attribute__((address_space(1))) pair gpair;
+  static __device__ pair load(const uint64_t* p, int j) { return *(const gpair*)((const gu64*)p + j); }
+  template <int LOGN, int PT, int GS>
+  __device__ void put_all(const PolyDesc& d, const int (&j)[PT], const double (&v)[PT], double q, double qi, double*, int) const {
+    static_assert(GS % 2 == 0, "runs of pairs");
+    constexpr int P = PT / 2;
+    pair u[P], a[P];
+    uint32_t swap = 0;
+    // (a rotation's element is 1 mod 4, so it keeps the exponents' bit that tells the halves apart)
+    const int up = d.flags & kUpperHalf ? 1 << (d.log_n - 1) : 0;
+    auto load_add = [&](int m) {
+      const int jp = d.gal ? (int)gal_perm((uint32_t)(j[2 * m] + up), d.gal, d.log_n) - up : j[2 * m];
+      a[m] = load(d.src3, jp & ~1);
+      swap |= (uint32_t)(jp & 1) << m;
+    };
+    auto add = [&](double& x, uint64_t y) {
+      x += u2d(y);
+      x = x >= q ? x - q : x;
+    };
 #pragma unroll
-    for (int i = 0; i < PT; ++i) {
-      const int j = tid + i * T;
-      lds[pad_idx(j)] = u2d(gld(d.src3, j));
+    for (int m = 0; m < P; ++m) u[m] = load(d.src2, j[2 * m]);
+    if (d.src3) {  // uniform over the workgroup (one descriptor)
+#pragma unroll
+      for (int m = 0; m < P / 2; ++m) load_add(m);
     }
-    lds_barrier();
-  }
-  __device__ Operand fetch(const PolyDesc& d, int j) const { return gld(d.src2, j); }
-  __device__ void put(const PolyDesc& d, int j, double v, Operand ui, double q, double qi, const double* lds) const {
-    double r = canon2(mulmod_s(u2d(ui) - v, d.aux2, q, qi), q, qi);  // |u_i - v| < 2.8 q: |product| < 1.6 q
+    double r[PT];
+#pragma unroll
+    for (int i = 0; i < PT; ++i)
+      r[i] = canon2(mulmod_s(u2d(u[i / 2][i % 2]) - v[i], d.aux2, q, qi), q, qi);  // |u_i - v| < 2.8 q: |product| < 1.6 q
     if (d.src3) {
-      // (a rotation's element is 1 mod 4, so it keeps the exponents' bit that tells the halves apart)
-      const int up = d.flags & kUpperHalf ? 1 << (d.log_n - 1) : 0;
-      r += lds[pad_idx(d.gal ? (int)gal_perm((uint32_t)(j + up), d.gal, d.log_n) - up : j)];
-      r = r >= q ? r - q : r;
+#pragma unroll
+      for (int m = P / 2; m < P; ++m) load_add(m);  // (all P at once do not fit 128 VGPRs)
+#pragma unroll
+      for (int m = 0; m < P; ++m) {
+        const bool s = swap >> m & 1;
+        add(r[2 * m], s ? a[m][1] : a[m][0]);
+        add(r[2 * m + 1], s ? a[m][0] : a[m][1]);
+      }
       if (d.flags & kAddBoth) {
-        r += lds[pad_idx(j)];
-        r = r >= q ? r - q : r;
+#pragma unroll
+        for (int m = 0; m < P; ++m) a[m] = load(d.src3, j[2 * m]);
+#pragma unroll
+        for (int i = 0; i < PT; ++i) add(r[i], a[i / 2][i % 2]);
+      }
+      // dst may be src3 itself: every work-item's permuted reads have arrived before any store
+      if (d.gal) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_barrier();
       }
     }
-    gst(d.dst, j, d2u(r));
+#pragma unroll
+    for (int m = 0; m < P; ++m) *(gpair*)((gu64*)d.dst + j[2 * m]) = pair{d2u(r[2 * m]), d2u(r[2 * m + 1])};
   }
 };
 
@@ -785,10 +809,9 @@ struct StModDown {
 struct StPack50 {
   static constexpr bool kLazy = false;
   static constexpr bool kPersistent = true;
-  static constexpr bool kPack = true;
-  struct Operand {};
+  static constexpr bool kAll = true;
   template <int LOGN, int PT, int GS>
-  __device__ void put_all(const PolyDesc& d, const int (&j)[PT], const double (&v)[PT], double* lds, int tid) const {
+  __device__ void put_all(const PolyDesc& d, const int (&j)[PT], const double (&v)[PT], double, double, double* lds, int tid) const {
     constexpr int N = 1 << LOGN, T = N / PT;
     typedef __attribute__((address_space(1))) uint32_t g32;
     typedef __attribute__((address_space(1))) uint16_t g16;
@@ -836,22 +859,16 @@ struct StPack50 {
       ((g32*)top)[t] = word;
     }
   }
-  template <int LOGN, int PT>
-  __device__ void prepare(const PolyDesc&, double*, int) const {}
-  __device__ Operand fetch(const PolyDesc&, int) const { return {}; }
-  __device__ void put(const PolyDesc&, int, double, Operand, double, double, const double*) const {}
 };
 
 // add-into epilogue: dst[j] <- src2[j] + v mod q  (mask added to c0 in evaluation form)
 struct StAddTo {
   static constexpr bool kLazy = false;
   static constexpr bool kPersistent = true;
-  static constexpr bool kPack = false;
+  static constexpr bool kAll = false;
   using Operand = uint64_t;
-  template <int LOGN, int PT>
-  __device__ void prepare(const PolyDesc&, double*, int) const {}
   __device__ Operand fetch(const PolyDesc& d, int j) const { return gld(d.src2, j); }
-  __device__ void put(const PolyDesc& d, int j, double v, Operand a, double q, double, const double*) const {
+  __device__ void put(const PolyDesc& d, int j, double v, Operand a, double q, double) const {
     double r = u2d(a) + v;
     r = r >= q ? r - q : r;
     gst(d.dst, j, d2u(r));

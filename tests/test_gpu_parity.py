@@ -156,6 +156,32 @@ def test_rotate_matches_oracle(request, name, steps):
 
 
 @pytest.mark.parametrize("name", ["c1", "c2s", "c3s"])
+@pytest.mark.parametrize("off_in,off_out", [(1, 0), (0, 1), (1, 1)])
+def test_rotate_at_odd_words(request, name, off_in, off_out):
+    """Ciphertexts need 8-byte alignment only: a rotation whose input and / or output starts at an odd word
+    gives the oracle's words and writes nothing around them."""
+    c = request.getfixturevalue(name)
+    keys_o = c.orc.Keys(c.o, 23, [c.o.galois_elt(5)])
+    keys_g = c.B.blb_keygen(c.h, 23, [5])
+    level = c.n_q - 1
+    rng = np.random.default_rng(23)
+    words = np.stack([np.stack([rng.integers(0, int(q), c.n, dtype=np.uint64) for q in c.o.q[: level + 1]]) for _ in range(2)])
+    bufs, cts = [], []
+    for off in (off_in, off_out):
+        t = torch.full((words.size + 2,), 77, dtype=torch.int64, device="cuda")
+        ct = c.ct(level)
+        ct.data = t.data_ptr() + 8 * off
+        bufs.append(t)
+        cts.append(ct)
+    c.B.blb_import(c.h, words, cts[0])
+    c.B.blb_rotate(c.h, keys_g, cts[0], 5, cts[1])
+    assert np.array_equal(c.export(cts[1]), keys_o.rotate(words, level, 5))
+    out = bufs[1].cpu().numpy()
+    assert (out[:off_out] == 77).all() and (out[off_out + words.size :] == 77).all()
+    c.B.blb_keys_destroy(keys_g)
+
+
+@pytest.mark.parametrize("name", ["c1", "c2s", "c3s"])
 def test_rescale_matches_oracle(request, name):
     c = request.getfixturevalue(name)
     rng = np.random.default_rng(4)
