@@ -692,13 +692,28 @@ int ks_apply(blb_ctx* c, int level, const std::vector<const uint64_t*>& srcs, co
       if (ko[a].key != ko[b].key) return ko[a].key < ko[b].key;
       return ko[a].gal < ko[b].gal;
     });
-    std::vector<KsGroup> groups;
-    for (int i = 0; i < O;) {
+    // The r-th runs of all keys read much the same sources (a hoisted input is rotated by every step), so
+    // they follow each other, prime by prime: the digits of a run's sources modulo one prime (16 x 3 limb-polys
+    // at N = 16384: 0.8 MB of each XCD's L2) then serve all of its rotations.
+    std::vector<std::vector<KsGroup>> runs;
+    int n_groups = 0;
+    for (int i = 0, r = 0; i < O; ++n_groups) {
       int j = i + 1;
-      while (j < O && j - i < cap && ko[ord[j]].key == ko[ord[i]].key && ko[ord[j]].gal == ko[ord[i]].gal) ++j;
-      groups.push_back(KsGroup{i, j - i});
+      auto same = [&](int x) { return ko[ord[x]].key == ko[ord[i]].key && ko[ord[x]].gal == ko[ord[i]].gal; };
+      while (j < O && j - i < cap && same(j)) ++j;
+      if ((int)runs.size() <= r) runs.emplace_back();
+      runs[r].push_back(KsGroup{i, j - i, 0});
+      r = j < O && same(j) ? r + 1 : 0;
       i = j;
     }
+    std::vector<KsGroup> groups;
+    groups.reserve((size_t)n_groups * n_ext);
+    for (const auto& run : runs)
+      for (int e = 0; e < n_ext; ++e)
+        for (KsGroup g : run) {
+          g.ext = e;
+          groups.push_back(g);
+        }
     const int* ord_dev = upload_vec(c, ord);
     const KsGroup* g_dev = upload_vec(c, groups);
     if (!ord_dev || !g_dev) return BLB_EDEVICE;

@@ -108,11 +108,12 @@ struct KsOut {
 };
 
 // Key-grouped inner product: ord lists output indices so that each group's outputs (first,
-// count <= kKsGroupMax) share one switching key and Galois element.
+// count <= kKsGroupMax) share one switching key and Galois element.  One entry per prime.
 constexpr int kKsGroupMax = 16;
 constexpr int kKsMaxDigits = 4;
 struct KsGroup {
   int first, count;
+  int ext;  // modulo this prime of the extended basis
 };
 
 // matmul_cc launch records

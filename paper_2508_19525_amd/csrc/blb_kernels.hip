@@ -167,7 +167,33 @@ __device__ __forceinline__ __attribute__((address_space(1))) T* gmem(T* p) {
 // digits (hoisted order).  Thread per (o, e, two adjacent k); writes U[o][2][e][k] (evaluation
 // form).  For one wave the permuted reads stay inside one aligned block of 64 words: sigma_g
 // keeps the low log2(N) - 6 bits of the exponent index, which bit reversal maps to the high
-// bits of k.
+// bits of k.  For the same reason an aligned pair of words stays a pair: one load, swapped or not.
+typedef uint64_t u64pair __attribute__((ext_vector_type(2), aligned(8)));  // ciphertexts are 8-byte aligned
+__device__ __forceinline__ u64pair ld_pair(const uint64_t* p) { return *(const __attribute__((address_space(1))) u64pair*)p; }
+__device__ __forceinline__ void st_pair(uint64_t* p, double a, double b) {
+  *(__attribute__((address_space(1))) u64pair*)p = u64pair{d2u(a), d2u(b)};
+}
+struct KsPair {  // where words k0, k0 + 1 (k0 even) come from under the Galois element
+  uint32_t at;
+  bool swap;
+  __device__ KsPair(uint32_t k0, uint32_t gal, int log_n) {
+    const uint32_t kk = gal ? gal_perm(k0, gal, log_n) : k0;
+    at = kk & ~1u;
+    swap = kk & 1;
+  }
+};
+__device__ __forceinline__ const uint64_t* ks_digit(const KsOut& od, const uint64_t* X, const KsLevelConst* kc, int j, int e, int n_digits, int n_ext,
+                                                    int n) {
+  return e >= kc->dlo[j] && e < kc->dhi[j] ? od.c1 + (size_t)e * n : X + (((size_t)od.src * n_digits + j) * n_ext + e) * n;
+}
+__device__ __forceinline__ void ks_madd(double (&acc0)[2], double (&acc1)[2], u64pair w, bool swap, u64pair kb, u64pair ka, const ModEntry& mm) {
+  const double x[2] = {u2d(swap ? w[1] : w[0]), u2d(swap ? w[0] : w[1])};
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    acc0[v] += mulmod_s(x[v], u2d(kb[v]), mm.q, mm.qinv);
+    acc1[v] += mulmod_s(x[v], u2d(ka[v]), mm.q, mm.qinv);
+  }
+}
 __global__ void k_ks_inner(const KsOut* __restrict__ outs, const uint64_t* __restrict__ X, const KsLevelConst* __restrict__ kc,
                            uint64_t* __restrict__ U, int n, int log_n, int nl, int n_ext, int n_digits, int n_q) {
   const int k0 = (blockIdx.x * blockDim.x + threadIdx.x) * 2;
@@ -175,22 +201,15 @@ __global__ void k_ks_inner(const KsOut* __restrict__ outs, const uint64_t* __res
   const int o = blockIdx.y / n_ext;
   if (k0 >= n) return;
   const KsOut od = outs[o];
-  uint32_t kk[2];
-#pragma unroll
-  for (int v = 0; v < 2; ++v) kk[v] = od.gal ? gal_perm((uint32_t)(k0 + v), od.gal, log_n) : (uint32_t)(k0 + v);
+  const KsPair kk((uint32_t)k0, od.gal, log_n);
   const ModEntry mm = kc->ext[e];
   const int key_mod = e < nl ? e : n_q + (e - nl);
   double acc0[2] = {0.0, 0.0}, acc1[2] = {0.0, 0.0};
   for (int j = 0; j < n_digits; ++j) {
-    const auto xs = gmem((e >= kc->dlo[j] && e < kc->dhi[j]) ? od.c1 + (size_t)e * n : X + (((size_t)od.src * n_digits + j) * n_ext + e) * n);
-    const auto kb = gmem(od.key + (((size_t)j * 2 + 0) * kc->n_key_mod + key_mod) * n + k0);
-    const auto ka = gmem(od.key + (((size_t)j * 2 + 1) * kc->n_key_mod + key_mod) * n + k0);
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const double x = u2d(xs[kk[v]]);
-      acc0[v] += mulmod_s(x, u2d(kb[v]), mm.q, mm.qinv);
-      acc1[v] += mulmod_s(x, u2d(ka[v]), mm.q, mm.qinv);
-    }
+    const u64pair w = ld_pair(ks_digit(od, X, kc, j, e, n_digits, n_ext, n) + kk.at);
+    const u64pair kb = ld_pair(od.key + (((size_t)j * 2 + 0) * kc->n_key_mod + key_mod) * n + k0);
+    const u64pair ka = ld_pair(od.key + (((size_t)j * 2 + 1) * kc->n_key_mod + key_mod) * n + k0);
+    ks_madd(acc0, acc1, w, kk.swap, kb, ka, mm);
     if ((j & 3) == 3) {  // keep |acc| < 5q < 2^53
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
@@ -199,13 +218,8 @@ __global__ void k_ks_inner(const KsOut* __restrict__ outs, const uint64_t* __res
       }
     }
   }
-  uint64_t* u0 = U + (((size_t)o * 2 + 0) * n_ext + e) * n + k0;
-  uint64_t* u1 = U + (((size_t)o * 2 + 1) * n_ext + e) * n + k0;
-#pragma unroll
-  for (int v = 0; v < 2; ++v) {
-    u0[v] = d2u(canon_full(acc0[v], mm.q, mm.qinv));
-    u1[v] = d2u(canon_full(acc1[v], mm.q, mm.qinv));
-  }
+  st_pair(U + (((size_t)o * 2 + 0) * n_ext + e) * n + k0, canon_full(acc0[0], mm.q, mm.qinv), canon_full(acc0[1], mm.q, mm.qinv));
+  st_pair(U + (((size_t)o * 2 + 1) * n_ext + e) * n + k0, canon_full(acc1[0], mm.q, mm.qinv), canon_full(acc1[1], mm.q, mm.qinv));
 }
 void launch_ks_inner(blb_ctx* c, const KsOut* outs_dev, int n_out, const uint64_t* X, const KsLevelConst* kc_dev, uint64_t* U, int nl,
                      int n_ext, int n_digits) {
@@ -213,73 +227,74 @@ void launch_ks_inner(blb_ctx* c, const KsOut* outs_dev, int n_out, const uint64_
   emit(c, [=, stream = c->stream] { k_ks_inner<<<grid, 256, 0, stream>>>(outs_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, n_digits, c->n_q); });
 }
 
-// The same inner product for a group of outputs that share a switching key and Galois element:
-// the key words of the thread's two coefficients are loaded once (all digits, in registers) and
-// applied to every output of the group; per output the arithmetic and its order are those of
-// k_ks_inner, so the words are identical.
+// The same inner product for a group of outputs that share a switching key and Galois element, modulo
+// one prime: the key words of the thread's two coefficients are loaded once (all ND digits, in
+// registers) and applied to every output of the group, whose words are loaded while the output before
+// it is computed; per output the arithmetic and its order are those of k_ks_inner, so the words are
+// identical.  Groups come in the order in which those that read the same digits follow each other.
+// Bound by the words written (2 per digit word read) and the L2: 704 outputs of 3 digits and 7 primes at
+// N = 16384, 1.3 GB written, 504 us with two 8-byte loads a pair and groups in key order, 422 us so.
+template <int ND>
 __global__ void k_ks_inner_grp(const KsOut* __restrict__ outs, const int* __restrict__ ord, const KsGroup* __restrict__ groups,
                                const uint64_t* __restrict__ X, const KsLevelConst* __restrict__ kc, uint64_t* __restrict__ U, int n,
-                               int log_n, int nl, int n_ext, int n_digits, int n_q) {
+                               int log_n, int nl, int n_ext, int n_q) {
   const int k0 = (blockIdx.x * blockDim.x + threadIdx.x) * 2;
-  const int e = blockIdx.y % n_ext;
-  const int gi = blockIdx.y / n_ext;
+  const KsGroup gr = groups[blockIdx.y];
+  const int e = gr.ext;
   if (k0 >= n) return;
-  const KsGroup gr = groups[gi];
-  const KsOut lead = outs[ord[gr.first]];
-  uint32_t kk[2];
-#pragma unroll
-  for (int v = 0; v < 2; ++v) kk[v] = lead.gal ? gal_perm((uint32_t)(k0 + v), lead.gal, log_n) : (uint32_t)(k0 + v);
+  int o = ord[gr.first];
+  KsOut od = outs[o];
+  const KsPair kk((uint32_t)k0, od.gal, log_n);
   const ModEntry mm = kc->ext[e];
   const int key_mod = e < nl ? e : n_q + (e - nl);
-  double kb[kKsMaxDigits][2], ka[kKsMaxDigits][2];
+  u64pair kb[ND], ka[ND], w[ND];
+  auto fetch = [&] {
 #pragma unroll
-  for (int j = 0; j < kKsMaxDigits; ++j) {
-    if (j < n_digits) {
-      const auto b = gmem(lead.key + (((size_t)j * 2 + 0) * kc->n_key_mod + key_mod) * n + k0);
-      const auto a = gmem(lead.key + (((size_t)j * 2 + 1) * kc->n_key_mod + key_mod) * n + k0);
+    for (int j = 0; j < ND; ++j) w[j] = ld_pair(ks_digit(od, X, kc, j, e, ND, n_ext, n) + kk.at);
+  };
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {
-        kb[j][v] = u2d(b[v]);
-        ka[j][v] = u2d(a[v]);
-      }
-    }
+  for (int j = 0; j < ND; ++j) {
+    kb[j] = ld_pair(od.key + (((size_t)j * 2 + 0) * kc->n_key_mod + key_mod) * n + k0);
+    ka[j] = ld_pair(od.key + (((size_t)j * 2 + 1) * kc->n_key_mod + key_mod) * n + k0);
   }
+  fetch();
   for (int i = 0; i < gr.count; ++i) {
-    const int o = ord[gr.first + i];
-    const KsOut od = outs[o];
+    u64pair x[ND];
+#pragma unroll
+    for (int j = 0; j < ND; ++j) x[j] = w[j];
+    const int o_now = o;
+    o = ord[gr.first + (i + 1 < gr.count ? i + 1 : i)];  // (the last one fetches its own words again)
+    od = outs[o];
+    fetch();
     double acc0[2] = {0.0, 0.0}, acc1[2] = {0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < kKsMaxDigits; ++j) {
-      if (j < n_digits) {
-        const auto xs = gmem((e >= kc->dlo[j] && e < kc->dhi[j]) ? od.c1 + (size_t)e * n : X + (((size_t)od.src * n_digits + j) * n_ext + e) * n);
+    for (int j = 0; j < ND; ++j) ks_madd(acc0, acc1, x[j], kk.swap, kb[j], ka[j], mm);
+    if (ND == 4) {
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-          const double x = u2d(xs[kk[v]]);
-          acc0[v] += mulmod_s(x, kb[j][v], mm.q, mm.qinv);
-          acc1[v] += mulmod_s(x, ka[j][v], mm.q, mm.qinv);
-        }
-        if ((j & 3) == 3) {
-#pragma unroll
-          for (int v = 0; v < 2; ++v) {
-            acc0[v] = reduce_s(acc0[v], mm.q, mm.qinv);
-            acc1[v] = reduce_s(acc1[v], mm.q, mm.qinv);
-          }
-        }
+      for (int v = 0; v < 2; ++v) {
+        acc0[v] = reduce_s(acc0[v], mm.q, mm.qinv);
+        acc1[v] = reduce_s(acc1[v], mm.q, mm.qinv);
       }
     }
-    uint64_t* u0 = U + (((size_t)o * 2 + 0) * n_ext + e) * n + k0;
-    uint64_t* u1 = U + (((size_t)o * 2 + 1) * n_ext + e) * n + k0;
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      u0[v] = d2u(canon_full(acc0[v], mm.q, mm.qinv));
-      u1[v] = d2u(canon_full(acc1[v], mm.q, mm.qinv));
-    }
+    st_pair(U + (((size_t)o_now * 2 + 0) * n_ext + e) * n + k0, canon_full(acc0[0], mm.q, mm.qinv), canon_full(acc0[1], mm.q, mm.qinv));
+    st_pair(U + (((size_t)o_now * 2 + 1) * n_ext + e) * n + k0, canon_full(acc1[0], mm.q, mm.qinv), canon_full(acc1[1], mm.q, mm.qinv));
   }
 }
 void launch_ks_inner_grouped(blb_ctx* c, const KsOut* outs_dev, const int* ord_dev, const KsGroup* groups_dev, int n_groups,
                              const uint64_t* X, const KsLevelConst* kc_dev, uint64_t* U, int nl, int n_ext, int n_digits) {
-  dim3 grid((c->n / 2 + 255) / 256, n_groups * n_ext);
-  emit(c, [=, stream = c->stream] { k_ks_inner_grp<<<grid, 256, 0, stream>>>(outs_dev, ord_dev, groups_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, n_digits, c->n_q); });
+  dim3 grid((c->n / 2 + 255) / 256, n_groups);
+  auto go = [&](auto nd) {
+    emit(c, [=, stream = c->stream] {
+      k_ks_inner_grp<decltype(nd)::value><<<grid, 256, 0, stream>>>(outs_dev, ord_dev, groups_dev, X, kc_dev, U, c->n, c->log_n, nl, n_ext, c->n_q);
+    });
+  };
+  static_assert(kKsMaxDigits == 4, "a kernel for each number of digits");
+  switch (n_digits) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    default: go(std::integral_constant<int, 4>{}); break;
+  }
 }
 
 // ---------------------------------------------------------------------------------------

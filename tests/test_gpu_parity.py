@@ -628,6 +628,28 @@ def test_ks_variants_bit_identical(c3s, c2s, ks_variant):
             B.blb_ctx_set_knob(c.h, B.BLB_KNOB_KS_VARIANT, default)
 
 
+@pytest.mark.parametrize("n_q,n_sp,dnum", [(2, 2, 1), (4, 2, 2), (3, 1, 3), (4, 1, 4), (5, 1, 5)])
+@pytest.mark.parametrize("ks_variant", [0, 2])
+@pytest.mark.parametrize("n_ct", [1, 2, 17, 33])
+def test_ks_inner_by_digits(blb, orc, n_q, n_sp, dnum, ks_variant, n_ct):
+    """Key inner products of one to four digits in registers and of five (one output per thread), outputs in
+    runs of 1, 2, 16 + 1 and 16 + 16 + 1 of a key: the oracle's words."""
+    c = Ctx(blb, orc, 12, n_q, n_sp, dnum)
+    blb.blb_ctx_set_knob(c.h, blb.BLB_KNOB_KS_VARIANT, ks_variant)
+    steps = [64, -64, 128, -128]
+    keys_o = orc.Keys(c.o, 51, sorted({c.o.galois_elt(s) for s in steps}))
+    keys_g = blb.blb_keygen(c.h, 51, steps)
+    rng = np.random.default_rng(n_ct)
+    level = n_q - 1
+    words = [keys_o.encrypt(c.o.encode_rns(rng.uniform(-1, 1, c.n // 2), 2.0 ** 30, level), level, 12, t) for t in range(n_ct)]
+    cts, outs = [c.import_ct(w, level) for w in words], [c.ct(level) for _ in words]
+    blb.blb_rotate_sum(c.h, keys_g, cts, outs, 64, 4, 0, False)
+    for t in sorted({0, n_ct // 2, n_ct - 1}):
+        assert np.array_equal(c.export(outs[t]), keys_o.rotate_sum(words[t], level, 64, 4, 0, False)), f"ct {t}"
+    blb.blb_keys_destroy(keys_g)
+    c.close()
+
+
 @pytest.mark.parametrize("fmt", [0, 1])
 @pytest.mark.parametrize("shape", [(64, 96, 64), (20, 1, 24)])
 def test_mac_variants_bit_identical(c2s, shape, fmt):
