@@ -500,10 +500,17 @@ void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind, int most = 
       case 3: launch_ntt_moddown(c, dd, (int)cnt, most, group); break;
       case 4: launch_ntt_addto(c, dd, (int)cnt); break;
       case 5: launch_ntt_modup(c, dd, (int)cnt, most, group); break;
+      case 6: launch_intt_masked(c, dd, (int)cnt); break;
+      case 7: {  // most: the level rescaled from
+        double inv[BLB_MAXQ];
+        for (int i = 0; i < most; ++i) inv[i] = (double)h_inv(c->mod[most] % c->mod[i], c->mod[i]);
+        launch_ntt_rescale_masked(c, dd, (int)cnt, most, inv);
+        break;
+      }
     }
   }
 }
-enum { NTT_FWD = 0, NTT_INV = 1, NTT_RESCALE = 2, NTT_MODDOWN = 3, NTT_ADDTO = 4, NTT_MODUP = 5 };
+enum { NTT_FWD = 0, NTT_INV = 1, NTT_RESCALE = 2, NTT_MODDOWN = 3, NTT_ADDTO = 4, NTT_MODUP = 5, NTT_INV_MASKED = 6, NTT_RESCALE_MASKED = 7 };
 
 // in-place transform of count limb-polys stored back to back ([item][nl][N]); no table upload
 void ntt_regular(blb_ctx* c, uint64_t* base, size_t count, int nl, bool fwd) {
@@ -788,6 +795,39 @@ int rescale_batch(blb_ctx* c, int level, int n_poly, const std::vector<const uin
         d.push_back(x);
       }
   ntt_descs(c, d, NTT_RESCALE);
+  return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
+}
+
+// The same of pairs[t].x (.) mx (+ y (.) my), degree-1 ciphertexts at `level` times evaluation-form masks: the
+// transforms form the products, so the masked ciphertexts are never written (pairs[t].out is not used).
+// 368 pairs of 5 limbs at N = 16384, out of HBM: mask pass, inverse and rescale 300 + 59 + 242 us -> 89 + 324 us in two launches.
+int mask_rescale_batch(blb_ctx* c, int level, const std::vector<CcPair>& pairs, const std::vector<uint64_t*>& out) {
+  const int n = c->n, nl = level + 1;
+  const int T = (int)pairs.size();
+  c->counters[5] += T;
+  Tmp tmp(c);
+  uint64_t* last = tmp.get<uint64_t>((size_t)T * 2 * n);
+  if (tmp.failed) return BLB_ENOMEM;
+  auto masked = [&](PolyDesc x, const CcPair& pr, int p, int i) {
+    x.src2 = pr.x + ((size_t)p * nl + i) * n;
+    x.src3 = pr.y ? pr.y + ((size_t)p * nl + i) * n : nullptr;
+    const uint64_t *mx = pr.mx + (size_t)i * n, *my = pr.y ? pr.my + (size_t)i * n : nullptr;
+    memcpy(&x.aux2, &mx, sizeof(mx));
+    memcpy(&x.aux, &my, sizeof(my));
+    return x;
+  };
+  std::vector<PolyDesc> d;
+  for (int t = 0; t < T; ++t) {
+    c->counters[2] += pairs[t].y ? 2 : 1;
+    for (int p = 0; p < 2; ++p) d.push_back(masked(pd(nullptr, last + ((size_t)t * 2 + p) * n, level, c->log_n), pairs[t], p, level));
+  }
+  ntt_descs(c, d, NTT_INV_MASKED);
+  d.clear();
+  for (int t = 0; t < T; ++t)
+    for (int p = 0; p < 2; ++p)
+      for (int i = 0; i < level; ++i)
+        d.push_back(masked(pd(last + ((size_t)t * 2 + p) * n, out[t] + ((size_t)p * level + i) * n, i, c->log_n), pairs[t], p, i));
+  ntt_descs(c, d, NTT_RESCALE_MASKED, level);
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
 
@@ -2445,7 +2485,6 @@ int cc_steps23_bsgs_dev(blb_ctx* c, const blb_keys* K, const blb_plan* P, const 
   uint64_t* RR = tmp.get<uint64_t>((size_t)(Bb - 1) * m * w1 + 1);
   uint64_t* GL = tmp.get<uint64_t>((size_t)(G - 1) * m * w1 + 1);
   uint64_t* GR = tmp.get<uint64_t>((size_t)(G - 1) * m * w1 + 1);
-  uint64_t* Pre = tmp.get<uint64_t>((size_t)(Bb + G - 1) * m * w1);
   uint64_t* Y = tmp.get<uint64_t>((size_t)Bb * m * w2);
   uint64_t* Ap = tmp.get<uint64_t>((size_t)G * m * w2);
   uint64_t* Oacc = tmp.get<uint64_t>((size_t)g.n_out * w3);
@@ -2498,7 +2537,7 @@ int cc_steps23_bsgs_dev(blb_ctx* c, const blb_keys* K, const blb_plan* P, const 
       CcPair pr;
       pr.mx = P->pt + (size_t)i * nl * n;
       pr.my = P->pt + (size_t)(Bb + i) * nl * n;
-      pr.out = Pre + k * w1;
+      pr.out = nullptr;
       if (i == 0) {
         pr.x = Bs + (size_t)a * w1;
         pr.y = nullptr;
@@ -2507,7 +2546,6 @@ int cc_steps23_bsgs_dev(blb_ctx* c, const blb_keys* K, const blb_plan* P, const 
         pr.y = RR + ((size_t)(i - 1) * m + a) * w1;
       }
       pairs.push_back(pr);
-      rin.push_back(Pre + k * w1);
       rout.push_back(Y + k * w2);
     }
   for (int j = 1; j < G; ++j)
@@ -2518,19 +2556,11 @@ int cc_steps23_bsgs_dev(blb_ctx* c, const blb_keys* K, const blb_plan* P, const 
       pr.my = P->pt_a + (size_t)(G + j) * nl * n;
       pr.x = GL + kg * w1;
       pr.y = GR + kg * w1;
-      pr.out = Pre + k * w1;
+      pr.out = nullptr;
       pairs.push_back(pr);
-      rin.push_back(Pre + k * w1);
       rout.push_back(Ap + ((size_t)j * m + a) * w2);
     }
-  {
-    const CcPair* pairs_dev = upload_vec(c, pairs);
-    if (!pairs_dev) return BLB_EDEVICE;
-    Span sp(c, BLB_T_EW, (double)pairs.size() * w1);
-    for (const CcPair& pr : pairs) c->counters[2] += pr.y ? 2 : 1;
-    launch_mask_pair(c, pairs_dev, (int)pairs.size(), nl);
-  }
-  if ((rc = rescale_batch(c, level, 2, rin, rout))) return rc;
+  if ((rc = mask_rescale_batch(c, level, pairs, rout))) return rc;
   // accumulator index of (output o, giant step j >= 1, half)
   auto acc_idx = [&](int o, int j, int half) { return ((size_t)o * (G - 1) + (j - 1)) * 2 + half; };
   std::vector<char> used((size_t)g.n_out * (G > 1 ? G - 1 : 0) * 2, 0);
@@ -2798,7 +2828,6 @@ static int matmul_cc_call(blb_ctx* c, const blb_keys* K, const blb_plan* P, cons
     uint64_t* Oacc = tmp.get<uint64_t>((size_t)g.n_out * w3);
     uint64_t* RL = tmp.get<uint64_t>((size_t)TC * m * w1);
     uint64_t* RR = tmp.get<uint64_t>((size_t)TC * m * w1);
-    uint64_t* Rpre = tmp.get<uint64_t>((size_t)TC * m * w1);
     uint64_t* R = tmp.get<uint64_t>((size_t)TC * m * w2);
     uint64_t* T3 = tmp.get<uint64_t>((size_t)TC * 3 * nl2 * n);
     uint64_t* Trl = tmp.get<uint64_t>((size_t)TC * w2);
@@ -2824,7 +2853,7 @@ static int matmul_cc_call(blb_ctx* c, const blb_keys* K, const blb_plan* P, cons
           CcPair pr;
           pr.mx = P->pt + (size_t)t * nl * n;
           pr.my = P->pt + (size_t)(lp + t) * nl * n;
-          pr.out = Rpre + slot * w1;
+          pr.out = nullptr;
           if (t == 0) {
             pr.x = b;
             pr.y = nullptr;
@@ -2839,22 +2868,14 @@ static int matmul_cc_call(blb_ctx* c, const blb_keys* K, const blb_plan* P, cons
         }
       }
       if ((rc = ks_apply(c, level, srcs, X, reqs))) return rc;
-      const CcPair* pairs_dev = upload_vec(c, pairs);
-      if (!pairs_dev) return BLB_EDEVICE;
-      {
-        Span sp(c, BLB_T_EW, (double)pairs.size() * w1);
-        for (const CcPair& pr : pairs) c->counters[2] += pr.y ? 2 : 1;
-        launch_mask_pair(c, pairs_dev, (int)pairs.size(), nl);
-      }
       std::vector<const uint64_t*> rin;
       std::vector<uint64_t*> rout;
       std::vector<const uint64_t*> r_tab;
       for (int i = 0; i < nt * m; ++i) {
-        rin.push_back(Rpre + (size_t)i * w1);
         rout.push_back(R + (size_t)i * w2);
         r_tab.push_back(R + (size_t)i * w2);
       }
-      if ((rc = rescale_batch(c, level, 2, rin, rout))) return rc;
+      if ((rc = mask_rescale_batch(c, level, pairs, rout))) return rc;
       // tensor with A (dropped one level) summed over a, one relinearisation per t
       const uint64_t* const* r_dev = upload_vec(c, r_tab);
       if (!r_dev) return BLB_EDEVICE;
@@ -3436,15 +3457,8 @@ static int rotate_sum_call(blb_ctx* c, const blb_keys* K, const blb_ct* in, int 
     run_encode_block(c, block, z, (double)c->mod[level], coef, c->d_flag);
     ntt_plan(c, coef, (uint8_t*)mpt, 1, nl, 0);
     std::vector<CcPair> pairs;
-    for (int t = 0; t < n_ct; ++t) pairs.push_back(CcPair{cur + (size_t)t * ctw, mpt, nullptr, nullptr, cur + (size_t)t * ctw});
-    const CcPair* p_dev = upload_vec(c, pairs);
-    if (!p_dev) return BLB_EDEVICE;
-    {
-      Span sp(c, BLB_T_EW, (double)n_ct * ctw);
-      c->counters[2] += n_ct;
-      launch_mask_pair(c, p_dev, n_ct, nl);
-    }
-    if ((rc = rescale_batch(c, level, 2, rin, rout))) return rc;
+    for (int t = 0; t < n_ct; ++t) pairs.push_back(CcPair{rin[t], mpt, nullptr, nullptr, nullptr});
+    if ((rc = mask_rescale_batch(c, level, pairs, rout))) return rc;
   } else if (!direct) {
     for (int t = 0; t < n_ct; ++t) copy_words(c, rout[t], rin[t], ctw);
   }

@@ -38,6 +38,8 @@ __device__ __forceinline__ uint32_t gal_perm(uint32_t j, uint32_t g, int log_n) 
 
 void launch_ntt(blb_ctx* c, const PolyDesc* d_descs, int count, bool fwd);
 void launch_ntt_rescale(blb_ctx* c, const PolyDesc* d_descs, int count);
+void launch_intt_masked(blb_ctx* c, const PolyDesc* d_descs, int count);
+void launch_ntt_rescale_masked(blb_ctx* c, const PolyDesc* d_descs, int count, int level, const double* inv);
 // ModUp: source limbs of a digit (y_i = [d_i Qhat_i^-1]_{q_i}, coefficient form) -> evaluation form of
 // their base conversion; n_src <= most.  The descriptors of each `group` share their sources.
 void launch_ntt_modup(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group);

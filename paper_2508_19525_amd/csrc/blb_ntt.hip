@@ -404,8 +404,12 @@ __device__ __forceinline__ void ntt_core(double* lds, double (&x)[PT], const dou
 
 template <int LOGN, int PT, bool FWD, class LoadOp>
 __device__ __forceinline__ void ntt_load(double (&x)[PT], const PolyDesc& d, const LoadOp& ld, double q, double qi, int tid) {
+  if constexpr (LoadOp::kAll) {
+    ld.template load_all<LOGN, PT, FWD>(x, d, q, qi, tid);
+  } else {
 #pragma unroll
-  for (int i = 0; i < PT; ++i) x[i] = ld(d, FirstPass<LOGN, PT, FWD>::idx(tid, i), q, qi);
+    for (int i = 0; i < PT; ++i) x[i] = ld(d, FirstPass<LOGN, PT, FWD>::idx(tid, i), q, qi);
+  }
 }
 
 // results of the last pass to global memory, canonical unless the epilogue multiplies them anyway
@@ -458,7 +462,7 @@ __global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_e
   double x[PT];
   ntt_load<LOGN, PT, FWD>(x, d, ld, q, qi, tid);
   ntt_core<LOGN, PT, FWD, false>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid);
-  ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
+  ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && !LoadOp::kAll && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
 }
 
 // Half a polynomial per workgroup (forward, N = 2^(LOGN + 1)): the first stage, x_j +- w x_{j + N/2}, is
@@ -547,7 +551,7 @@ __global__ __launch_bounds__((1 << LOGN) / PT) __attribute__((amdgpu_waves_per_e
       for (int i = 0; i < PF; ++i) nx[i] = ld.raw(dn, First::idx(tid, i));
     };
     ntt_core<LOGN, PT, FWD, true>(lds, x, tw_all + (size_t)d.mod * N, q, qi, tid, prefetch);
-    ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
+    ntt_store<LOGN, PT, FWD>(x, d, st, q, qi, !FWD && !LoadOp::kAll && d.aux2 != 0.0 ? d.aux2 : mt.m[d.mod].ninv, tid, lds);
     p = pn;
     if (p >= count) break;
   }
@@ -609,6 +613,12 @@ void launch_ntt_generic(blb_ctx* c, NttSrc d_descs, int count, LoadOp ld, StoreO
 typedef __attribute__((address_space(1))) uint64_t gu64;
 __device__ __forceinline__ uint64_t gld(const uint64_t* p, int j) { return ((const gu64*)p)[j]; }
 __device__ __forceinline__ void gst(uint64_t* p, int j, uint64_t v) { ((gu64*)p)[j] = v; }
+// words j, j + 1 (ciphertexts need 8-byte alignment only)
+typedef uint64_t u64pair __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ u64pair gld2(const uint64_t* p, int j) { return *(const __attribute__((address_space(1))) u64pair*)((const gu64*)p + j); }
+__device__ __forceinline__ void gst2(uint64_t* p, int j, double a, double b) {
+  *(__attribute__((address_space(1))) u64pair*)((gu64*)p + j) = u64pair{d2u(a), d2u(b)};
+}
 
 // Loads: raw(d, j) fetches word j, cvt() turns it into this pass's double operand.
 // kHalf: k_ntt_half may run it; half_constants() and half() then give the first forward stage's result
@@ -616,6 +626,7 @@ __device__ __forceinline__ void gst(uint64_t* p, int j, uint64_t v) { ((gu64*)p)
 // is scratch that nothing writes meanwhile: both halves read all of it.
 // kPersistent: whether the persistent kernel, which prefetches one raw word per value, may run it.
 struct LdPlain {
+  static constexpr bool kAll = false;
   static constexpr bool kHalf = false;
   static constexpr bool kPersistent = true;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
@@ -637,6 +648,7 @@ struct StPlain {
 };
 // load an integer coefficient (int64) and reduce it into this modulus: plan transforms
 struct LdCoef {
+  static constexpr bool kAll = false;
   static constexpr bool kHalf = false;
   static constexpr bool kPersistent = true;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
@@ -646,6 +658,7 @@ struct LdCoef {
 // load a residue of another modulus (aux = that modulus as double) and lift it centred into
 // this modulus: used by rescale (last limb -> limb i)
 struct LdCentredLift {
+  static constexpr bool kAll = false;
   static constexpr bool kHalf = true;
   static constexpr bool kPersistent = false;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
@@ -662,6 +675,41 @@ struct LdCentredLift {
     return reduce_s(cvt(d, a, q, qi) + mulmod_s(cvt(d, b, q, qi), w, q, qi), q, qi);
   }
 };
+// Masked rescale (a mask product or a sum of two, then the rescale) without the masked ciphertext in
+// memory: the inverse transform of the last limb forms src2 mx + src3 my (src3 may be null) while it reads,
+// and the other limbs' epilogue forms theirs.  The descriptor's aux2 and aux hold the addresses of mx, my.
+__device__ __forceinline__ const uint64_t* mask_of(double bits) { return (const uint64_t*)__double_as_longlong(bits); }
+struct LdMasked {
+  static constexpr bool kAll = true;
+  static constexpr bool kHalf = false;
+  static constexpr bool kPersistent = false;
+  template <int LOGN, int PT, bool FWD>
+  __device__ void load_all(double (&x)[PT], const PolyDesc& d, double q, double qi, int tid) const {
+    auto idx = [&](int i) { return FirstPass<LOGN, PT, FWD>::idx(tid, i); };
+#pragma unroll
+    for (int i = 0; i < PT; ++i) x[i] = mulmod_s(u2d(gld(d.src2, idx(i))), u2d(gld(mask_of(d.aux2), idx(i))), q, qi);
+    if (d.src3)  // uniform over the workgroup (one descriptor)
+#pragma unroll
+      for (int i = 0; i < PT; ++i) x[i] = reduce_s(x[i] + mulmod_s(u2d(gld(d.src3, idx(i))), u2d(gld(mask_of(d.aux), idx(i))), q, qi), q, qi);
+  }
+};
+struct LdLift {  // LdCentredLift with the lifted modulus given once (the descriptors hold the masks)
+  static constexpr bool kAll = false;
+  double q_last;
+  static constexpr bool kHalf = true;
+  static constexpr bool kPersistent = false;
+  __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
+  __device__ double cvt(const PolyDesc&, uint64_t u, double q, double qi) const {
+    const double v = u2d(u);
+    return reduce_s(v > 0.5 * q_last ? v - q_last : v, q, qi);
+  }
+  __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
+  __device__ double half_constants(const PolyDesc&, double w, double, double) const { return w; }
+  __device__ double half(const PolyDesc& d, int j, int H, double w, double q, double qi) const {
+    const uint64_t a = raw(d, j), b = raw(d, j + H);
+    return reduce_s(cvt(d, a, q, qi) + mulmod_s(cvt(d, b, q, qi), w, q, qi), q, qi);
+  }
+};
 // Base conversion (no centring) of n_src limbs into this modulus, sum_i y_i cst_i with y_i < q_i of
 // limb i: the ModUp of a digit and the ModDown of the special limbs, done while the transform reads
 // its operands instead of in a pass of its own that wrote every converted limb and had it read
@@ -670,6 +718,7 @@ struct LdCentredLift {
 // MOST: bound on n_src (1: one limb always); STRIDE: distance of the constants.
 template <int MOST, int STRIDE>
 struct LdConv {
+  static constexpr bool kAll = false;
   static constexpr bool kPersistent = false;
   static constexpr bool kHalf = MOST <= 2;  // more: the stage's constants would not fit the registers
   __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const {
@@ -745,20 +794,17 @@ struct StModDown {
   static constexpr bool kLazy = true;
   static constexpr bool kPersistent = false;
   static constexpr bool kAll = true;
-  typedef uint64_t pair __attribute__((ext_vector_type(2), aligned(8)));
-  typedef __attribute__((address_space(1))) pair gpair;
-  static __device__ pair load(const uint64_t* p, int j) { return *(const gpair*)((const gu64*)p + j); }
   template <int LOGN, int PT, int GS>
   __device__ void put_all(const PolyDesc& d, const int (&j)[PT], const double (&v)[PT], double q, double qi, double*, int) const {
     static_assert(GS % 2 == 0, "runs of pairs");
     constexpr int P = PT / 2;
-    pair u[P], a[P];
+    u64pair u[P], a[P];
     uint32_t swap = 0;
     // (a rotation's element is 1 mod 4, so it keeps the exponents' bit that tells the halves apart)
     const int up = d.flags & kUpperHalf ? 1 << (d.log_n - 1) : 0;
     auto load_add = [&](int m) {
       const int jp = d.gal ? (int)gal_perm((uint32_t)(j[2 * m] + up), d.gal, d.log_n) - up : j[2 * m];
-      a[m] = load(d.src3, jp & ~1);
+      a[m] = gld2(d.src3, jp & ~1);
       swap |= (uint32_t)(jp & 1) << m;
     };
     auto add = [&](double& x, uint64_t y) {
@@ -766,7 +812,7 @@ struct StModDown {
       x = x >= q ? x - q : x;
     };
 #pragma unroll
-    for (int m = 0; m < P; ++m) u[m] = load(d.src2, j[2 * m]);
+    for (int m = 0; m < P; ++m) u[m] = gld2(d.src2, j[2 * m]);
     if (d.src3) {  // uniform over the workgroup (one descriptor)
 #pragma unroll
       for (int m = 0; m < P / 2; ++m) load_add(m);
@@ -786,7 +832,7 @@ struct StModDown {
       }
       if (d.flags & kAddBoth) {
 #pragma unroll
-        for (int m = 0; m < P; ++m) a[m] = load(d.src3, j[2 * m]);
+        for (int m = 0; m < P; ++m) a[m] = gld2(d.src3, j[2 * m]);
 #pragma unroll
         for (int i = 0; i < PT; ++i) add(r[i], a[i / 2][i % 2]);
       }
@@ -797,7 +843,35 @@ struct StModDown {
       }
     }
 #pragma unroll
-    for (int m = 0; m < P; ++m) *(gpair*)((gu64*)d.dst + j[2 * m]) = pair{d2u(r[2 * m]), d2u(r[2 * m + 1])};
+    for (int m = 0; m < P; ++m) gst2(d.dst, j[2 * m], r[2 * m], r[2 * m + 1]);
+  }
+};
+
+// masked rescale epilogue: dst[j] <- (src2[j] mx[j] + src3[j] my[j] - v) * q_l^-1 mod q_i (src3 may be null)
+struct StMaskRescale {
+  double inv[BLB_MAXQ];  // q_l^-1 modulo each prime
+  static constexpr bool kLazy = true;
+  static constexpr bool kPersistent = false;
+  static constexpr bool kAll = true;
+  template <int LOGN, int PT, int GS>
+  __device__ void put_all(const PolyDesc& d, const int (&j)[PT], const double (&v)[PT], double q, double qi, double*, int) const {
+    static_assert(GS % 2 == 0, "runs of pairs");
+    const int up = d.flags & kUpperHalf ? 1 << (d.log_n - 1) : 0;
+    double r[PT];
+    auto add = [&](const uint64_t* x, const uint64_t* m, const double (&to)[PT], double sign) {
+#pragma unroll
+      for (int i = 0; i < PT; i += 2) {
+        const u64pair a = gld2(x, j[i]), b = gld2(m + up, j[i]);
+        r[i] = mulmod_s(u2d(a[0]), u2d(b[0]), q, qi) + sign * to[i];
+        r[i + 1] = mulmod_s(u2d(a[1]), u2d(b[1]), q, qi) + sign * to[i + 1];
+      }
+    };
+    add(d.src2, mask_of(d.aux2), v, -1.0);
+    if (d.src3) add(d.src3, mask_of(d.aux), r, 1.0);  // uniform over the workgroup (one descriptor)
+    const double w = inv[d.mod];
+#pragma unroll
+    for (int i = 0; i < PT; i += 2)  // |r| < 0.875 q + 0.875 q + 1.8 q: |product| < 1.84 q
+      gst2(d.dst, j[i], canon2(mulmod_s(r[i], w, q, qi), q, qi), canon2(mulmod_s(r[i + 1], w, q, qi), q, qi));
   }
 };
 
@@ -885,6 +959,14 @@ void launch_ntt(blb_ctx* c, const PolyDesc* d_descs, int count, bool fwd) {
 }
 void launch_ntt_rescale(blb_ctx* c, const PolyDesc* d_descs, int count) {
   launch_ntt_generic<true>(c, table(c, d_descs), count, LdCentredLift{}, StRescale{});
+}
+void launch_intt_masked(blb_ctx* c, const PolyDesc* d_descs, int count) {
+  launch_ntt_generic<false>(c, table(c, d_descs), count, LdMasked{}, StPlain{});
+}
+void launch_ntt_rescale_masked(blb_ctx* c, const PolyDesc* d_descs, int count, int level, const double* inv) {
+  StMaskRescale st{};
+  for (int i = 0; i < level; ++i) st.inv[i] = inv[i];
+  launch_ntt_generic<true>(c, table(c, d_descs), count, LdLift{(double)c->mod[level]}, st);
 }
 static NttSrc grouped(blb_ctx* c, const PolyDesc* d_descs, int count, int group) {
   return NttSrc{d_descs, nullptr, 1, c->log_n, group, count};

@@ -908,6 +908,31 @@ def test_transforms_in_halves(blb, orc, n_q, n_sp, dnum, radix):
     c.close()
 
 
+@pytest.mark.parametrize("name,block,n_ct", [("c1", 64, 1), ("c1", 512, 3), ("c2s", 1024, 2), ("c3s", 2048, 1), ("c3s", 4096, 3)])
+@pytest.mark.parametrize("radix", [16, 32])
+def test_masked_rescale_in_transforms(request, name, block, n_ct, radix):
+    """The mask product formed by the rescale's transforms (whole limb-polys, and halves at N = 16384): the
+    oracle's rotate-and-sum with the first-block mask, from random residues with 0 and q - 1 among them."""
+    c = request.getfixturevalue(name)
+    c.B.blb_ctx_set_knob(c.h, c.B.BLB_KNOB_NTT_RADIX, radix)
+    keys_o = c.orc.Keys(c.o, 61, sorted({c.o.galois_elt(s) for s in (block, -block)}))
+    keys_g = c.B.blb_keygen(c.h, 61, [block, -block])
+    rng = np.random.default_rng(block + n_ct)
+    level = c.n_q - 1
+    words = []
+    for t in range(n_ct):
+        w = np.stack([np.stack([rng.integers(0, int(q), c.n, dtype=np.uint64) for q in c.o.q[: level + 1]]) for _ in range(2)])
+        w[t % 2, :, 100:200] = (c.o.q[: level + 1] - 1)[:, None]
+        w[t % 2, :, 300:400] = 0
+        words.append(w)
+    cts, outs = [c.import_ct(w, level) for w in words], [c.ct(level - 1) for _ in words]
+    c.B.blb_rotate_sum(c.h, keys_g, cts, outs, block, 2, 0, True)
+    for t in range(n_ct):
+        assert np.array_equal(c.export(outs[t]), keys_o.rotate_sum(words[t], level, block, 2, 0, True)), f"ct {t}"
+    c.B.blb_keys_destroy(keys_g)
+    c.B.blb_ctx_set_knob(c.h, c.B.BLB_KNOB_NTT_RADIX, 16)
+
+
 @pytest.mark.parametrize("n_polys", [85, 86, 130])
 def test_ntt_persistent_grid(c3s, n_polys):
     """The persistent grid (N = 16384, more than two limb-polys per compute unit: 86 and 130 polys of 6 limbs
