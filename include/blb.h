@@ -82,7 +82,8 @@ const char* blb_status_str(int code);
  * When enabled, every launch of the listed kernel families is bracketed by HIP events.
  * blb_ctx_read_timing synchronises the stream and returns, for one family, the summed
  * elapsed milliseconds, the number of launches and the summed work units (polynomials for
- * the NTT family, output ciphertext-limbs x coefficients for the others). */
+ * the NTT family, output ciphertext-limbs x coefficients for the others).  Base conversions and the
+ * mask products before a rescale are part of the transforms: BLB_T_MODUP and BLB_T_MODDOWN stay 0. */
 enum { BLB_T_CP_MAC = 0, BLB_T_NTT = 1, BLB_T_KS_INNER = 2, BLB_T_MODUP = 3, BLB_T_MODDOWN = 4, BLB_T_MASK = 5,
        BLB_T_EW = 6, BLB_T_CC_TENSOR = 7, BLB_T_KINDS = 8 };
 int blb_ctx_set_timing(blb_ctx* ctx, int enable);
