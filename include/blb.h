@@ -70,11 +70,13 @@ int blb_ctx_create(const blb_params* params, blb_ctx** out);
 void blb_ctx_destroy(blb_ctx* ctx);
 /* out: n_q + n_special moduli (q's then p's); synchronises nothing. */
 int blb_ctx_moduli(const blb_ctx* ctx, uint64_t* out);
-/* Library-owned device bytes currently allocated (keys, plans, scratch). */
+/* Library-owned device bytes currently allocated (keys, plans, scratch).  A plan counts with the bytes it
+ * needs; without a budget it may sit in a destroyed plan's block up to a quarter larger. */
 uint64_t blb_ctx_device_bytes(const blb_ctx* ctx);
 /* Synchronises the stream and returns memory kept for later calls to the device: the temporaries of
  * the eager path and the blocks of destroyed matmul_cp plans (at most 1/32 of the device's
- * memory, kept for the next plans and not counted by blb_ctx_device_bytes). */
+ * memory, kept for the next plans and not counted by blb_ctx_device_bytes; a context with a budget
+ * gives them back before it allocates past the budget beside them). */
 int blb_ctx_trim(blb_ctx* ctx);
 const char* blb_status_str(int code);
 

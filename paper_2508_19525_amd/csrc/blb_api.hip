@@ -116,12 +116,12 @@ size_t idle_release(int device, size_t keep) {
   }
   return freed;
 }
-// the smallest idle block that fits and wastes at most a quarter of the request; null if there is none
-void* idle_take(int device, size_t bytes, size_t* got) {
+// the smallest idle block that fits and wastes at most `waste` bytes; null if there is none
+void* idle_take(int device, size_t bytes, size_t waste, size_t* got) {
   std::lock_guard<std::mutex> lk(g_idle_mu);
   auto best = g_idle.end();
   for (auto it = g_idle.begin(); it != g_idle.end(); ++it)
-    if (it->device == device && it->bytes >= bytes && it->bytes - bytes <= bytes / 4 && (best == g_idle.end() || it->bytes < best->bytes))
+    if (it->device == device && it->bytes >= bytes && it->bytes - bytes <= waste && (best == g_idle.end() || it->bytes < best->bytes))
       best = it;
   if (best == g_idle.end()) return nullptr;
   void* p = best->p;
@@ -135,6 +135,11 @@ size_t idle_bytes(int device) {
   for (const IdleBlock& b : g_idle)
     if (b.device == device) held += b.bytes;
   return held;
+}
+
+// Idle blocks count against a context's budget: they are given back where `bytes` more would not fit beside them.
+void idle_fit_budget(blb_ctx* c, size_t bytes) {
+  if (c->budget && c->dev_bytes + idle_bytes(c->device) + bytes > c->budget) (void)idle_release(c->device, 0);
 }
 
 // hipMalloc, giving idle plan memory back when the device has none left
@@ -151,7 +156,7 @@ int dalloc(blb_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) return BLB_OK;
   if (c->budget && c->dev_bytes + bytes > c->budget) return BLB_ENOMEM;
-  if (c->budget && c->dev_bytes + idle_bytes(c->device) + bytes > c->budget) (void)idle_release(c->device, 0);
+  idle_fit_budget(c, bytes);
   if (device_malloc(c->device, p, bytes) != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
@@ -167,12 +172,13 @@ void dfree(blb_ctx* c, void* p, size_t bytes) {
 }
 
 // A plan's plaintexts: an idle block of about the size, else a new one.  *held: the block's bytes
-// (dev_bytes counts the plan's own).
+// (dev_bytes counts the plan's own, so under a budget only a block of exactly that size will do).
 int plan_mem_alloc(blb_ctx* c, void** p, size_t bytes, size_t* held) {
   *p = nullptr;
   if (c->budget && c->dev_bytes + bytes > c->budget) return BLB_ENOMEM;
-  if ((*p = idle_take(c->device, bytes, held))) {
+  if ((*p = idle_take(c->device, bytes, c->budget ? 0 : bytes / 4, held))) {
     c->dev_bytes += bytes;
+    idle_fit_budget(c, 0);
     return BLB_OK;
   }
   *held = bytes;
@@ -224,6 +230,7 @@ void stack_fit(blb_ctx* c, Workspace* w) {
   (void)hipStreamSynchronize(w->stream);
   stack_release(c, w);
   bool ok = !c->budget || c->dev_bytes + cap <= c->budget;
+  if (ok) idle_fit_budget(c, cap);
   if (ok && hipMalloc((void**)&w->base, cap) != hipSuccess) {
     // memory the stream-ordered pool keeps cached may be what is missing: release it, retry
     (void)hipGetLastError();

@@ -1,0 +1,127 @@
+"""Host paths of the library on a machine without a GPU: libblb.so over a HIP runtime of host memory
+(tests/host/hip_stub.cpp), where kernels do not run.  Memory accounting, failures of the runtime or of host
+allocations, and what is launched in which order.
+
+Each case runs in a process of its own (the stub has to be loaded before the library):
+``python test_host_paths_cpu.py STUB CASE``.
+"""
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+sys.path.insert(0, ROOT)
+N = 4096
+
+
+# ---------------------------------------------------------------------------------------
+# cases (run in the child)
+# ---------------------------------------------------------------------------------------
+class Stub:
+    def __init__(self, path):
+        self.l = ctypes.CDLL(path, mode=ctypes.RTLD_GLOBAL)
+        for name in ("stub_live", "stub_peak"):
+            getattr(self.l, name).restype = ctypes.c_size_t
+        for name in ("stub_launch_name", "stub_event"):
+            getattr(self.l, name).restype = ctypes.c_char_p
+        self.l.stub_launch_arg0.restype = ctypes.c_void_p
+        self.l.stub_cap.argtypes = [ctypes.c_size_t]
+        self.l.stub_fail_new.argtypes = [ctypes.c_long]
+
+    def __getattr__(self, name):
+        return getattr(self.l, "stub_" + name)
+
+    def events(self):
+        return [self.l.stub_event(i).decode() for i in range(self.l.stub_events())]
+
+
+def _buf(B, words, level):
+    import numpy as np
+    a = np.zeros(words, np.uint64)
+    c = B.blb_ct(a.ctypes.data, level, 1, 2.0 ** 30)
+    return c, a
+
+
+def _plan(B, h, n_out):
+    """16 x 256 times 256 x 128 n_out at level 1, N = 4096: 16 MiB a column block"""
+    import numpy as np
+    plan = B.blb_plan_matmul_cp(h, np.zeros((256, 128 * n_out)), 16, 1)
+    g = B.blb_plan_info(plan)
+    assert g["n_out"] == n_out
+    return plan, g["n_out"] * g["G"] * g["n_in"] * g["B"] * 2 * N * 8
+
+
+def case_budget_caps_kept_plan_memory(S, B):
+    """What the context holds (plans with their blocks' full size, kept blocks, grown temporaries) stays
+    within hbm_budget_bytes, and a plan of a kept block's size takes that block."""
+    mb = 1 << 20
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    K = B.blb_keygen(h, 1, [64])
+    base = B.blb_ctx_device_bytes(h)
+    B.blb_keys_destroy(K)
+    B.blb_ctx_destroy(h)
+    budget = base + 164 * mb
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None, budget)
+    uncounted = S.live() - B.blb_ctx_device_bytes(h)  # the descriptor ring
+    K = B.blb_keygen(h, 1, [64])
+
+    def check(what):
+        assert S.live() - uncounted <= budget, f"{what}: {(S.live() - uncounted - budget) / mb:.0f} MiB over"
+
+    plan, size = _plan(B, h, 10)
+    check("one plan")
+    B.blb_plan_destroy(plan)
+    before = S.live()
+    plan, same = _plan(B, h, 10)
+    assert same == size and S.live() == before, "the kept block was not taken"
+    B.blb_plan_destroy(plan)
+    # a plan a tenth smaller than the kept block, and one in the bytes that are then left
+    plan, smaller = _plan(B, h, 9)
+    assert size * 4 / 5 <= smaller < size
+    check("a smaller plan")
+    other, _ = _plan(B, h, 1)
+    check("another plan beside it")
+    B.blb_plan_destroy(other)
+    B.blb_plan_destroy(plan)
+    check("kept blocks")
+    # temporaries that grow by about 100 MiB beside kept blocks of 160
+    k = 300
+    a = _buf(B, 2 * k * 4 * N, 1)[1]
+    cts = [[B.blb_ct(a.ctypes.data + (o * k + t) * 4 * N * 8, 1, 1, 2.0 ** 30) for t in range(k)] for o in range(2)]
+    held = B.blb_ctx_device_bytes(h)
+    for _ in range(3):
+        B.blb_rotate_sum(h, K, cts[0], cts[1], 64, 2, 0, False)
+        check("grown temporaries")
+    assert B.blb_ctx_device_bytes(h) >= held + 64 * mb
+    B.blb_keys_destroy(K)
+    B.blb_ctx_destroy(h)
+    assert S.live() == 0
+
+
+# ---------------------------------------------------------------------------------------
+CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "host", "hip_stub.cpp"), "-o", so], check=True)
+    return so
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_host_path(stub, case):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                       text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-3000:]
+
+
+if __name__ == "__main__":
+    S = Stub(sys.argv[1])
+    import paper_2508_19525_amd as B
+    globals()["case_" + sys.argv[2]](S, B)
