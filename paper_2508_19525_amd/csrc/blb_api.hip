@@ -89,7 +89,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // the next plans, oldest given back first beyond 1/32 of the device's memory.  Blocks
 // enter the list after a device synchronisation (as hipFree does), so any context and stream of the
 // device may take them.  All are given back by blb_ctx_trim, with the device's last context, and
-// before an allocation of this library fails for lack of memory.
+// before an allocation of this library (device_malloc, temporaries) fails for lack of memory.
 struct IdleBlock {
   int device;
   void* p;
@@ -140,16 +140,6 @@ size_t idle_bytes(int device) {
 // Idle blocks count against a context's budget: they are given back where `bytes` more would not fit beside them.
 void idle_fit_budget(blb_ctx* c, size_t bytes) {
   if (c->budget && c->dev_bytes + idle_bytes(c->device) + bytes > c->budget) (void)idle_release(c->device, 0);
-}
-
-// hipMalloc, giving idle plan memory back when the device has none left
-hipError_t device_malloc(int device, void** p, size_t bytes) {
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess && idle_release(device, 0) > 0) {
-    (void)hipGetLastError();
-    e = hipMalloc(p, bytes);
-  }
-  return e;
 }
 
 int dalloc(blb_ctx* c, void** p, size_t bytes) {
@@ -348,7 +338,7 @@ Uploader* ring_for(blb_ctx* c) {
   u->stream = c->stream;
   u->cap = kUploadCap;
   if (hipHostMalloc((void**)&u->host, u->cap, hipHostMallocMapped) != hipSuccess ||
-      hipHostGetDevicePointer((void**)&u->mapped, u->host, 0) != hipSuccess || hipMalloc((void**)&u->dev, u->cap) != hipSuccess) {
+      hipHostGetDevicePointer((void**)&u->mapped, u->host, 0) != hipSuccess || device_malloc(c->device, (void**)&u->dev, u->cap) != hipSuccess) {
     (void)hipGetLastError();
     ring_free(u);
     return nullptr;
@@ -864,6 +854,15 @@ void ntt_plan(blb_ctx* c, const uint64_t* coef, uint8_t* out, int count, int nl,
 }
 
 }  // namespace
+
+hipError_t device_malloc(int device, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && idle_release(device, 0) > 0) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
 
 void run_held(blb_ctx* c) {
   Deferred* d = c->defer;

@@ -352,6 +352,8 @@ struct blb_plan {
 // ---------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------
+// hipMalloc, giving kept plan memory back when the device has none left
+hipError_t device_malloc(int device, void** p, size_t bytes);
 // copies the tables of the call so far and runs the launches it holds back
 void run_held(blb_ctx* c);
 // every launch on the context's stream goes through here

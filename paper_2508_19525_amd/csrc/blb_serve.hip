@@ -504,7 +504,7 @@ int blb_server_create(blb_ctx* c, const blb_server_config* cfg, blb_server** out
       delete S;
       return BLB_ENOMEM;
     }
-    if (hipMalloc((void**)&S->arena.base, S->arena.cap) != hipSuccess) {
+    if (device_malloc(c->device, (void**)&S->arena.base, S->arena.cap) != hipSuccess) {
       (void)hipGetLastError();
       delete S;
       return BLB_ENOMEM;
@@ -552,7 +552,7 @@ static int add_weights(blb_server* S, int weight_id, const double* W, int d_in, 
   if (S->weights.count(weight_id)) return BLB_EINVAL;  // a registered weight id is immutable
   const size_t bytes = (size_t)d_in * d_out * 8;
   double* dev = nullptr;
-  if (hipMalloc((void**)&dev, bytes) != hipSuccess) {
+  if (device_malloc(S->c->device, (void**)&dev, bytes) != hipSuccess) {
     (void)hipGetLastError();
     return BLB_ENOMEM;
   }

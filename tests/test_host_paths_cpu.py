@@ -102,6 +102,37 @@ def case_budget_caps_kept_plan_memory(S, B):
     assert S.live() == 0
 
 
+def case_kept_plan_memory_is_given_back_to_any_allocation(S, B):
+    """With the device's memory short of what a new context's descriptor ring, a server's weights or a server's
+    plan arena take, and more than that in a destroyed plan's block, the allocation succeeds."""
+    import numpy as np
+    mb = 1 << 20
+
+    def short_of(bytes_free):
+        S.cap(0)
+        plan, size = _plan(B, h, 10)
+        B.blb_plan_destroy(plan)
+        assert size == 160 * mb
+        S.cap(S.live() + bytes_free)
+
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    short_of(32 * mb)
+    h2 = B.blb_ctx_create(12, 2, 1, 2, 0, 0x5000)  # 64 MiB ring, 2 MiB of tables
+    S.cap(0)
+    h3 = B.blb_ctx_create(12, 2, 1, 2, 0, 0x6000)
+    srv = B.blb_server_create(h2, 1 * mb)
+    short_of(32 * mb)
+    B.blb_server_add_weights(srv, 1, np.zeros((2048, 4096)), 1)  # 64 MiB
+    short_of(32 * mb)
+    srv2 = B.blb_server_create(h3, 64 * mb)
+    for s in (srv, srv2):
+        B.blb_server_destroy(s)
+    S.cap(0)
+    for x in (h, h2, h3):
+        B.blb_ctx_destroy(x)
+    assert S.live() == 0
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
