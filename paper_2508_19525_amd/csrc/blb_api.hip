@@ -460,24 +460,24 @@ struct Span {
 };
 
 // Runs one eager call's body with its launches held back (nothing is held while a graph is being
-// recorded, launches are timed, or an allocation-free call runs).
+// recorded, launches are timed, or an allocation-free call runs).  A launch or copy of the call that failed,
+// held or not, is the runtime's last error and the call's result.
 template <class F>
 int in_call(blb_ctx* c, F&& body) {
-  if (!c || c->defer || c->rec || c->fixed || c->timing) return body();
+  if (!c || c->defer) return body();  // (a call made by another: the outer one reports)
+  const bool hold = !(c->rec || c->fixed || c->timing);
   Deferred d;
-  c->defer = &d;
+  if (hold) c->defer = &d;
   int rc = body();
   run_held(c);
   c->defer = nullptr;
-  if (rc == BLB_OK && (d.failed || hipGetLastError() != hipSuccess)) rc = BLB_EDEVICE;
+  if (rc == BLB_OK && hipGetLastError() != hipSuccess) rc = BLB_EDEVICE;
   return rc;
 }
 
-// device-to-device copy in the order of the launches
+// device-to-device copy in the order of the launches (in_call reports a failure)
 void copy_words(blb_ctx* c, uint64_t* dst, const uint64_t* src, size_t words) {
-  emit(c, [=, stream = c->stream] {
-    if (hipMemcpyAsync(dst, src, words * 8, hipMemcpyDeviceToDevice, stream) != hipSuccess && c->defer) c->defer->failed = true;
-  });
+  emit(c, [=, stream = c->stream] { (void)hipMemcpyAsync(dst, src, words * 8, hipMemcpyDeviceToDevice, stream); });
 }
 
 // descriptor batches can exceed the ring: split into chunks

@@ -202,7 +202,6 @@ struct Deferred {
   static constexpr size_t kMost = 12;  // held launches; the device starts on a long call's first ones meanwhile
   Uploader* ring = nullptr;            // set by the first table of the call
   std::vector<std::function<void()>> ops;
-  bool failed = false;
 };
 
 // Kernel timing spans recorded with HIP events on the context stream (when enabled).

@@ -133,6 +133,31 @@ def case_kept_plan_memory_is_given_back_to_any_allocation(S, B):
     assert S.live() == 0
 
 
+def case_failed_copy_is_the_calls_result(S, B):
+    """A device copy that fails is BLB_EDEVICE from the call that made it, with launches held back and with
+    timing on (nothing held), in the allocation-free rotation too; the next call is not blamed for it."""
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    K = B.blb_keygen(h, 1, [64])
+    x, xa = _buf(B, 4 * N, 1)
+    y, ya = _buf(B, 4 * N, 1)
+    for timing in (0, 1):
+        B.blb_ctx_set_timing(h, timing)
+        for call in (lambda: B.blb_rotate(h, K, x, 0, y), lambda: B.blb_rotate_noalloc(h, K, x, 0, y),
+                     lambda: B.blb_rotate_sum(h, K, [x], [y], 64, 1, 0, False)):
+            S.fail_copies(1)
+            try:
+                call()
+            except B.BlbError as e:
+                assert e.code == B.BLB_EDEVICE
+            else:
+                raise AssertionError("a failed copy was not reported")
+            S.fail_copies(0)
+            B.blb_rotate(h, K, x, 64, y)
+            call()
+    B.blb_keys_destroy(K)
+    B.blb_ctx_destroy(h)
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
