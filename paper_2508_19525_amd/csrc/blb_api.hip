@@ -185,7 +185,11 @@ void plan_mem_free(blb_ctx* c, void* p, size_t bytes, size_t held) {
   }
   (void)idle_release(c->device, c->idle_cap - held);
   std::lock_guard<std::mutex> lk(g_idle_mu);
-  g_idle.push_back(IdleBlock{c->device, p, held});
+  try {
+    g_idle.push_back(IdleBlock{c->device, p, held});
+  } catch (const std::bad_alloc&) {
+    (void)hipFree(p);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -364,12 +368,14 @@ void stage_tables(blb_ctx* c, Uploader& u, bool close) {
   } else if (c->fixed || hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
     ev = nullptr;
   }
-  if (ev) {
-    (void)hipEventRecord(ev, u.stream);
-    u.inflight.push_back(UploadRegion{u.open, u.head, ev});
-  } else {
-    (void)hipStreamSynchronize(u.stream);
+  try {
+    if (ev) u.inflight.push_back(UploadRegion{u.open, u.head, ev});
+  } catch (const std::bad_alloc&) {  // (this runs in destructors)
+    (void)hipEventDestroy(ev);
+    ev = nullptr;
   }
+  if (ev) (void)hipEventRecord(ev, u.stream);
+  else (void)hipStreamSynchronize(u.stream);
   u.open = u.head;
 }
 // Writes `bytes` of a table to the ring of the context's stream; the device region returned holds
@@ -446,6 +452,7 @@ struct Span {
   hipEvent_t a = nullptr;
   Span(blb_ctx* cc, int k, double u) : c(cc), kind(k), units(u) {
     if (c->timing && !c->rec && !c->fixed) {
+      if (c->spans.size() == c->spans.capacity()) c->spans.reserve(2 * c->spans.size() + 16);  // the destructor must not throw
       a = pool_event(c);
       (void)hipEventRecord(a, c->stream);
     }
@@ -461,14 +468,20 @@ struct Span {
 
 // Runs one eager call's body with its launches held back (nothing is held while a graph is being
 // recorded, launches are timed, or an allocation-free call runs).  A launch or copy of the call that failed,
-// held or not, is the runtime's last error and the call's result.
+// held or not, is the runtime's last error and the call's result.  A host allocation that fails (tables and
+// held launches are host containers) is BLB_ENOMEM: what was enqueued by then runs, as for any other error.
 template <class F>
 int in_call(blb_ctx* c, F&& body) {
   if (!c || c->defer) return body();  // (a call made by another: the outer one reports)
   const bool hold = !(c->rec || c->fixed || c->timing);
   Deferred d;
   if (hold) c->defer = &d;
-  int rc = body();
+  int rc;
+  try {
+    rc = body();
+  } catch (const std::bad_alloc&) {
+    rc = BLB_ENOMEM;
+  }
   run_held(c);
   c->defer = nullptr;
   if (rc == BLB_OK && hipGetLastError() != hipSuccess) rc = BLB_EDEVICE;

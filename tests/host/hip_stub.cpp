@@ -15,6 +15,12 @@
 #include <vector>
 
 namespace {
+long new_countdown = 0;  // > 0: that many-th operator new from now, outside this file, throws
+int inside = 0;
+struct Inside {
+  Inside() { ++inside; }
+  ~Inside() { --inside; }
+};
 std::mutex mu;
 std::map<void*, size_t> live;  // device allocations
 size_t live_bytes = 0, peak_bytes = 0, cap_bytes = 0;
@@ -45,6 +51,7 @@ void* map_bytes(size_t n) {
   return p == MAP_FAILED ? nullptr : p;
 }
 hipError_t take(void** p, size_t n) {
+  Inside quiet;
   std::lock_guard<std::mutex> lk(mu);
   if (cap_bytes && live_bytes + n > cap_bytes) return done(hipErrorOutOfMemory);
   if (!(*p = map_bytes(n))) return done(hipErrorOutOfMemory);
@@ -76,11 +83,10 @@ hipError_t handle(T* h) {
   *h = (T)(handles += 16);
   return hipSuccess;
 }
-long new_countdown = 0;  // > 0: that many-th operator new from now throws
 }  // namespace
 
 void* operator new(size_t n) {
-  if (new_countdown > 0 && --new_countdown == 0) throw std::bad_alloc();
+  if (!inside && new_countdown > 0 && --new_countdown == 0) throw std::bad_alloc();
   void* p = malloc(n ? n : 1);
   if (!p) throw std::bad_alloc();
   return p;
@@ -119,6 +125,7 @@ void __hipUnregisterFatBinary(void**) {}
 void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { kernels[host] = name; }
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t s, hipStream_t st) {
+  Inside quiet;
   configs.push_back(Config{g, b, s, st});
   return hipSuccess;
 }
@@ -132,6 +139,7 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* s
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t) {
+  Inside quiet;
   Launch l{kernels[f], grid.x, {}};
   if (l.name.find("k_stage") != std::string::npos) {
     memcpy(*(void**)args[0], *(void**)args[1], (size_t) * (unsigned*)args[2] * 16);
@@ -157,6 +165,7 @@ hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) {
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { return copy(d, s, n); }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  Inside quiet;
   events.push_back("copy");
   return copy(d, s, n);
 }
@@ -187,6 +196,7 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() {
+  Inside quiet;
   events.push_back("wait device");
   if (fail_device_syncs > 0) {
     --fail_device_syncs;
@@ -195,6 +205,7 @@ hipError_t hipDeviceSynchronize() {
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) {
+  Inside quiet;
   events.push_back("wait stream");
   return hipSuccess;
 }

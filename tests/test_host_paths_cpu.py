@@ -158,6 +158,63 @@ def case_failed_copy_is_the_calls_result(S, B):
     B.blb_ctx_destroy(h)
 
 
+def case_failed_host_allocation_is_a_status(S, B):
+    """Every host allocation of an eager call made to fail in turn: the call returns BLB_ENOMEM (no exception
+    crosses the C boundary), and the same call then succeeds with the launches of a call of its own; with
+    launches held back and not (timing)."""
+    L = B.lib()
+    ref = ctypes.byref
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    plan, _ = _plan(B, h, 1)
+    g = B.blb_plan_info(plan)
+    K = B.blb_keygen(h, 1, [64] + [i * g["Lp"] for i in range(1, g["B"])] + [j * g["B"] * g["Lp"] for j in range(1, g["G"])])
+    x = [_buf(B, 4 * N, 1) for _ in range(2)]
+    y = [_buf(B, 4 * N, 1) for _ in range(2)]
+    xa, ya = (B.blb_ct * 2)(*[c for c, _ in x]), (B.blb_ct * 2)(*[c for c, _ in y])
+    calls = {"rotate": lambda: L.blb_rotate(h, K, ref(xa[0]), 64, ref(ya[0])),
+             "rotate_sum": lambda: L.blb_rotate_sum(h, K, xa, 2, 64, 2, 0, 1, ya),
+             "mul_relin": lambda: L.blb_ew_mul_relin(h, K, xa, xa, 2, ya),
+             "scalar_op": lambda: L.blb_scalar_op(h, K, xa, xa, 2, 64, 2, 1, 0, ya),
+             "matmul_cp": lambda: L.blb_matmul_cp(h, K, plan, xa, 2, ya, 1)}
+    K2 = B.blb_keygen(h, 1, [-64])
+    calls["scalar_op"] = lambda: L.blb_scalar_op(h, K2, xa, xa, 2, 64, 2, 1, 0, ya)
+
+    def launched(call):
+        for t in range(2):
+            xa[t].level, ya[t].level = 1, 1
+        S.clear()
+        rc = call()
+        return rc, [S.launch_name(i) for i in range(S.launches()) if b"k_stage" not in S.launch_name(i)]
+
+    for timing in (0, 1):
+        B.blb_ctx_set_timing(h, timing)
+        for name, call in calls.items():
+            launched(call)
+            rc, want = launched(call)
+            assert rc == 0 and want, name
+            failures = 0
+            for k in range(1, 2000):
+                S.fail_new(k)
+                rc, _ = launched(call)
+                S.fail_new(0)
+                if rc == 0:
+                    break
+                assert rc == B.BLB_ENOMEM, (name, k, rc)
+                failures += 1
+                assert launched(call) == (0, want), (name, k)
+            assert failures >= 5, (name, failures)
+    B.blb_ctx_set_timing(h, 0)
+    for k in (K, K2):
+        B.blb_keys_destroy(k)
+    plans = [plan] + [_plan(B, h, 1)[0] for _ in range(40)]
+    for p in plans:  # (the list of kept blocks grows now and then)
+        S.fail_new(1)
+        L.blb_plan_destroy(p)
+        S.fail_new(0)
+    B.blb_ctx_destroy(h)
+    assert S.live() == 0
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
