@@ -180,6 +180,7 @@ void plan_mem_free(blb_ctx* c, void* p, size_t bytes, size_t held) {
   c->dev_bytes -= bytes;
   int cur = -1;
   if (held > c->idle_cap || hipGetDevice(&cur) != hipSuccess || cur != c->device || hipDeviceSynchronize() != hipSuccess) {
+    (void)hipGetLastError();  // (no later call is blamed for a wait that was refused)
     (void)hipFree(p);
     return;
   }

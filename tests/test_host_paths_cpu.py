@@ -215,6 +215,29 @@ def case_failed_host_allocation_is_a_status(S, B):
     assert S.live() == 0
 
 
+def case_refused_wait_of_a_plans_destruction(S, B):
+    """Where the device cannot be waited for (another thread records a graph), a destroyed plan's memory goes
+    back to the device at once, and the next call is not blamed for the refused wait."""
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    K = B.blb_keygen(h, 1, [64])
+    x, xa = _buf(B, 4 * N, 1)
+    y, ya = _buf(B, 4 * N, 1)
+    for _ in range(2):  # (the temporaries grow to their size)
+        plan, size = _plan(B, h, 2)
+        B.blb_plan_destroy(plan)
+        B.blb_ctx_trim(h)
+    plan, size = _plan(B, h, 2)
+    B.blb_rotate(h, K, x, 64, y)
+    held = S.live()
+    S.fail_device_syncs(1)
+    B.blb_plan_destroy(plan)
+    S.fail_device_syncs(0)
+    assert held - S.live() == size
+    B.blb_rotate(h, K, x, 64, y)
+    B.blb_keys_destroy(K)
+    B.blb_ctx_destroy(h)
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
