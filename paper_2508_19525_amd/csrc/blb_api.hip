@@ -494,12 +494,17 @@ void copy_words(blb_ctx* c, uint64_t* dst, const uint64_t* src, size_t words) {
   emit(c, [=, stream = c->stream] { (void)hipMemcpyAsync(dst, src, words * 8, hipMemcpyDeviceToDevice, stream); });
 }
 
-// descriptor batches can exceed the ring: split into chunks
-// (most: source limbs of a base-conversion prologue; group: descriptors in a row that read the same words)
-void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind, int most = 1, int group = 1) {
-  const size_t chunk = 16384;
-  for (size_t off = 0; off < d.size(); off += chunk) {
-    const size_t cnt = std::min(chunk, d.size() - off);
+// descriptor batches can exceed the ring: split into chunks, of whole runs of one length
+// (most: source limbs of a base-conversion prologue; runs: descriptors in a row that read the same words)
+void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind, int most = 1, NttRuns all = {1, 0, 1}) {
+  const size_t chunk = 16384, split = all.split;
+  for (size_t off = 0, cnt; off < d.size(); off += cnt) {
+    cnt = d.size() - off;
+    if (cnt > chunk) {
+      const size_t run = off < split ? all.group : all.tail;
+      cnt = std::min(chunk / run * run, (off < split ? split : d.size()) - off);
+    }
+    const NttRuns runs{all.group, (int)std::min(cnt, split > off ? split - off : 0), all.tail};
     const PolyDesc* dd = (const PolyDesc*)upload(c, d.data() + off, cnt * sizeof(PolyDesc));
     if (!dd) return;
     Span sp(c, BLB_T_NTT, (double)cnt);
@@ -508,9 +513,9 @@ void ntt_descs(blb_ctx* c, const std::vector<PolyDesc>& d, int kind, int most = 
       case 0: launch_ntt(c, dd, (int)cnt, true); break;
       case 1: launch_ntt(c, dd, (int)cnt, false); break;
       case 2: launch_ntt_rescale(c, dd, (int)cnt); break;
-      case 3: launch_ntt_moddown(c, dd, (int)cnt, most, group); break;
+      case 3: launch_ntt_moddown(c, dd, (int)cnt, most, runs); break;
       case 4: launch_ntt_addto(c, dd, (int)cnt); break;
-      case 5: launch_ntt_modup(c, dd, (int)cnt, most, group); break;
+      case 5: launch_ntt_modup(c, dd, (int)cnt, most, runs); break;
       case 6: launch_intt_masked(c, dd, (int)cnt); break;
       case 7: {  // most: the level rescaled from
         double inv[BLB_MAXQ];
@@ -658,19 +663,23 @@ int ks_modup(blb_ctx* c, int level, const std::vector<const uint64_t*>& srcs, ui
   ntt_descs(c, d, NTT_INV);
   c->counters[6] += S;
   d.clear();
-  int most = 1;
+  const int most = kc.dhi[0] - kc.dlo[0], least = kc.dhi[nd - 1] - kc.dlo[nd - 1];  // (the last digit may be shorter)
+  auto push_digit = [&](int s, int j) {
+    for (int e = 0; e < n_ext; ++e) {
+      if (e >= kc.dlo[j] && e < kc.dhi[j]) continue;
+      PolyDesc x = pd(dcoef + ((size_t)s * nl + kc.dlo[j]) * n, X + (((size_t)s * nd + j) * n_ext + e) * n,
+                      e < nl ? e : c->n_q + (e - nl), c->log_n);
+      x.n_src = (int16_t)(kc.dhi[j] - kc.dlo[j]);
+      x.cst = &c->d_kc[level]->qhat_mod[j][0][e];  // a device address, not read here
+      d.push_back(x);
+    }
+  };
+  const int nd_full = least < most ? nd - 1 : nd;
   for (int s = 0; s < S; ++s)
-    for (int j = 0; j < nd; ++j)
-      for (int e = 0; e < n_ext; ++e) {
-        if (e >= kc.dlo[j] && e < kc.dhi[j]) continue;
-        PolyDesc x = pd(dcoef + ((size_t)s * nl + kc.dlo[j]) * n, X + (((size_t)s * nd + j) * n_ext + e) * n,
-                        e < nl ? e : c->n_q + (e - nl), c->log_n);
-        x.n_src = (int16_t)(kc.dhi[j] - kc.dlo[j]);
-        x.cst = &c->d_kc[level]->qhat_mod[j][0][e];  // a device address, not read here
-        most = std::max(most, (int)x.n_src);
-        d.push_back(x);
-      }
-  ntt_descs(c, d, NTT_MODUP, most, n_ext - most);
+    for (int j = 0; j < nd_full; ++j) push_digit(s, j);
+  const int split = (int)d.size();
+  for (int s = 0; s < S && nd_full < nd; ++s) push_digit(s, nd - 1);
+  ntt_descs(c, d, NTT_MODUP, most, NttRuns{n_ext - most, split, n_ext - least});
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
 size_t ks_modup_words(const blb_ctx* c, int level, int n_src) {
@@ -765,7 +774,7 @@ int ks_apply(blb_ctx* c, int level, const std::vector<const uint64_t*>& srcs, co
         x.flags = p == 0 && reqs[o].both ? kAddBoth : 0;
         d.push_back(x);
       }
-  ntt_descs(c, d, NTT_MODDOWN, c->n_sp, nl);
+  ntt_descs(c, d, NTT_MODDOWN, c->n_sp, NttRuns{nl, (int)d.size(), 1});
   return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
 }
 

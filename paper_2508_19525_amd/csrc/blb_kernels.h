@@ -40,11 +40,15 @@ void launch_ntt(blb_ctx* c, const PolyDesc* d_descs, int count, bool fwd);
 void launch_ntt_rescale(blb_ctx* c, const PolyDesc* d_descs, int count);
 void launch_intt_masked(blb_ctx* c, const PolyDesc* d_descs, int count);
 void launch_ntt_rescale_masked(blb_ctx* c, const PolyDesc* d_descs, int count, int level, const double* inv);
+// Descriptors that share their sources stand in a row: runs of `group` among the first `split`, of `tail` after them.
+struct NttRuns {
+  int group, split, tail;
+};
 // ModUp: source limbs of a digit (y_i = [d_i Qhat_i^-1]_{q_i}, coefficient form) -> evaluation form of
-// their base conversion; n_src <= most.  The descriptors of each `group` share their sources.
-void launch_ntt_modup(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group);
+// their base conversion; n_src <= most.  A run is a digit of a source; the digits of fewer limbs come last.
+void launch_ntt_modup(blb_ctx* c, const PolyDesc* d_descs, int count, int most, NttRuns runs);
 // ModDown: special limbs (y_t = [u_t Phat_t^-1]_{p_t}, coefficient form) -> (u_i - conversion) P^-1 + addend
-void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group);
+void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count, int most, NttRuns runs);
 void launch_ntt_addto(blb_ctx* c, const PolyDesc* d_descs, int count);
 // in-place transform of `count` limb-polys stored back to back at base ([item][nl][N]), no
 // descriptor table

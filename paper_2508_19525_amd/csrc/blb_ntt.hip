@@ -32,17 +32,21 @@ struct NttSrc {
   uint64_t* base;
   int nl;
   int log_n;
-  int group = 1;  // runs of this many descriptors read the same words
+  int group = 1;  // runs of this many of the first `split` descriptors read the same words,
+  int split = 0;
+  int tail = 1;   // of this many of the rest
   int count = 0;
   const uint64_t* coef = nullptr;
   size_t out_bytes = 0;
   // Workgroup w of the launch takes descriptor at(w): workgroups go round-robin over the 8 XCDs, so the
   // `group` descriptors of a run are given to workgroups 8 apart and meet in one XCD's L2.
   __device__ __forceinline__ int at(int w) const {
-    if (group <= 1) return w;
-    const int span = 8 * group, base = w / span * span;
-    if (base + span > count) return w;
-    return base + (w - base) % 8 * group + (w - base) / 8;
+    const int lo = w < split ? 0 : split, end = w < split ? split : count, run = w < split ? group : tail;
+    const int span = 8 * run;
+    if (run <= 1 || end - lo < span) return w;
+    const int base = lo + (w - lo) / span * span;
+    if (base + span > end) return w;
+    return base + (w - base) % 8 * run + (w - base) / 8;
   }
   __device__ __forceinline__ PolyDesc get(int w) const { return desc(at(w)); }
   __device__ __forceinline__ PolyDesc desc(int p) const {
@@ -571,6 +575,8 @@ void launch_ntt_pt(blb_ctx* c, NttSrc d_descs, int count, LoadOp ld, StoreOp st)
     if (c->log_n == 14) {
       NttSrc src = d_descs;
       src.group = 2 * src.group;
+      src.split = 2 * src.split;
+      src.tail = 2 * src.tail;
       src.count = 2 * count;
       emit(c, [=, stream = c->stream] { k_ntt_half<13, PT><<<2 * count, threads / 2, 0, stream>>>(src, tw, c->mt, ld, st); });
       return;
@@ -968,17 +974,17 @@ void launch_ntt_rescale_masked(blb_ctx* c, const PolyDesc* d_descs, int count, i
   for (int i = 0; i < level; ++i) st.inv[i] = inv[i];
   launch_ntt_generic<true>(c, table(c, d_descs), count, LdLift{(double)c->mod[level]}, st);
 }
-static NttSrc grouped(blb_ctx* c, const PolyDesc* d_descs, int count, int group) {
-  return NttSrc{d_descs, nullptr, 1, c->log_n, group, count};
+static NttSrc grouped(blb_ctx* c, const PolyDesc* d_descs, int count, NttRuns r) {
+  return NttSrc{d_descs, nullptr, 1, c->log_n, r.group, r.split, r.tail, count};
 }
-void launch_ntt_modup(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group) {
-  const NttSrc src = grouped(c, d_descs, count, group);
+void launch_ntt_modup(blb_ctx* c, const PolyDesc* d_descs, int count, int most, NttRuns runs) {
+  const NttSrc src = grouped(c, d_descs, count, runs);
   if (most <= 1) launch_ntt_generic<true>(c, src, count, LdConv<1, BLB_MAXM>{}, StPlain{});
   else if (most <= 2) launch_ntt_generic<true>(c, src, count, LdConv<2, BLB_MAXM>{}, StPlain{});
   else launch_ntt_generic<true>(c, src, count, LdConv<BLB_MAXALPHA, BLB_MAXM>{}, StPlain{});
 }
-void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count, int most, int group) {
-  const NttSrc src = grouped(c, d_descs, count, group);
+void launch_ntt_moddown(blb_ctx* c, const PolyDesc* d_descs, int count, int most, NttRuns runs) {
+  const NttSrc src = grouped(c, d_descs, count, runs);
   if (most <= 1) launch_ntt_generic<true>(c, src, count, LdConv<1, BLB_MAXQ>{}, StModDown{});
   else if (most <= 2) launch_ntt_generic<true>(c, src, count, LdConv<2, BLB_MAXQ>{}, StModDown{});
   else launch_ntt_generic<true>(c, src, count, LdConv<BLB_MAXSP, BLB_MAXQ>{}, StModDown{});
@@ -989,7 +995,7 @@ void launch_ntt_regular(blb_ctx* c, uint64_t* base, int count, int nl, bool fwd)
   else launch_ntt_generic<false>(c, src, count, LdPlain{}, StPlain{});
 }
 void launch_ntt_plan(blb_ctx* c, const uint64_t* coef, uint8_t* out, int count, int nl, int p50) {
-  NttSrc src{nullptr, (uint64_t*)out, nl, c->log_n, nl, count * nl};  // a plaintext's limbs read the same words
+  NttSrc src{nullptr, (uint64_t*)out, nl, c->log_n, nl, count * nl, 1, count * nl};  // a plaintext's limbs read the same words
   src.coef = coef;
   src.out_bytes = pt_poly_bytes(c->n, p50);
   if (p50) launch_ntt_generic<true>(c, src, count * nl, LdCoef{}, StPack50{});

@@ -238,6 +238,49 @@ def case_refused_wait_of_a_plans_destruction(S, B):
     B.blb_ctx_destroy(h)
 
 
+def case_base_conversions_in_whole_runs(S, B):
+    """The descriptors of every base conversion come in runs that read the same source limbs (the runs that meet
+    in one XCD's L2): the digits of a source at every level, a shorter last digit, launches cut at 16384
+    descriptors, and halves at N = 16384; a launch takes whole runs only."""
+    import struct
+
+    def runs_of(i):
+        """(descriptors, run length of the first `split`, split, run length of the rest) of launch i"""
+        raw = ctypes.string_at(S.launch_arg0(i), 64)
+        descs, _, _, _, group, split, tail, count = struct.unpack_from("<QQiiiiii", raw)
+        k = 2 if b"k_ntt_half" in S.launch_name(i) else 1
+        assert group % k == 0 and split % k == 0 and tail % k == 0 and count == S.launch_grid(i) // k * k
+        d = ctypes.string_at(descs, count // k * 64)
+        return [struct.unpack_from("<Q", d, 64 * j)[0] for j in range(count // k)], group // k, split // k, tail // k
+
+    # uneven digits (2 + 2 + 1 primes; 3 + 2; 4 + 4 + 2), even ones, one prime each
+    for log_n, n_q, n_sp, dnum, cts in ((12, 5, 2, 3, 9), (14, 5, 2, 3, 9), (12, 5, 1, 2, 3), (13, 10, 1, 3, 2), (12, 4, 2, 2, 5),
+                                        (12, 3, 1, 3, 4), (12, 5, 2, 3, 1100)):
+        n = 1 << log_n
+        h = B.blb_ctx_create(log_n, n_q, n_sp, dnum, 0, None)
+        K = B.blb_keygen(h, 1, [64])
+        a = _buf(B, 2 * cts * 2 * n_q * n, 1)[1]
+        for level in range(n_q) if cts < 100 else [n_q - 1]:
+            x, y = [[B.blb_ct(a.ctypes.data + (o * cts + t) * 2 * n_q * n * 8, level, 1, 1.0) for t in range(cts)] for o in range(2)]
+            S.clear()
+            B.blb_rotate_sum(h, K, x, y, 64, 2, 0, False)
+            seen = 0
+            for i in range(S.launches()):
+                if b"LdConv" not in S.launch_name(i):
+                    continue
+                seen += 1
+                src, group, split, tail = runs_of(i)
+                for lo, hi, run in ((0, split, group), (split, len(src), tail)):
+                    assert (hi - lo) % run == 0
+                    for r in range(lo, hi, run):
+                        assert len(set(src[r:r + run])) == 1, (log_n, n_q, dnum, level, S.launch_name(i), r)
+                runs = [src[r] for r in range(0, split, group)] + [src[r] for r in range(split, len(src), tail)]
+                assert len(set(runs)) == len(runs)  # and a run is all of its source's descriptors
+            assert seen >= 2
+        B.blb_keys_destroy(K)
+        B.blb_ctx_destroy(h)
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
