@@ -856,13 +856,16 @@ int check_ct(const blb_ctx* c, const blb_ct* ct) {
   return BLB_OK;
 }
 
-// encode `count` dense slot vectors (device, [count][n_vals]) into integer coefficients coef[count][N]
-int encode_dense_dev(blb_ctx* c, const double* d_vals, int n_vals, int count, double scale, uint64_t* coef) {
+// encode `count` dense slot vectors (device, [count][n_vals]) into integer coefficients coef[count][N] and, if
+// pt is not null, their residues pt[count][nl][N] (enqueued before the wait for the overflow flag, so that the
+// caller's own wait finds them done; not written on overflow)
+int encode_dense_dev(blb_ctx* c, const double* d_vals, int n_vals, int count, double scale, uint64_t* coef, uint64_t* pt = nullptr,
+                     int nl = 0) {
   Tmp tmp(c);
   double* z = tmp.get<double>((size_t)count * (c->n / 2) * 4);
   if (tmp.failed) return BLB_ENOMEM;
-  (void)hipMemsetAsync(c->d_flag, 0, sizeof(int), c->stream);
   run_encode_dense(c, d_vals, n_vals, count, z, scale, coef, c->d_flag);
+  if (pt) launch_coef_residues(c, coef, pt, count, nl, c->d_flag);
   int flag = 0;
   (void)hipMemcpyAsync(&flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream);
   if (hipStreamSynchronize(c->stream) != hipSuccess) return BLB_EDEVICE;
@@ -1375,10 +1378,7 @@ int blb_encode(blb_ctx* c, const double* v, int64_t n_vals, double scale, int le
   if (n_vals > 0 && hipMemcpyAsync(dv, v, n_vals * 8, hipMemcpyHostToDevice, c->stream) != hipSuccess) return BLB_EDEVICE;
   uint64_t* coef = tmp.get<uint64_t>((size_t)c->n);
   if (tmp.failed) return BLB_ENOMEM;
-  const int rc = encode_dense_dev(c, dv, (int)n_vals, 1, scale, coef);
-  if (rc) return rc;
-  launch_coef_residues(c, coef, pt_dev, 1, level + 1);
-  return hipGetLastError() == hipSuccess ? BLB_OK : BLB_EDEVICE;
+  return encode_dense_dev(c, dv, (int)n_vals, 1, scale, coef, pt_dev, level + 1);
 }
 
 int blb_encrypt(blb_ctx* c, const blb_keys* K, const uint64_t* pt_dev, int level, double scale, uint64_t seed, uint32_t ct_id,

@@ -406,7 +406,8 @@ void launch_cp_mac_batch(blb_ctx* c, const MacGroup* groups, const MacItem* item
 // forward NTT of `count` plaintexts' integer coefficients coef[count][N] (int64) into every limb of
 // out[count][nl]: evaluation-form words, or the 50-bit plan format (p50)
 void launch_ntt_plan(blb_ctx* c, const uint64_t* coef, uint8_t* out, int count, int nl, int p50);
-void launch_coef_residues(blb_ctx* c, const uint64_t* coef, uint64_t* out, int count, int nl);
+// (nothing is written where *overflow is set)
+void launch_coef_residues(blb_ctx* c, const uint64_t* coef, uint64_t* out, int count, int nl, const int* overflow);
 void launch_sum_var(blb_ctx* c, const uint64_t* const* srcs, const int* off, uint64_t* const* dsts, int n_out, int nl);
 // out[t] ([2][nl][N]) = k * (the first nl limbs of each poly of in[t], stored with nl_in >= nl limbs)
 void launch_scale_cts(blb_ctx* c, const uint64_t* const* in, uint64_t* out, int count, int nl, double k, int nl_in = 0);
@@ -425,6 +426,7 @@ void launch_set_u64(blb_ctx* c, uint64_t* dst, uint64_t value);
 void launch_zero(blb_ctx* c, uint64_t* dst, size_t words);
 // Encoders: integer coefficients coef[count][N] (int64 in 64-bit words); zbuf: 32 bytes x N/2 per complex
 // vector ((count + 1) / 2 of them for run_encode_cp without g.cplx, which packs two real inputs in each)
+// (clears *d_overflow first)
 int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow);
 int run_encode_block(blb_ctx* c, int block, double* zbuf, double scale, uint64_t* coef, int* d_overflow);
 int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow,

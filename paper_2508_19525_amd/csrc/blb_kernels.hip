@@ -840,20 +840,26 @@ __device__ __forceinline__ void dft_small(cdd (&a)[R], cdd w8) {
 // M1 = 8 R2: n1 = na + R2 nb, k1 = kb + 8 ka,
 //   X[kb + 8 ka] = sum_na e^(-2 pi i na ka / R2) e^(-2 pi i na kb / M1) DFT8_nb(x[na + R2 nb])[kb].
 // Step 1 (work-item (c, na)): the DFT8 over nb and its twiddle, into LDS S[kb][na][c]; step 2
-// (work-item (c, kb), 8 / R2 values of kb each): the DFT of size R2 over na, the four-step twiddle, the
-// store.  CB = 128 / R2, so every work-item has a DFT8 of its own (with 16 columns at every size half
-// of them had none at N = 8192 and three quarters at N = 4096).
-template <class Src, int R2>
-__global__ __launch_bounds__(kEncThreads) void k_enc_cols(Src src, double* zbuf, const double* tw, int M) {
-  constexpr int M1 = 8 * R2, CB = kEncThreads / R2;
+// (work-item (c, kb), CB / 16 values of kb each): the DFT of size R2 over na, the four-step twiddle, the
+// store.  With CB = 128 / R2 every work-item has a DFT8 of its own (of 16 columns half of the work-items
+// have none at N = 8192 and three quarters at N = 4096): right for many vectors.  A few leave most of the GPU
+// idle either way, and 16 columns give them more workgroups and each work-item one DFT of step 2 (a single
+// vector encoded and waited for, with and without the flag's launch of its own that `clear` saves: N = 4096 53.5
+// against 56.8 us, N = 8192 59.8 against 63.9, N = 16384, 16 columns either way, 64.0 against 65.5).
+// clear: the overflow flag, zeroed for the row pass (null: it is kept).
+template <class Src, int R2, int CB>
+__global__ __launch_bounds__(kEncThreads) void k_enc_cols(Src src, double* zbuf, const double* tw, int M, int* clear) {
+  constexpr int M1 = 8 * R2, QN = kEncThreads / CB;
+  static_assert(QN >= R2 && 8 % QN == 0, "work-items of a column");
   __shared__ cdd S[8 * R2 * CB];
   const int n2_0 = blockIdx.x * CB;
   const int p = blockIdx.y;
   const int t = threadIdx.x;
-  const int c = t % CB, q = t / CB;  // q: na in step 1, kb mod R2 in step 2
+  const int c = t % CB, q = t / CB;  // q: na in step 1, kb mod QN in step 2
   const cdd w8 = enc_twiddle(tw, M / 8, M);
   const auto ctx = src.begin(p);
-  {
+  if (clear && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *clear = 0;
+  if (QN == R2 || q < R2) {
     cdd a[8];
 #pragma unroll
     for (int nb = 0; nb < 8; ++nb) a[nb] = src(ctx, kEncM2 * (q + R2 * nb) + n2_0 + c);
@@ -867,8 +873,8 @@ __global__ __launch_bounds__(kEncThreads) void k_enc_cols(Src src, double* zbuf,
   __syncthreads();
   const int n2 = n2_0 + c;
 #pragma unroll
-  for (int i = 0; i < 8 / R2; ++i) {
-    const int kb = q + R2 * i;
+  for (int i = 0; i < 8 / QN; ++i) {
+    const int kb = q + QN * i;
     cdd b[R2];
 #pragma unroll
     for (int na = 0; na < R2; ++na) b[na] = S[(kb * R2 + na) * CB + c];
@@ -986,32 +992,45 @@ __global__ __launch_bounds__(kEncRB * 16) void k_enc_rows(const double* zbuf, co
 
 // integer coefficients -> coefficient-form residues out[p][limb][N] (blb_encode's result; plaintexts
 // that go to evaluation form are reduced by their transforms)
-__global__ void k_coef_residues(const long long* __restrict__ coef, uint64_t* __restrict__ out, int n, int nl, ModTable mt) {
+__global__ void k_coef_residues(const long long* __restrict__ coef, uint64_t* __restrict__ out, int n, int nl, ModTable mt,
+                                const int* __restrict__ overflow) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   const int p = blockIdx.y;
-  if (k >= n) return;
+  if (k >= n || *overflow) return;
   const uint64_t u = (uint64_t)coef[(size_t)p * n + k];
   for (int i = 0; i < nl; ++i) {
     const ModEntry me = mt.m[i];
     out[((size_t)p * nl + i) * n + k] = d2u(canon_full(i64_mod(u, me.q, me.qinv), me.q, me.qinv));
   }
 }
-void launch_coef_residues(blb_ctx* c, const uint64_t* coef, uint64_t* out, int count, int nl) {
+void launch_coef_residues(blb_ctx* c, const uint64_t* coef, uint64_t* out, int count, int nl, const int* overflow) {
   dim3 grid((c->n + 255) / 256, count);
-  emit(c, [=, stream = c->stream] { k_coef_residues<<<grid, 256, 0, stream>>>((const long long*)coef, out, c->n, nl, c->mt); });
+  emit(c, [=, stream = c->stream] { k_coef_residues<<<grid, 256, 0, stream>>>((const long long*)coef, out, c->n, nl, c->mt, overflow); });
 }
 
 // Encodes `count` plaintexts into integer coefficients coef[count][N] (int64; the DFT of the slot
-// values from src, then twist, scale and rounding).  zbuf: [complex vectors][M][4].
+// values from src, then twist, scale and rounding).  zbuf: [complex vectors][M][4].  clear: *d_overflow is
+// zeroed first.
 template <class Src>
-int encode_with(blb_ctx* c, const Src& src, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow, bool paired) {
+int encode_with(blb_ctx* c, const Src& src, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow, bool paired, bool clear) {
   const int M = c->n / 2, M1 = M / kEncM2;
   if (M1 != 16 && M1 != 32 && M1 != 64) return BLB_EINVAL;  // M1 = 8 R2, R2 = 2, 4, 8; M1 >= kEncRB
   const int n_vec = paired ? (count + 1) / 2 : count;  // complex vectors transformed
-  const dim3 gc(kEncM2 * (M1 / 8) / kEncThreads, n_vec), gr(M1 / kEncRB, n_vec);
-  if (M1 == 64) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 8><<<gc, kEncThreads, 0, stream>>>(src, zbuf, c->d_enc_tw, M); });
-  else if (M1 == 32) emit(c, [=, stream = c->stream] { k_enc_cols<Src, 4><<<gc, kEncThreads, 0, stream>>>(src, zbuf, c->d_enc_tw, M); });
-  else emit(c, [=, stream = c->stream] { k_enc_cols<Src, 2><<<gc, kEncThreads, 0, stream>>>(src, zbuf, c->d_enc_tw, M); });
+  const dim3 gr(M1 / kEncRB, n_vec);
+  int* const zero = clear ? d_overflow : nullptr;
+  auto cols = [&](auto r2, auto cb) {
+    constexpr int R2 = decltype(r2)::value, CB = decltype(cb)::value;
+    emit(c, [=, stream = c->stream] {
+      k_enc_cols<Src, R2, CB><<<dim3(kEncM2 / CB, n_vec), kEncThreads, 0, stream>>>(src, zbuf, c->d_enc_tw, M, zero);
+    });
+  };
+  typedef std::integral_constant<int, 16> c16;
+  const bool few = n_vec <= 32;  // 8 workgroups each: they fit the 256 CUs
+  if (M1 == 64) cols(std::integral_constant<int, 8>{}, c16{});
+  else if (M1 == 32 && few) cols(std::integral_constant<int, 4>{}, c16{});
+  else if (M1 == 32) cols(std::integral_constant<int, 4>{}, std::integral_constant<int, 32>{});
+  else if (few) cols(std::integral_constant<int, 2>{}, c16{});
+  else cols(std::integral_constant<int, 2>{}, std::integral_constant<int, 64>{});
   const double sm = scale / (double)M;
   long long* out = (long long*)coef;
   if (paired)
@@ -1025,16 +1044,16 @@ int encode_with(blb_ctx* c, const Src& src, int count, double* zbuf, double scal
   return BLB_OK;
 }
 int run_encode_dense(blb_ctx* c, const double* vals, int n_vals, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow) {
-  return encode_with(c, EncSrcDense{vals, n_vals, c->d_slot_inv}, count, zbuf, scale, coef, d_overflow, false);
+  return encode_with(c, EncSrcDense{vals, n_vals, c->d_slot_inv}, count, zbuf, scale, coef, d_overflow, false, true);
 }
 int run_encode_block(blb_ctx* c, int block, double* zbuf, double scale, uint64_t* coef, int* d_overflow) {
-  return encode_with(c, EncSrcBlock{block, c->d_slot_inv}, 1, zbuf, scale, coef, d_overflow, false);
+  return encode_with(c, EncSrcBlock{block, c->d_slot_inv}, 1, zbuf, scale, coef, d_overflow, false, false);
 }
 int run_encode_cp(blb_ctx* c, const double* W, CpGeom g, int p0, int count, double* zbuf, double scale, uint64_t* coef, int* d_overflow,
                   CpDiag dg) {
   int lLp = 0;
   while ((1 << lLp) < g.Lp) ++lLp;
-  return encode_with(c, EncSrcCp{W, g, p0, count, c->n / 2, lLp, c->d_slot_inv, dg}, count, zbuf, scale, coef, d_overflow, !g.cplx);
+  return encode_with(c, EncSrcCp{W, g, p0, count, c->n / 2, lLp, c->d_slot_inv, dg}, count, zbuf, scale, coef, d_overflow, !g.cplx, false);
 }
 
 // ---------------------------------------------------------------------------------------

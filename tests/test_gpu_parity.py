@@ -959,3 +959,33 @@ def test_ntt_persistent_grid(c3s, n_polys):
         out.append(fwd)
     B.blb_ctx_set_knob(c3s.h, B.BLB_KNOB_NTT_VARIANT, 1)
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("name,L", [("c1", 16), ("c2s", 32)])
+@pytest.mark.parametrize("blocks", [1, 64, 65])
+def test_encoder_few_and_many_vectors(request, name, L, blocks):
+    """Plans of 1, 32 and 33 complex vectors (one plaintext a column block, two a vector): the encoder's column
+    pass takes narrow workgroups up to 32 of them and wide ones beyond; the product is the oracle's."""
+    c = request.getfixturevalue(name)
+    r = _cp_case(c, L, 1, 128 * blocks, c.n_q - 1, 1904)
+    assert r["g"]["n_out"] * r["g"]["G"] * r["g"]["n_in"] * r["g"]["B"] == blocks
+    want = r["keys_o"].matmul_cp(r["X_words"], c.n_q - 1, r["W"], L)
+    for b in range(blocks):
+        assert np.array_equal(c.export(r["Yc"][b]), want[b]), f"output {b}"
+    c.B.blb_plan_destroy(r["plan"])
+    c.B.blb_keys_destroy(r["keys_g"])
+
+
+def test_encode_overflow_leaves_the_plaintext(c1):
+    """A vector whose coefficients pass the encoder's range is refused with the plaintext buffer as it was, and
+    the next vector is encoded."""
+    v = np.random.default_rng(1905).normal(0, 1, c1.n // 2)
+    pt = c1.pt_dev(1)
+    pt.fill_(-7)
+    with pytest.raises(c1.B.BlbError) as e:
+        c1.B.blb_encode(c1.h, v, 2.0 ** 80, 1, pt)
+    assert e.value.code == c1.B.BLB_EINVAL
+    assert bool((pt == -7).all())
+    c1.B.blb_encode(c1.h, v, 2.0 ** 40, 1, pt)
+    torch.cuda.synchronize()
+    assert np.array_equal(pt.cpu().numpy().view(np.uint64).reshape(2, c1.n), c1.o.encode_rns(v, 2.0 ** 40, 1))

@@ -281,6 +281,22 @@ def case_base_conversions_in_whole_runs(S, B):
         B.blb_ctx_destroy(h)
 
 
+def case_encode_waits_once(S, B):
+    """blb_encode waits for the overflow flag with the residues enqueued before it, so that its caller's own
+    wait has nothing left to wait for, and clears the flag without a launch of its own."""
+    import numpy as np
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    v, pt = np.zeros(N // 2), np.zeros(2 * N, np.uint64)
+    for _ in range(2):
+        S.clear()
+        B.blb_encode(h, v, 2.0 ** 30, 1, pt.ctypes.data)
+        ev = S.events()
+    kernels = [e for e in ev if e.startswith("launch")]
+    assert len(kernels) == 3 and "k_coef_residues" in kernels[-1], ev
+    assert ev[-2:] == ["copy", "wait stream"] and ev.count("wait stream") == 1, ev
+    B.blb_ctx_destroy(h)
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
