@@ -961,6 +961,129 @@ def test_ntt_persistent_grid(c3s, n_polys):
     assert np.array_equal(out[0], out[1])
 
 
+# --------------------------------------------------------------------------------------
+# digits of three and more primes, three and four special primes
+# --------------------------------------------------------------------------------------
+@pytest.mark.parametrize("n_q,n_sp,dnum", [(6, 1, 2), (8, 2, 1), (5, 4, 2), (5, 3, 3), (10, 1, 3)])
+@pytest.mark.parametrize("log_n", [12, 13, 14])
+def test_wide_digits(blb, orc, log_n, n_q, n_sp, dnum):
+    """Base conversions of up to eight source primes and of three and four special primes: rotations and a
+    rotate-and-sum over several sources give the oracle's words, from residues with 0 and q - 1 among them, at
+    the levels where the digits are full, where the last one is shorter and where one prime is left."""
+    c = Ctx(blb, orc, log_n, n_q, n_sp, dnum)
+    steps = [64, 128, -3]
+    keys_o = orc.Keys(c.o, 91, sorted({c.o.galois_elt(s) for s in steps}))
+    keys_g = blb.blb_keygen(c.h, 91, steps)
+    rng = np.random.default_rng(100 * log_n + n_q)
+
+    def residues(level, t):
+        w = np.stack([np.stack([rng.integers(0, int(q), c.n, dtype=np.uint64) for q in c.o.q[: level + 1]]) for _ in range(2)])
+        w[1, :, 100 * t:100 * t + 64] = (c.o.q[: level + 1] - 1)[:, None]
+        w[t % 2, :, 2000:2064] = 0
+        w[1, level, 3000:] = int(c.o.q[level]) - 1
+        return w
+
+    for level in sorted({n_q - 1, n_q - 2, (n_q - 1) // 2, 0}):
+        w = residues(level, 0)
+        ct, out = c.import_ct(w, level), c.ct(level)
+        blb.blb_rotate(c.h, keys_g, ct, -3, out)
+        assert np.array_equal(c.export(out), keys_o.rotate(w, level, -3)), f"rotation at level {level}"
+    level = n_q - 1
+    words = [residues(level, t) for t in range(3)]
+    cts, outs = [c.import_ct(w, level) for w in words], [c.ct(level) for _ in words]
+    blb.blb_rotate_sum(c.h, keys_g, cts, outs, 64, 4, 0, False)
+    for t, w in enumerate(words):
+        assert np.array_equal(c.export(outs[t]), keys_o.rotate_sum(w, level, 64, 4, 0, False)), f"ct {t}"
+    blb.blb_keys_destroy(keys_g)
+    c.close()
+
+
+# --------------------------------------------------------------------------------------
+# terms that do not divide over the waves that share them; kept plan memory
+# --------------------------------------------------------------------------------------
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("L,d_in,n_ai", [(4096, 7, 7), (4096, 3, 3), (4096, 1, 1), (2048, 5, 6)])
+@pytest.mark.parametrize("n_bj", [5, 11, 30])
+def test_mac_uneven_terms(c2s, L, d_in, n_ai, n_bj, fmt):
+    """The launch shapes that divide a product's terms over two and four waves (5 and 11 outputs: four, 30: two)
+    with numbers of terms that are no multiple of them, or fewer than the waves, give the words of a shape
+    whose waves take all terms."""
+    B = c2s.B
+    level, c = 2, 4096 // L
+    rng = np.random.default_rng(1900 + n_bj)
+    B.blb_ctx_set_knob(c2s.h, B.BLB_KNOB_PLAN_FORMAT, fmt)
+    try:
+        plan = B.blb_plan_matmul_cp(c2s.h, rng.normal(0, 0.02, (d_in, c * n_bj)), L, level)
+    finally:
+        B.blb_ctx_set_knob(c2s.h, B.BLB_KNOB_PLAN_FORMAT, 0)
+    g = B.blb_plan_info(plan)
+    assert (g["n_in"] * g["B"], g["n_out"] * g["G"]) == (n_ai, n_bj)
+    keys = B.blb_keygen(c2s.h, 1901, [i * g["Lp"] for i in range(1, g["B"])] + [j * g["B"] * g["Lp"] for j in range(1, g["G"])])
+    X = [c2s.ct(level) for _ in range(g["n_in"])]
+    for x in X:
+        B.blb_import(c2s.h, np.stack([np.stack([rng.integers(0, int(q), c2s.n, dtype=np.uint64) for q in c2s.o.q[: level + 1]])
+                                      for _ in range(2)]), x)
+        x.scale = 2.0 ** 40
+    words = []
+    for var in (13, 0):
+        B.blb_ctx_set_knob(c2s.h, B.BLB_KNOB_MAC_VARIANT, var)
+        Y = [c2s.ct(level - 1) for _ in range(g["n_out"])]
+        B.blb_matmul_cp(c2s.h, keys, plan, X, Y)
+        words.append([c2s.export(y) for y in Y])
+    assert all(np.array_equal(a, b) for a, b in zip(*words))
+    torch.cuda.synchronize()
+    B.blb_plan_destroy(plan)
+    B.blb_keys_destroy(keys)
+
+
+@pytest.mark.parametrize("blocks,taken", [(10, True), (9, True), (7, False)])
+def test_plan_in_kept_memory(c1, blocks, taken):
+    """A plan of `blocks` column blocks (16 MiB each) made after one of 10 was destroyed takes its memory where
+    at most a quarter of its own size is wasted, and gives the words of a plan in memory of its own either way.
+    Taken or not is read from the device's free memory, which the temporaries' 35 MiB and their stack change
+    too: less than half of a plan's size (112 to 160 MiB) means that it was taken."""
+    B = c1.B
+    rng = np.random.default_rng(1902)
+    L, d_in, level = 16, 256, 1
+    W = rng.normal(0, 0.02, (d_in, 1280))
+    plan = B.blb_plan_matmul_cp(c1.h, W[:, : 128 * blocks], L, level)
+    g = B.blb_plan_info(plan)
+    assert (g["n_out"], g["G"] * g["n_in"] * g["B"]) == (blocks, 256)
+    keys = B.blb_keygen(c1.h, 1903, [i * g["Lp"] for i in range(1, g["B"])] + [j * g["B"] * g["Lp"] for j in range(1, g["G"])])
+    X = [c1.ct(level) for _ in range(g["n_in"])]
+    for x in X:
+        B.blb_import(c1.h, np.stack([np.stack([rng.integers(0, int(q), c1.n, dtype=np.uint64) for q in c1.o.q[: level + 1]])
+                                     for _ in range(2)]), x)
+        x.scale = 2.0 ** 30
+
+    def product(p):
+        Y = [c1.ct(level - 1) for _ in range(blocks)]
+        B.blb_matmul_cp(c1.h, keys, p, X, Y)
+        return [c1.export(y) for y in Y]
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    want = product(plan)
+    B.blb_plan_destroy(plan)
+    B.blb_ctx_trim(c1.h)
+    first = B.blb_plan_matmul_cp(c1.h, W, L, level)
+    before = free()
+    B.blb_plan_destroy(first)
+    assert free() - before < 80 << 20, "the block was not kept"
+    held = B.blb_ctx_device_bytes(c1.h)
+    plan = B.blb_plan_matmul_cp(c1.h, W[:, : 128 * blocks], L, level)
+    size = blocks * 256 * (level + 1) * c1.n * 8
+    grown = B.blb_ctx_device_bytes(c1.h) - held - size  # the temporaries
+    assert (before - free() - grown < size / 2) == taken
+    got = product(plan)
+    assert all(np.array_equal(a, b) for a, b in zip(want, got))
+    B.blb_plan_destroy(plan)
+    B.blb_keys_destroy(keys)
+    B.blb_ctx_trim(c1.h)
+
+
 @pytest.mark.parametrize("name,L", [("c1", 16), ("c2s", 32)])
 @pytest.mark.parametrize("blocks", [1, 64, 65])
 def test_encoder_few_and_many_vectors(request, name, L, blocks):

@@ -297,6 +297,30 @@ def case_encode_waits_once(S, B):
     B.blb_ctx_destroy(h)
 
 
+def case_kept_blocks_by_size(S, B):
+    """Without a budget a plan takes a destroyed plan's block of its size or at most a quarter of its own size
+    larger; other sizes get memory of their own, and the block waits for the next."""
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    for _ in range(3):  # (the temporaries grow to their size)
+        B.blb_plan_destroy(_plan(B, h, 10)[0])
+    first, size = _plan(B, h, 10)
+    for blocks, taken in ((10, True), (9, True), (8, True), (7, False), (11, False)):
+        held = S.live()
+        B.blb_plan_destroy(first)
+        assert S.live() == held
+        plan, own = _plan(B, h, blocks)
+        assert S.live() - held == (0 if taken else own), blocks
+        B.blb_plan_destroy(plan)
+        B.blb_ctx_trim(h)
+        for _ in range(3):
+            B.blb_plan_destroy(_plan(B, h, 10)[0])
+        first, same = _plan(B, h, 10)
+        assert same == size
+    B.blb_plan_destroy(first)
+    B.blb_ctx_destroy(h)
+    assert S.live() == 0
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
