@@ -142,10 +142,28 @@ void idle_fit_budget(blb_ctx* c, size_t bytes) {
   if (c->budget && c->dev_bytes + idle_bytes(c->device) + bytes > c->budget) (void)idle_release(c->device, 0);
 }
 
+void stack_release(blb_ctx* c, Workspace* w);
+// Whether `bytes` more fit the budget.  The stacks of temporaries that no call uses give way to what a caller
+// keeps (they grow again where there is room; a smaller need of temporaries must not make them the
+// reason for a refusal that a larger one, served by the stream-ordered pool, was not).
+bool budget_fits(blb_ctx* c, size_t bytes) {
+  if (!c->budget || c->dev_bytes + bytes <= c->budget) return true;
+  size_t unused = 0;
+  for (const Workspace* w : c->stacks) unused += w->off == 0 ? w->cap : 0;
+  if (c->dev_bytes - unused + bytes > c->budget) return false;
+  run_held(c);
+  for (Workspace* w : c->stacks)
+    if (w->off == 0 && c->dev_bytes + bytes > c->budget) {
+      (void)hipStreamSynchronize(w->stream);
+      stack_release(c, w);
+    }
+  return true;
+}
+
 int dalloc(blb_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) return BLB_OK;
-  if (c->budget && c->dev_bytes + bytes > c->budget) return BLB_ENOMEM;
+  if (!budget_fits(c, bytes)) return BLB_ENOMEM;
   idle_fit_budget(c, bytes);
   if (device_malloc(c->device, p, bytes) != hipSuccess) {
     *p = nullptr;
@@ -165,7 +183,7 @@ void dfree(blb_ctx* c, void* p, size_t bytes) {
 // (dev_bytes counts the plan's own, so under a budget only a block of exactly that size will do).
 int plan_mem_alloc(blb_ctx* c, void** p, size_t bytes, size_t* held) {
   *p = nullptr;
-  if (c->budget && c->dev_bytes + bytes > c->budget) return BLB_ENOMEM;
+  if (!budget_fits(c, bytes)) return BLB_ENOMEM;
   if ((*p = idle_take(c->device, bytes, c->budget ? 0 : bytes / 4, held))) {
     c->dev_bytes += bytes;
     idle_fit_budget(c, 0);

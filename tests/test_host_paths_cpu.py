@@ -321,6 +321,34 @@ def case_kept_blocks_by_size(S, B):
     assert S.live() == 0
 
 
+def case_temporaries_give_way_to_what_is_kept(S, B):
+    """Under a budget that holds a plan, an executor and the context's tables but not a stack of temporaries
+    beside them, the plan and the executor are made, whatever calls came before."""
+    mb = 1 << 20
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    base = B.blb_ctx_device_bytes(h)
+    B.blb_ctx_destroy(h)
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None, base + 148 * mb)
+    K = B.blb_keygen(h, 1, [16 * i for i in range(1, 16)] + [256 * j for j in range(1, 8)])
+    plan, _ = _plan(B, h, 1)
+    for _ in range(3):
+        B.blb_plan_destroy(plan)
+        plan, _ = _plan(B, h, 1)
+    x = [_buf(B, 4 * N, 1) for _ in range(2)]
+    y, ya = _buf(B, 4 * N, 1)
+    E = B.blb_exec_create_cp(h, K, plan, [c for c, _ in x], [y])
+    for _ in range(2):
+        B.blb_matmul_cp(h, K, plan, [c for c, _ in x], [y])
+    plan2, _ = _plan(B, h, 1)
+    assert B.blb_ctx_device_bytes(h) <= base + 148 * mb
+    B.blb_exec_destroy(E)
+    for p in (plan, plan2):
+        B.blb_plan_destroy(p)
+    B.blb_keys_destroy(K)
+    B.blb_ctx_destroy(h)
+    assert S.live() == 0
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
