@@ -360,7 +360,9 @@ Uploader* ring_for(blb_ctx* c) {
   if (!u) return nullptr;
   u->stream = c->stream;
   u->cap = kUploadCap;
-  if (hipHostMalloc((void**)&u->host, u->cap, hipHostMallocMapped) != hipSuccess ||
+  // coherent: a kernel reads tables that the host wrote after the kernel before it had started, at addresses
+  // that earlier tables had (the runtime's default may leave such lines in a cache)
+  if (hipHostMalloc((void**)&u->host, u->cap, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
       hipHostGetDevicePointer((void**)&u->mapped, u->host, 0) != hipSuccess || device_malloc(c->device, (void**)&u->dev, u->cap) != hipSuccess) {
     (void)hipGetLastError();
     ring_free(u);

@@ -26,6 +26,8 @@ std::map<void*, size_t> live;  // device allocations
 size_t live_bytes = 0, peak_bytes = 0, cap_bytes = 0;
 int fail_copies = 0, fail_device_syncs = 0;
 hipError_t last = hipSuccess;
+size_t largest_host = 0;
+unsigned largest_host_flags = 0;
 std::map<const void*, std::string> kernels;
 struct Launch {
   std::string name;
@@ -105,6 +107,7 @@ void stub_cap(size_t bytes) { cap_bytes = bytes; }
 void stub_fail_copies(int n) { fail_copies = n; }
 void stub_fail_device_syncs(int n) { fail_device_syncs = n; }
 void stub_fail_new(long n) { new_countdown = n; }
+unsigned stub_host_flags() { return largest_host_flags; }  // of the largest pinned allocation
 int stub_last_error() { return (int)last; }
 void stub_clear() {
   launches.clear();
@@ -154,7 +157,10 @@ hipError_t hipMalloc(void** p, size_t n) { return take(p, n); }
 hipError_t hipFree(void* p) { return give(p); }
 hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) { return take(p, n); }
 hipError_t hipFreeAsync(void* p, hipStream_t) { return give(p); }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return (*p = malloc(n)) ? hipSuccess : done(hipErrorOutOfMemory); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) {
+  if (n > largest_host) largest_host = n, largest_host_flags = flags;
+  return (*p = malloc(n)) ? hipSuccess : done(hipErrorOutOfMemory);
+}
 hipError_t hipHostFree(void* p) {
   free(p);
   return hipSuccess;

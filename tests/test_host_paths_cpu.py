@@ -349,6 +349,14 @@ def case_temporaries_give_way_to_what_is_kept(S, B):
     assert S.live() == 0
 
 
+def case_tables_are_in_coherent_memory(S, B):
+    """The ring's host side, which kernels read, is allocated mapped and coherent."""
+    h = B.blb_ctx_create(12, 2, 1, 2, 0, None)
+    mapped, coherent = 0x2, 0x40000000  # hipHostMallocMapped, hipHostMallocCoherent
+    assert S.host_flags() & (mapped | coherent) == mapped | coherent
+    B.blb_ctx_destroy(h)
+
+
 # ---------------------------------------------------------------------------------------
 CASES = [n[len("case_"):] for n in list(globals()) if n.startswith("case_")]
 
