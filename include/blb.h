@@ -105,7 +105,8 @@ enum { BLB_KNOB_MAC_VARIANT = 0, BLB_KNOB_BATCH_VARIANT = 1, BLB_KNOB_BATCH_GRID
  * product; others: a fixed shape, outputs per wave x coefficients per thread x waves that share a
  * tile's terms x waves per workgroup), batch variant 0..BLB_BATCH_VARIANTS-1 (0, the default: by
  * the instances that share a plan; others: a fixed shape, outputs x instances x coefficients per
- * thread), batch grid 1..2^20 workgroups, NTT variant 0..1 (one workgroup per limb-poly, or a
+ * thread; with variant 0 the batch grid and the limb grouping act only on the instances whose plan no other
+ * instance has and whose product is small), batch grid 1..2^20 workgroups, NTT variant 0..1 (one workgroup per limb-poly, or a
  * persistent grid prefetching the next one where that is faster: N = 16384, more than two
  * limb-polys per compute unit; key switches and rescales at that size take half a limb-poly per
  * workgroup either way), NTT radix 16 or 32 (values per

@@ -602,7 +602,6 @@ void build_ks_level(blb_ctx* c, int level, KsLevelConst* k) {
       uint64_t prod = 1;
       for (int i2 = lo; i2 < hi; ++i2)
         if (i2 != i) prod = h_mul(prod, ext[i2] % ext[i], ext[i]);
-      k->qhat_inv[j][i - lo] = (double)h_inv(prod, ext[i]);
       k->qhat_scale[j][i - lo] = prod == 1 ? 0.0 : h_centred(h_inv(h_mul(prod, (uint64_t)c->n, ext[i]), ext[i]), ext[i]);
       for (int e = 0; e < k->n_ext; ++e) {
         uint64_t pm = 1;
@@ -617,7 +616,6 @@ void build_ks_level(blb_ctx* c, int level, KsLevelConst* k) {
     uint64_t prod = 1;
     for (int t2 = 0; t2 < c->n_sp; ++t2)
       if (t2 != t) prod = h_mul(prod, ext[nl + t2] % p, p);
-    k->phat_inv[t] = (double)h_inv(prod, p);
     k->phat_scale[t] = prod == 1 ? 0.0 : h_centred(h_inv(h_mul(prod, (uint64_t)c->n, p), p), p);
     for (int i = 0; i < nl; ++i) {
       uint64_t pm = 1;
@@ -1058,10 +1056,8 @@ int blb_ctx_create(const blb_params* prm, blb_ctx** out) {
   };
   if ((rc = dalloc(c, (void**)&c->d_tw_fwd, sizeof(double) * nm * n))) return fail(rc);
   if ((rc = dalloc(c, (void**)&c->d_tw_inv, sizeof(double) * nm * n))) return fail(rc);
-  if ((rc = dalloc(c, (void**)&c->d_mods, sizeof(uint64_t) * BLB_MAXM))) return fail(rc);
   if (hipMemcpy(c->d_tw_fwd, tw_f.data(), sizeof(double) * nm * n, hipMemcpyHostToDevice) != hipSuccess) return fail(BLB_EDEVICE);
   if (hipMemcpy(c->d_tw_inv, tw_i.data(), sizeof(double) * nm * n, hipMemcpyHostToDevice) != hipSuccess) return fail(BLB_EDEVICE);
-  if (hipMemcpy(c->d_mods, c->mod, sizeof(uint64_t) * BLB_MAXM, hipMemcpyHostToDevice) != hipSuccess) return fail(BLB_EDEVICE);
   // encoder tables (double-double from quad precision)
   {
     const int M = n / 2;
@@ -1125,7 +1121,6 @@ void blb_ctx_destroy(blb_ctx* c) {
   const int nm = c->n_q + c->n_sp;
   dfree(c, c->d_tw_fwd, sizeof(double) * nm * c->n);
   dfree(c, c->d_tw_inv, sizeof(double) * nm * c->n);
-  dfree(c, c->d_mods, sizeof(uint64_t) * BLB_MAXM);
   dfree(c, c->d_enc_tw, sizeof(double) * (c->n / 4) * 4);
   dfree(c, c->d_enc_twist, sizeof(double) * (c->n / 2) * 4);
   dfree(c, c->d_slot_inv, sizeof(int32_t) * (c->n / 2));
@@ -1577,8 +1572,8 @@ int blb_rotate(blb_ctx* c, const blb_keys* K, const blb_ct* in, int32_t steps, b
 }
 
 // blb_rotate with every temporary in the device's fixed scratch array: the key switch's
-// ModUp digits, inner products and ModDown corrections (all written before they are read, so
-// nothing needs clearing).  No allocation of any kind.
+// ModUp digits and inner products (all written before they are read, so nothing needs clearing).  No
+// allocation of any kind.  Refused by a bound with 2 nl limb-polys more than it uses.
 int blb_rotate_noalloc(blb_ctx* c, const blb_keys* K, const blb_ct* in, int32_t steps, blb_ct* out) {
   if (!c || !K || !out || !out->data || check_ct(c, in) || in->degree != 1 || in->data == out->data) return BLB_EINVAL;
   if (c->rec) return BLB_EINVAL;

@@ -44,7 +44,8 @@ __device__ __forceinline__ double mulmod_s(double a, double b, double q, double 
   const double r = __builtin_fma(-t, q, p);
   return r + e;
 }
-// x - round(x/q) q, |result| <= q/2 + tiny, for |x| < 2^52
+// x - round(x/q) q for an integer |x| <= 8 q < 2^53: the quotient estimate is off by less than 2^-48, so
+// |result| < q/2 + 4
 __device__ __forceinline__ double reduce_s(double x, double q, double qinv) {
   const double t = __builtin_rint(x * qinv);
   return __builtin_fma(-t, q, x);
@@ -62,7 +63,7 @@ __device__ __forceinline__ double canon2(double x, double q, double qinv) {
 __device__ __forceinline__ double i64_mod(uint64_t u, double q, double qinv) {
   return mulmod_s((double)(int32_t)(u >> 32), 4294967296.0, q, qinv) + (double)(uint32_t)u;
 }
-// any |x| < 2^52 -> canonical
+// any integer |x| <= 8 q < 2^53 -> canonical
 __device__ __forceinline__ double canon_full(double x, double q, double qinv) { return canon(reduce_s(x, q, qinv), q); }
 
 // ---------------------------------------------------------------------------------------
@@ -87,12 +88,10 @@ struct KsLevelConst {
   int nl, n_ext, n_digits, n_key_mod;
   int dlo[BLB_MAXQ], dhi[BLB_MAXQ];               // digit j covers extended indices [dlo, dhi)
   ModEntry ext[BLB_MAXM];
-  double qhat_inv[BLB_MAXQ][BLB_MAXALPHA];        // [(Q_D/q_i)^-1]_{q_i}
   double qhat_mod[BLB_MAXQ][BLB_MAXALPHA][BLB_MAXM];  // [Q_D/q_i]_{m_e}
-  double phat_inv[BLB_MAXSP];                     // [(P/p_t)^-1]_{p_t}
   double phat_mod[BLB_MAXSP][BLB_MAXQ];           // [P/p_t]_{q_i}
   double p_inv[BLB_MAXQ];                         // [P^-1]_{q_i}
-  // inverse-transform scales: N^-1 times qhat_inv / phat_inv (0 where that factor is 1: plain N^-1)
+  // inverse-transform scales: N^-1 [(Q_D/q_i)^-1]_{q_i} and N^-1 [(P/p_t)^-1]_{p_t} (0 where the factor is 1: plain N^-1)
   double qhat_scale[BLB_MAXQ][BLB_MAXALPHA];
   double phat_scale[BLB_MAXSP];
 };
@@ -264,7 +263,6 @@ struct blb_ctx {
   size_t idle_cap = 0;  // most bytes of destroyed plans' memory kept for new plans (whole device)
   uint64_t mod[BLB_MAXM];
   ModTable mt;
-  uint64_t* d_mods = nullptr;
   double* d_tw_fwd = nullptr;
   double* d_tw_inv = nullptr;
   double* d_enc_tw = nullptr;     // [N/4][4] eta^k (dd complex), eta = exp(2 pi i / (N/2))

@@ -524,6 +524,13 @@ constexpr MacShape kMacShapes[BLB_MAC_VARIANTS] = {
 // {4,4,1,1} 370; 2304: {6,4,1,1} 561, {4,4,1,1} 643, {8,4,1,4} 753 and 1728: {4,4,1,4} 418, {4,4,1,1} 438, {6,4,1,1} 465
 // (both inside the operator); 960: {4,4,2,2} 119, {4,4,1,1} 154; 384: {4,2,4,4} 15.4, {4,4,2,2} 22; 128:
 // {2,2,4,4} 12.6, {4,2,4,4} 14.2.  12 rows only where they pad the outputs by little.
+// Larger products, alone: 64-bit words, N = 8192 (n_ai 48) at 4224 / 8256 / 16512 waves: {12,2,1,1} 313 / 610 / 1208,
+// {8,2,1,1} 328 / 626 / 1249, {8,2,1,4} 327 / 621 / 1231, {12,2,1,4} 308 / 593 / 1181; N = 16384 (n_ai 32) at 4224 / 9216 /
+// 16512: 228-235 / 448 / 852, 233 / 470 / 881, 236 / 469 / 891, 241 / 457 / 846: within 3 % of the best, and of the
+// 256-thread blocks that were the rule before.  50-bit words, 4224-4608 waves: {8,4,1,4} 238-242 (N = 16384), 332-338
+// (N = 8192), {6,4,1,1} 204-217, 292-307; 8064-8256: 353, 566 against 382, 561; 16512: 736, 1056 against 772, 1117; 1536 waves:
+// {4,4,1,4} 120, {4,4,2,2} 112.  So the 50-bit lines at 4096 and 1536 stand too low by these sizes; the points
+// inside the operators above put them there.
 int64_t mac_waves(int n, int nl, int n_bj) { return (int64_t)n * nl / 128 * ((n_bj + 7) / 8); }
 MacShape mac_shape_for(int n, int nl, int n_bj, int p50) {
   const int64_t cols = (int64_t)n * nl;

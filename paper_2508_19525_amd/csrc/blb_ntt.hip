@@ -661,16 +661,18 @@ struct LdCoef {
   __device__ double cvt(const PolyDesc&, uint64_t u, double q, double qi) const { return i64_mod(u, q, qi); }
   __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
 };
-// load a residue of another modulus (aux = that modulus as double) and lift it centred into
-// this modulus: used by rescale (last limb -> limb i)
-struct LdCentredLift {
+// load a residue of another modulus and lift it centred into this modulus: used by rescale (last limb ->
+// limb i).  That modulus is the descriptor's aux, or (GIVEN: the descriptors hold masks) q_last.
+template <bool GIVEN>
+struct LdLift {
+  double q_last;
   static constexpr bool kAll = false;
   static constexpr bool kHalf = true;
   static constexpr bool kPersistent = false;
   __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
   __device__ double cvt(const PolyDesc& d, uint64_t u, double q, double qi) const {
     const double v = u2d(u);
-    const double ql = d.aux;
+    const double ql = GIVEN ? q_last : d.aux;
     const double t = v > 0.5 * ql ? v - ql : v;  // centred, |t| < q_l / 2
     return reduce_s(t, q, qi);
   }
@@ -699,28 +701,16 @@ struct LdMasked {
       for (int i = 0; i < PT; ++i) x[i] = reduce_s(x[i] + mulmod_s(u2d(gld(d.src3, idx(i))), u2d(gld(mask_of(d.aux), idx(i))), q, qi), q, qi);
   }
 };
-struct LdLift {  // LdCentredLift with the lifted modulus given once (the descriptors hold the masks)
-  static constexpr bool kAll = false;
-  double q_last;
-  static constexpr bool kHalf = true;
-  static constexpr bool kPersistent = false;
-  __device__ uint64_t raw(const PolyDesc& d, int j) const { return gld(d.src, j); }
-  __device__ double cvt(const PolyDesc&, uint64_t u, double q, double qi) const {
-    const double v = u2d(u);
-    return reduce_s(v > 0.5 * q_last ? v - q_last : v, q, qi);
-  }
-  __device__ double operator()(const PolyDesc& d, int j, double q, double qi) const { return cvt(d, raw(d, j), q, qi); }
-  __device__ double half_constants(const PolyDesc&, double w, double, double) const { return w; }
-  __device__ double half(const PolyDesc& d, int j, int H, double w, double q, double qi) const {
-    const uint64_t a = raw(d, j), b = raw(d, j + H);
-    return reduce_s(cvt(d, a, q, qi) + mulmod_s(cvt(d, b, q, qi), w, q, qi), q, qi);
-  }
-};
 // Base conversion (no centring) of n_src limbs into this modulus, sum_i y_i cst_i with y_i < q_i of
 // limb i: the ModUp of a digit and the ModDown of the special limbs, done while the transform reads
 // its operands instead of in a pass of its own that wrote every converted limb and had it read
 // back (the conversions' write and read were a third of a key switch's ModDown traffic).  A single
 // limb's constant is 1 and its words, below 2^50, are operands as they are.
+// Wider digits read their limbs once for each limb they give (the runs of descriptors keep that in the L2), and
+// at N = 16384 more than two are converted by whole polynomials; against the pass of its own and the in-place
+// transforms a rotate-and-sum step over 16 / 64 ciphertexts took, two steps, us: 6 primes in digits of 3,
+// 2 special, N = 16384 436 / 1280 -> 230 / 655; 8 in 4, 4 special 502 / 1672 -> 288 / 1012; 8 in 8, 1 special
+// 445 / 1263 -> 270 / 553; 12 in 4, 3 special, N = 8192 482 / 1333 -> 268 / 775.
 // MOST: bound on n_src (1: one limb always); STRIDE: distance of the constants.
 template <int MOST, int STRIDE>
 struct LdConv {
@@ -964,7 +954,7 @@ void launch_ntt(blb_ctx* c, const PolyDesc* d_descs, int count, bool fwd) {
   else launch_ntt_generic<false>(c, table(c, d_descs), count, LdPlain{}, StPlain{});
 }
 void launch_ntt_rescale(blb_ctx* c, const PolyDesc* d_descs, int count) {
-  launch_ntt_generic<true>(c, table(c, d_descs), count, LdCentredLift{}, StRescale{});
+  launch_ntt_generic<true>(c, table(c, d_descs), count, LdLift<false>{}, StRescale{});
 }
 void launch_intt_masked(blb_ctx* c, const PolyDesc* d_descs, int count) {
   launch_ntt_generic<false>(c, table(c, d_descs), count, LdMasked{}, StPlain{});
@@ -972,7 +962,7 @@ void launch_intt_masked(blb_ctx* c, const PolyDesc* d_descs, int count) {
 void launch_ntt_rescale_masked(blb_ctx* c, const PolyDesc* d_descs, int count, int level, const double* inv) {
   StMaskRescale st{};
   for (int i = 0; i < level; ++i) st.inv[i] = inv[i];
-  launch_ntt_generic<true>(c, table(c, d_descs), count, LdLift{(double)c->mod[level]}, st);
+  launch_ntt_generic<true>(c, table(c, d_descs), count, LdLift<true>{(double)c->mod[level]}, st);
 }
 static NttSrc grouped(blb_ctx* c, const PolyDesc* d_descs, int count, NttRuns r) {
   return NttSrc{d_descs, nullptr, 1, c->log_n, r.group, r.split, r.tail, count};
