@@ -203,12 +203,15 @@ void plan_mem_free(blb_ctx* c, void* p, size_t bytes, size_t held) {
     return;
   }
   (void)idle_release(c->device, c->idle_cap - held);
-  std::lock_guard<std::mutex> lk(g_idle_mu);
-  try {
-    g_idle.push_back(IdleBlock{c->device, p, held});
-  } catch (const std::bad_alloc&) {
-    (void)hipFree(p);
+  {
+    std::lock_guard<std::mutex> lk(g_idle_mu);
+    try {
+      g_idle.push_back(IdleBlock{c->device, p, held});
+    } catch (const std::bad_alloc&) {
+      (void)hipFree(p);
+    }
   }
+  (void)idle_release(c->device, c->idle_cap);  // (another thread's block may have joined the list in between)
 }
 
 // ------------------------------------------------------------------------------------------

@@ -8,6 +8,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <sys/mman.h>
+#include <condition_variable>
 #include <map>
 #include <mutex>
 #include <new>
@@ -16,16 +17,19 @@
 
 namespace {
 long new_countdown = 0;  // > 0: that many-th operator new from now, outside this file, throws
-int inside = 0;
+thread_local int inside = 0;
 struct Inside {
   Inside() { ++inside; }
   ~Inside() { --inside; }
 };
-std::mutex mu;
+std::recursive_mutex mu;
+size_t total_bytes = size_t(288) << 30;
+int meet = 0, met = 0;  // device waits that return together
 std::map<void*, size_t> live;  // device allocations
 size_t live_bytes = 0, peak_bytes = 0, cap_bytes = 0;
 int fail_copies = 0, fail_device_syncs = 0;
-hipError_t last = hipSuccess;
+std::condition_variable_any together;
+thread_local hipError_t last = hipSuccess;
 size_t largest_host = 0;
 unsigned largest_host_flags = 0;
 std::map<const void*, std::string> kernels;
@@ -41,7 +45,7 @@ struct Config {
   size_t shared;
   hipStream_t stream;
 };
-std::vector<Config> configs;
+thread_local std::vector<Config> configs;
 intptr_t handles = 0x1000;
 
 hipError_t done(hipError_t e) {
@@ -54,7 +58,7 @@ void* map_bytes(size_t n) {
 }
 hipError_t take(void** p, size_t n) {
   Inside quiet;
-  std::lock_guard<std::mutex> lk(mu);
+  std::lock_guard<std::recursive_mutex> lk(mu);
   if (cap_bytes && live_bytes + n > cap_bytes) return done(hipErrorOutOfMemory);
   if (!(*p = map_bytes(n))) return done(hipErrorOutOfMemory);
   live[*p] = n;
@@ -64,7 +68,7 @@ hipError_t take(void** p, size_t n) {
 }
 hipError_t give(void* p) {
   if (!p) return hipSuccess;
-  std::lock_guard<std::mutex> lk(mu);
+  std::lock_guard<std::recursive_mutex> lk(mu);
   const auto it = live.find(p);
   if (it == live.end()) return done(hipErrorInvalidValue);
   live_bytes -= it->second;
@@ -104,6 +108,8 @@ size_t stub_peak(int reset) {
   return p;
 }
 void stub_cap(size_t bytes) { cap_bytes = bytes; }
+void stub_total(size_t bytes) { total_bytes = bytes; }
+void stub_meet(int n) { meet = n, met = 0; }
 void stub_fail_copies(int n) { fail_copies = n; }
 void stub_fail_device_syncs(int n) { fail_device_syncs = n; }
 void stub_fail_new(long n) { new_countdown = n; }
@@ -143,6 +149,7 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* s
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t) {
   Inside quiet;
+  std::lock_guard<std::recursive_mutex> lk(mu);
   Launch l{kernels[f], grid.x, {}};
   if (l.name.find("k_stage") != std::string::npos) {
     memcpy(*(void**)args[0], *(void**)args[1], (size_t) * (unsigned*)args[2] * 16);
@@ -172,6 +179,7 @@ hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) {
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { return copy(d, s, n); }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
   Inside quiet;
+  std::lock_guard<std::recursive_mutex> lk(mu);
   events.push_back("copy");
   return copy(d, s, n);
 }
@@ -198,12 +206,19 @@ hipError_t hipGetDevice(int* d) {
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   memset(p, 0, sizeof(*p));
   p->multiProcessorCount = 256;
-  p->totalGlobalMem = size_t(288) << 30;
+  p->totalGlobalMem = total_bytes;
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() {
   Inside quiet;
+  std::unique_lock<std::recursive_mutex> lk(mu);
   events.push_back("wait device");
+  if (meet) {
+    const int target = (met / meet + 1) * meet;
+    ++met;
+    together.notify_all();
+    together.wait(lk, [&] { return met >= target; });
+  }
   if (fail_device_syncs > 0) {
     --fail_device_syncs;
     return done(hipErrorStreamCaptureUnsupported);
@@ -212,6 +227,7 @@ hipError_t hipDeviceSynchronize() {
 }
 hipError_t hipStreamSynchronize(hipStream_t) {
   Inside quiet;
+  std::lock_guard<std::recursive_mutex> lk(mu);
   events.push_back("wait stream");
   return hipSuccess;
 }

@@ -29,7 +29,7 @@ class Stub:
         for name in ("stub_launch_name", "stub_event"):
             getattr(self.l, name).restype = ctypes.c_char_p
         self.l.stub_launch_arg0.restype = ctypes.c_void_p
-        self.l.stub_cap.argtypes = [ctypes.c_size_t]
+        self.l.stub_cap.argtypes = self.l.stub_total.argtypes = [ctypes.c_size_t]
         self.l.stub_fail_new.argtypes = [ctypes.c_long]
 
     def __getattr__(self, name):
@@ -355,6 +355,33 @@ def case_tables_are_in_coherent_memory(S, B):
     mapped, coherent = 0x2, 0x40000000  # hipHostMallocMapped, hipHostMallocCoherent
     assert S.host_flags() & (mapped | coherent) == mapped | coherent
     B.blb_ctx_destroy(h)
+
+
+def case_kept_memory_is_bounded_with_several_threads(S, B):
+    """Threads that destroy plans at the same moment (their waits for the device return together) keep no more
+    than 1/32 of the device's memory between them, every time."""
+    import threading
+    mb = 1 << 20
+    n, cap = 8, 40 * mb  # two plans of 16 MiB
+    S.total(32 * cap)
+    hs = [B.blb_ctx_create(12, 2, 1, 2, 0, 0x1000 * (t + 1)) for t in range(n)]
+    for h in hs:  # (the temporaries grow to their size)
+        for _ in range(3):
+            B.blb_plan_destroy(_plan(B, h, 1)[0])
+    for _ in range(200):
+        plans = [_plan(B, h, 1)[0] for h in hs]
+        rest = S.live() - n * 16 * mb
+        S.meet(n)
+        threads = [threading.Thread(target=B.blb_plan_destroy, args=(p,)) for p in plans]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        S.meet(0)
+        assert S.live() - rest <= cap, f"{(S.live() - rest) / mb:.0f} MiB kept"
+    for h in hs:
+        B.blb_ctx_destroy(h)
+    assert S.live() == 0
 
 
 # ---------------------------------------------------------------------------------------
